@@ -198,6 +198,86 @@ __device__ __forceinline__ void roots4(const float* c, float* x) {
   for (int i = 0; i < 3; ++i) x[i + 1] = quartic_newton(c, x3[i], 2);
 }
 
+// roots3 in two steps: roots3_raw leaves x[1] and x[2] for the Newton steps (polish3; not where the
+// degree dropped, returned true).
+__device__ __forceinline__ bool roots3_raw(const float* c, float* x) {
+  float scale = fabsf(c[0]) + fabsf(c[1]) + fabsf(c[2]) + fabsf(c[3]);
+  if (!(fabsf(c[3]) > 1e-12f * scale)) {
+    // degree drop: one atom at infinity (zero weight)
+    roots2(c, x);
+    x[2] = copysignf(1e30f, -c[2] * c[3]);
+    return true;
+  }
+  float inv = fast_rcp(c[3]);
+  float a = c[2] * inv, b = c[1] * inv, cc = c[0] * inv;
+  float a3 = a * (1.f / 3.f);
+  float q = a3 * a3 - b * (1.f / 3.f);
+  float r = a3 * a3 * a3 - 0.5f * a3 * b + 0.5f * cc;
+  q = fmaxf(q, 0.f);
+  float sq = fast_sqrt(q);
+  float den = q * sq;
+  float arg = den > 0.f ? fminf(fmaxf(r * fast_rcp(den), -1.f), 1.f) : 0.f;
+  // the trigonometric roots only seed the Newton steps below, so a short
+  // arccosine (Abramowitz & Stegun 4.4.45, |error| < 7e-5) and the hardware
+  // cosine are accurate enough
+  const float aa = fabsf(arg);
+  float ac = fast_sqrt(1.f - aa) * (1.5707288f + aa * (-0.2121144f + aa * (0.0742610f + aa * -0.0187293f)));
+  ac = arg < 0.f ? 3.14159265358979f - ac : ac;
+  float th = ac * (1.f / 3.f);
+  const float two_pi_3 = 2.0943951023931953f;
+  float big = 0.f;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    float xk = -2.f * sq * __cosf(th + two_pi_3 * (float)k) - a3;
+    big = fabsf(xk) > fabsf(big) ? xk : big;
+  }
+  big = cubic_newton(c, big, 2);
+  // p(x) = (x - big)(A x^2 + B x + C), matched from the constant term up
+  float ib = fast_rcp(big);
+  float cq = -c[0] * ib;
+  float bq = (cq - c[1]) * ib;
+  float aq = (bq - c[2]) * ib;
+  float qc[3] = {cq, bq, aq};
+  float x2[2];
+  roots2(qc, x2);
+  x[0] = big;
+  x[1] = x2[0];
+  x[2] = x2[1];
+  return false;
+}
+__device__ __forceinline__ float polish3(const float* c, float x) { return cubic_newton(c, x, 2); }
+// roots4 likewise: roots4_raw leaves x[1..3] for the steps on the quartic (polish4; not where the
+// degree dropped, returned true).
+__device__ __forceinline__ bool roots4_raw(const float* c, float* x) {
+  float scale = fabsf(c[0]) + fabsf(c[1]) + fabsf(c[2]) + fabsf(c[3]) + fabsf(c[4]);
+  if (!(fabsf(c[4]) > 1e-12f * scale)) {
+    roots3(c, x);
+    x[3] = copysignf(1e30f, -c[3] * c[4]);
+    return true;
+  }
+  float inv = fast_rcp(c[4]);
+  float a[4] = {c[0] * inv, c[1] * inv, c[2] * inv, c[3] * inv};
+  float mean = -0.25f * a[3];
+  float var = fmaxf(0.25f * (a[3] * a[3] - 2.f * a[2]) - mean * mean, 0.f);
+  float half = fast_sqrt(3.f * var) * 1.0001f + 1e-6f * (fabsf(mean) + 1.f);
+  float hi = laguerre4(a, mean + half, 4);
+  float lo = laguerre4(a, mean - half, 4);
+  float big = quartic_newton(c, fabsf(hi) >= fabsf(lo) ? hi : lo, 1);
+  // p(x) = (x - big)(A x^3 + B x^2 + C x + D), matched from the constant term up
+  float ib = fast_rcp(big);
+  float d = -c[0] * ib;
+  float cc = (d - c[1]) * ib;
+  float b = (cc - c[2]) * ib;
+  float aa = (b - c[3]) * ib;
+  float qc[4] = {d, cc, b, aa};
+  float x3[3];
+  roots3(qc, x3);
+  x[0] = big;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) x[i + 1] = x3[i];
+  return false;
+}
+__device__ __forceinline__ float polish4(const float* c, float x) { return quartic_newton(c, x, 2); }
 template <int NH>
 __device__ __forceinline__ void kernel_roots(const float* c, float* x) {
   static_assert(NH >= 2 && NH <= 4, "two to four atoms besides the query");
@@ -207,6 +287,21 @@ __device__ __forceinline__ void kernel_roots(const float* c, float* x) {
     roots3(c, x);
   else
     roots4(c, x);
+}
+
+// x[0..3] sorted: the smallest two and the largest
+__device__ __forceinline__ void sort4(const float* x, float& s0, float& s1, float& s3) {
+  s0 = fminf(x[0], x[1]);
+  s1 = fmaxf(x[0], x[1]);
+  float s2 = fminf(x[2], x[3]);
+  s3 = fmaxf(x[2], x[3]);
+  float t = fminf(s0, s2);
+  s2 = fmaxf(s0, s2);
+  s0 = t;
+  t = fmaxf(s1, s3);
+  s1 = fminf(s1, s3);
+  s3 = t;
+  s1 = fminf(s1, s2);
 }
 
 // sum_{x_i < y} w_i from the count of atoms below y: the weights of the
@@ -237,18 +332,8 @@ __device__ __forceinline__ float mass_below(const LInv<NH>& L, float y, float w0
     const float ws = weight(cnt <= 1 ? lo : hi);
     return cnt == 0 ? 0.f : (cnt == 1 ? ws : (cnt == 2 ? 1.f - w0 - ws : 1.f - w0));
   } else {
-    // sorting network: s0 <= s1 <= s2 <= s3
-    float s0 = fminf(x[0], x[1]), s1 = fmaxf(x[0], x[1]);
-    float s2 = fminf(x[2], x[3]), s3 = fmaxf(x[2], x[3]);
-    float t = fminf(s0, s2);
-    s2 = fmaxf(s0, s2);
-    s0 = t;
-    t = fmaxf(s1, s3);
-    s1 = fminf(s1, s3);
-    s3 = t;
-    t = fminf(s1, s2);
-    s2 = fmaxf(s1, s2);
-    s1 = t;
+    float s0, s1, s3;
+    sort4(x, s0, s1, s3);
     const float wa = weight(cnt <= 2 ? s0 : s3);
     const float wb = weight(s1);
     return cnt == 0 ? 0.f
@@ -256,18 +341,71 @@ __device__ __forceinline__ float mass_below(const LInv<NH>& L, float y, float w0
   }
 }
 
-// Normalised interpolated bound F(y) = sum_{x_i<y} w_i + beta w_0.
+// Normalised interpolated bound F(y) = sum_{x_i<y} w_i + beta w_0. The value is
+// canon_at's to the last bit (the backward pass forms the same optical depths
+// again), but only the atom whose weight enters is finished: the others' last
+// Newton steps, and for NH = 2 the other zero and the comparisons, are left out
+// (K(y, y) > 0, so the two atoms lie on either side of y exactly when the
+// leading coefficient is negative, else both on the side of their mean).
 template <int NH>
 __device__ __forceinline__ float bound_F(const LInv<NH>& L, float y, float beta) {
-  float z[NH + 1], c[NH + 1], x[NH];
+  float z[NH + 1], c[NH + 1];
   linv_apply<NH>(L, y, z);
   float zz = z[0] * z[0];
 #pragma unroll
   for (int i = 1; i <= NH; ++i) zz = fmaf(z[i], z[i], zz);
   const float w0 = fast_rcp(zz);
   linv_t_apply<NH>(L, z, c);
-  kernel_roots<NH>(c, x);
-  return mass_below<NH>(L, y, w0, x) + beta * w0;
+  // a weight lies in [0, 1] (the first polynomial is 1); the clamp, an output
+  // modifier of the reciprocal, also turns the NaN of an atom at infinity into 0
+  auto weight = [&](float xs) __attribute__((always_inline)) {
+    return __builtin_amdgcn_fmed3f(christoffel<NH>(L, xs), 0.f, 1.f);
+  };
+  float mass;
+  if constexpr (NH == 2) {
+    // where the zeros enclose y they are apart, and the discriminant is positive
+    const float sq = fast_sqrt(c[1] * c[1] - 4.f * c[2] * c[0]);
+    const float q = -0.5f * (c[1] + copysignf(sq, c[1]));
+    const bool pos = c[1] >= 0.f;
+    const float lo = (pos ? c[0] : q) * fast_rcp(pos ? q : c[2]);  // the lower zero where c2 < 0
+    const float ws = weight(lo);
+    const float all = fmaf(2.f * c[2], y, c[1]) > 0.f ? 1.f - w0 : 0.f;
+    mass = c[2] < 0.f ? ws : all;
+  } else if constexpr (NH == 3) {
+    float x[3];
+    const bool drop = roots3_raw(c, x);
+    int cnt = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      x[i] = x[i] == x[i] ? x[i] : 1e30f;
+      cnt += x[i] < y ? 1 : 0;
+    }
+    float xs = cnt <= 1 ? fminf(fminf(x[0], x[1]), x[2]) : fmaxf(fmaxf(x[0], x[1]), x[2]);
+    const float xp = polish3(c, xs);
+    xs = drop || xs == x[0] ? xs : xp;
+    const float ws = weight(xs);
+    mass = cnt == 0 ? 0.f : (cnt == 1 ? ws : (cnt == 2 ? 1.f - w0 - ws : 1.f - w0));
+  } else {
+    float x[4];
+    const bool drop = roots4_raw(c, x);
+    const float big = x[0];
+    int cnt = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[i] = x[i] == x[i] ? x[i] : 1e30f;
+      cnt += x[i] < y ? 1 : 0;
+    }
+    float s0, s1, s3;
+    sort4(x, s0, s1, s3);
+    float xa = cnt <= 2 ? s0 : s3;
+    const float xap = polish4(c, xa), xbp = polish4(c, s1);
+    xa = drop || xa == big ? xa : xap;
+    s1 = drop || s1 == big ? s1 : xbp;
+    const float wa = weight(xa), wb = weight(s1);
+    mass = cnt == 0 ? 0.f
+                    : (cnt == 1 ? wa : (cnt == 2 ? wa + wb : (cnt == 3 ? 1.f - w0 - wa : 1.f - w0)));
+  }
+  return mass + beta * w0;
 }
 
 // Canonical representation at y with its atoms (for the adjoint): returns F
@@ -443,10 +581,10 @@ __device__ __forceinline__ void normal_moments(double m, double v, double* nm) {
   for (int k = 2; k < NK; ++k) nm[k] = m * nm[k - 1] + (double)(k - 1) * v * nm[k - 2];
 }
 
-// Returns the mixture weight eps used (0: none; -1: identity factor) and the
-// moments the factor belongs to in bmix[0..2 NH].
+// The factor in lc; returns the mixture weight eps used (0: none; -1: identity
+// factor) and the moments the factor belongs to in bmix[0..2 NH].
 template <int NH>
-__device__ __forceinline__ double hankel_factor(const double* b, LInv<NH>& out, double* bmix) {
+__device__ __forceinline__ double hankel_lower(const double* b, double (&lc)[NH + 1][NH + 1], double* bmix) {
   constexpr int M = NH + 1;
   constexpr int NK = 2 * NH + 1;
   const double mean = b[1], var = b[2] - b[1] * b[1];
@@ -473,8 +611,8 @@ __device__ __forceinline__ double hankel_factor(const double* b, LInv<NH>& out, 
       c[k] = acc * sk;
     }
     normal_moments<NK>(0.0, 1.0, sn);
-    double lc[M][M];
-    if (hankel_chol<M>(c, lc)) {
+    double ls[M][M];
+    if (hankel_chol<M>(c, ls)) {
       eps = 0.0;
     } else {
 #pragma unroll 1
@@ -482,7 +620,7 @@ __device__ __forceinline__ double hankel_factor(const double* b, LInv<NH>& out, 
         double cm[NK];
 #pragma unroll
         for (int k = 0; k < NK; ++k) cm[k] = (1.0 - kMixEps[l]) * c[k] + kMixEps[l] * sn[k];
-        if (hankel_chol<M>(cm, lc)) eps = kMixEps[l];
+        if (hankel_chol<M>(cm, ls)) eps = kMixEps[l];
       }
     }
   }
@@ -491,7 +629,6 @@ __device__ __forceinline__ double hankel_factor(const double* b, LInv<NH>& out, 
 #pragma unroll
   for (int k = 0; k < NK; ++k) bmix[k] = eps > 0.0 ? (1.0 - eps) * b[k] + eps * nm[k] : b[k];
   // the factor in the pixel's moment variable
-  double lc[M][M];
 #pragma unroll
   for (int i = 0; i < M; ++i)
 #pragma unroll
@@ -523,6 +660,15 @@ __device__ __forceinline__ double hankel_factor(const double* b, LInv<NH>& out, 
 #pragma unroll
       for (int j = 0; j < M; ++j) lc[i][j] = i == j ? 1.0 : 0.0;
   }
+  return eps;
+}
+
+// The factor kept as L^-1.
+template <int NH>
+__device__ __forceinline__ double hankel_factor(const double* b, LInv<NH>& out, double* bmix) {
+  constexpr int M = NH + 1;
+  double lc[M][M];
+  const double eps = hankel_lower<NH>(b, lc, bmix);
   // invert the lower-triangular factor
   double li[M][M];
 #pragma unroll
@@ -567,6 +713,158 @@ __device__ __forceinline__ void mixture_adjoint(const double* b, double eps, dou
   // mean = b_1, var = b_2 - b_1^2
   D[1] += eps * (gm - 2.0 * mean * gv);
   D[2] += eps * gv;
+}
+
+// ---------------------------------------------------------------------------
+// The bounds at the nodes of the tabulated schedule, whose frames no backward
+// pass follows (bound_F keeps the bits of the adjoint's F). F alone needs less
+// than the canonical representation with all its atoms:
+//
+//  - The Hankel factor is kept as the three-term recurrence of the monic
+//    orthogonal polynomials in the standardised variable s = (y - mean) / sd:
+//    pi_0 = 1, pi_1 = s, pi_{k+1} = (s - alpha_k) pi_k - beta_k pi_{k-1}, with
+//    1 / h_k (h_k the squared norm of pi_k; h_0 = h_1 = 1): 3 (n - 1) numbers
+//    where L^-1 has (n + 1)(n + 2) / 2.
+//  - The other atoms are the zeros of K(s, x) = sum_k pi_k(s) pi_k(x) / h_k in
+//    x. With x = s + 1 / v they become the zeros of the monic polynomial
+//    v^n + (k_1 v^(n-1) + .. + k_n) / k_0, k_j the Taylor coefficients of
+//    K(s, .) at s: its leading coefficient k_0 = K(s, s) = 1 / w_0 never
+//    vanishes, and an atom sent to infinity is the zero v = 0. All zeros are
+//    real, so the sign changes in the coefficients count the atoms above s
+//    exactly (Descartes), without any zero.
+//  - The weights sum to 1, so the mass below s needs the lone atom's weight on
+//    the smaller side only (none when all atoms lie on one side). For n = 3 one
+//    zero is solved for, the largest after a change of sign that puts the lone
+//    atom there, where Newton steps from above are monotone.
+// n = 2 and 3 (four and six moments).
+// ---------------------------------------------------------------------------
+template <int NH>
+struct Orth {
+  float l1, l2;                            // s = l2 y + l1
+  float al[NH - 1], be[NH - 1], ih[NH - 1];  // alpha_k, beta_k, 1 / h_{k+1}, k = 1..NH-1
+};
+
+// From the Cholesky factor of the Hankel matrix: alpha_k = L_{k+1,k} / L_kk -
+// L_{k,k-1} / L_{k-1,k-1} and h_k = L_kk^2 in the moment variable, mapped by
+// s = (y - alpha_0) / L_11. The identity factor (eps < 0; polynomials y^k) takes
+// beta = 0, h = 1.
+template <int NH>
+__device__ __forceinline__ double hankel_orth(const double* b, Orth<NH>& o) {
+  constexpr int M = NH + 1;
+  double lc[M][M], bmix[2 * NH + 1];
+  const double eps = hankel_lower<NH>(b, lc, bmix);
+  const bool id = eps < 0.0;
+  const double is = 1.0 / lc[1][1];
+  const double mean = lc[1][0];
+  double r = mean;  // L_{k,k-1} / L_{k-1,k-1}
+  o.l1 = (float)(-mean * is);
+  o.l2 = (float)is;
+  double be = 1.0, h = 1.0;  // beta_k, h_k
+#pragma unroll
+  for (int k = 1; k < NH; ++k) {
+    const double ik = 1.0 / lc[k][k];
+    const double rn = lc[k + 1][k] * ik;
+    o.al[k - 1] = (float)(((rn - r) - mean) * is);
+    o.be[k - 1] = id ? 0.f : (float)be;
+    r = rn;
+    const double up = lc[k + 1][k + 1] * ik * is;  // sqrt(beta_{k+1})
+    be = up * up;
+    h *= be;
+    o.ih[k - 1] = id ? 1.f : (float)(1.0 / h);
+  }
+  return eps;
+}
+
+// pi_0..pi_n at s
+template <int NH>
+__device__ __forceinline__ void orth_eval(const Orth<NH>& o, float s, float* pi) {
+  pi[0] = 1.f;
+  pi[1] = s;
+#pragma unroll
+  for (int k = 1; k < NH; ++k) {
+    const float e = s - o.al[k - 1];
+    pi[k + 1] = k == 1 ? fmaf(e, s, -o.be[0]) : fmaf(e, pi[k], -o.be[k - 1] * pi[k - 1]);
+  }
+}
+
+// Christoffel weight of an atom at x (an atom at infinity has none; a zero
+// that is no number, from the identity factor's polynomials, counts as one)
+template <int NH>
+__device__ __forceinline__ float orth_weight(const Orth<NH>& o, float x) {
+  float pi[NH + 1];
+  orth_eval<NH>(o, x, pi);
+  float z = fmaf(x, x, 1.f);
+#pragma unroll
+  for (int k = 2; k <= NH; ++k) z = fmaf(pi[k] * o.ih[k - 2], pi[k], z);
+  const float w = fast_rcp(z);
+  return w <= 1.f ? w : 0.f;
+}
+
+// Largest zero of v^3 + A v^2 + B v - C (C >= 0, all zeros real, the other two
+// not positive). The trigonometric solution needs cos(acos(x) / 3), x in
+// [-1, 1], here a cubic in sqrt((1 + x) / 2) (error 9e-5), then two Newton
+// steps; the start is kept above a small fraction of the zeros' spread, clear
+// of the stationary point between a tiny zero (an atom far away, of negligible
+// weight) and its neighbour.
+__device__ __forceinline__ float cubic_top(float A, float B, float C) {
+  const float a3 = A * (1.f / 3.f);
+  const float q = fmaxf(fmaf(a3, a3, B * (-1.f / 3.f)), 0.f);
+  const float sq = fast_sqrt(q);
+  const float r = fmaf(a3, fmaf(a3, a3, B * -0.5f), C * -0.5f);  // half the cubic at its inflection point
+  const float x = -r * fast_rcp(q * sq);                          // cos of the angle (clamped below)
+  const float y = fast_sqrt(__builtin_amdgcn_fmed3f(fmaf(x, 0.5f, 0.5f), 0.f, 1.f));
+  const float f = fmaf(y, fmaf(y, fmaf(y, 0.022022f, -0.09735423f), 0.57541675f), 0.5f);
+  float v = fmaxf(fmaf(2.f * sq, f, -a3), 1e-3f * sq);
+#pragma unroll
+  for (int it = 0; it < 2; ++it) {
+    const float p = fmaf(fmaf(v + A, v, B), v, -C);
+    const float dp = fmaf(fmaf(3.f, v, 2.f * A), v, B);
+    v = fmaf(-p, fast_rcp(dp), v);
+  }
+  return v;
+}
+
+// Normalised interpolated bound F = sum_{x_i < s} w_i + beta w_0 at the
+// standardised query s.
+template <int NH>
+__device__ __forceinline__ float orth_F(const Orth<NH>& o, float s, float beta) {
+  static_assert(NH == 2 || NH == 3, "two or three atoms besides the query");
+  if constexpr (NH == 2) {
+    // K(s, x) = c0 + c1 x + c2 x^2; K(s, s) > 0, so the atoms lie on either side of
+    // s exactly when c2 < 0
+    const float pi2 = fmaf(s - o.al[0], s, -o.be[0]);
+    const float c2 = pi2 * o.ih[0];
+    const float c0 = fmaf(-o.be[0], c2, 1.f);
+    const float h1 = 0.5f * fmaf(-o.al[0], c2, s);  // c1 / 2
+    const float w0 = fast_rcp(fmaf(pi2, c2, fmaf(s, s, 1.f)));
+    const float sq = fast_sqrt(fabsf(fmaf(h1, h1, -c2 * c0)));
+    const float q = -(h1 + copysignf(sq, h1));
+    const bool pos = h1 >= 0.f;
+    const float lo = (pos ? c0 : q) * fast_rcp(pos ? q : c2);  // the lower zero, for c2 < 0
+    const float wl = orth_weight<NH>(o, lo);
+    const float all = fmaf(s, c2, h1) > 0.f ? 1.f - w0 : 0.f;  // c2 >= 0: the zeros' mean -h1 / c2 against s
+    return fmaf(beta, w0, c2 < 0.f ? wl : all);
+  } else {
+    float pi[4];
+    orth_eval<NH>(o, s, pi);
+    // pi_k' and pi_k'' / 2 by the recurrence
+    const float d2 = (s - o.al[0]) + s;
+    const float e2 = s - o.al[1];
+    const float d3 = fmaf(e2, d2, pi[2]) - o.be[1];
+    const float h3 = e2 + d2;
+    const float g2 = pi[2] * o.ih[0], g3 = pi[3] * o.ih[1];
+    const float w0 = fast_rcp(fmaf(pi[3], g3, fmaf(pi[2], g2, fmaf(s, s, 1.f))));
+    const float a = fmaf(d3, g3, fmaf(d2, g2, s)) * w0, b = fmaf(h3, g3, g2) * w0, c = g3 * w0;
+    // c < 0: an odd number of atoms above s (the lone one above, or all three);
+    // otherwise the lone one below, or all three below; turned so that the lone
+    // atom is the positive zero
+    const bool odd = c < 0.f;
+    const float A = odd ? a : -a;
+    const bool none = A <= 0.f && b >= 0.f;
+    const float iv = fast_rcp(cubic_top(A, b, fabsf(c)));
+    const float wl = none ? 0.f : orth_weight<NH>(o, odd ? s + iv : s - iv);
+    return fmaf(beta, w0, odd != none ? (1.f - w0) - wl : wl);
+  }
 }
 
 }  // namespace mb

@@ -216,91 +216,226 @@ __device__ __forceinline__ void load_batch_covered(Stage& st, const float4* rec,
 // 2^-24 (9 (|a_x| + |a_y|) + 2 (|o_x| + |o_y|) + 2 (h1 + h2) + 100) (a: the
 // tile origin's offset from the rectangle's centre, o: the centre's offset
 // from the projected mean), and the band 1e-6 (16 + |a_x| + |a_y| + |o_x| +
-// |o_y| + h1 + h2) is about twice that. Near an edge the wave re-tests in
-// double against rectd. Only the first pass tests coverage: every later pass,
-// forward and backward, reads the masks it stores.
+// |o_y| + h1 + h2) is about twice that. An entry with a pixel inside its band
+// is tested again by the whole wave, those pixels in double against rectd.
+// Only the first pass tests coverage: every later pass, forward and backward,
+// reads the masks it stores.
 //
 // The set-up lives in LDS the kernel already holds: (c1, c2) at the tile
 // origin replace the staged record's centre offset (st.f[0][j].zw, which
-// the first pass reads nowhere else and the later passes stage again), and
-// the band shares a 32-bit word with the quadrant bits (cover_word: the band's
-// four low mantissa bits carry them; clearing them lowers the band by a
-// relative 2^-19 at most).
-//
-// cover_setup also returns the 8x8 quadrants of the tile the rectangle can
-// reach (bit q for quadrant q = 2 row + column): those whose pixel-centre
-// square overlaps the rectangle's axis-aligned box, and whose centre lies
-// within h + 3.5 (|e1x| + |e1y|) of the rectangle along both of its axes
-// (the separating-axis test of two rectangles); a margin beyond the
-// rounding bound keeps the bits from ever missing a covered pixel.
-__device__ __forceinline__ uint32_t cover_setup(Stage& st, int j, int xt, int yt) {
+// the first pass reads nowhere else). Returns the band.
+__device__ __forceinline__ float cover_setup(Stage& st, int j, int xt, int yt) {
   const float4 f0 = st.f[0][j], f1 = st.f[1][j];
   const float ax = ((float)xt + 0.5f - f0.x) - f0.z;
   const float ay = ((float)yt + 0.5f - f0.y) - f0.w;
   const float a1 = ax * f1.x + ay * f1.y;
   const float a2 = ay * f1.x - ax * f1.y;
-  const float band = 1e-6f * (16.f + fabsf(ax) + fabsf(ay) + fabsf(f0.z) + fabsf(f0.w) + f1.z + f1.w);
   st.f[0][j] = make_float4(f0.x, f0.y, a1, a2);
-  const float cx = f0.x + f0.z, cy = f0.y + f0.w;
-  const float eax = fabsf(f1.x), eay = fabsf(f1.y);
-  const float mx = 0.01f + 1e-5f * fabsf(cx), my = 0.01f + 1e-5f * fabsf(cy);
-  const float bx = eax * f1.z + eay * f1.w + mx, by = eay * f1.z + eax * f1.w + my;
-  const float reach = 3.5f * (eax + eay) + band + 0.01f;
-  uint32_t bits = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float lx = (float)(xt + (q & 1) * 8) + 0.5f, ly = (float)(yt + (q >> 1) * 8) + 0.5f;
-    const bool box = cx + bx >= lx && cx - bx <= lx + 7.f && cy + by >= ly && cy - by <= ly + 7.f;
-    const float qi = 8.f * (float)(q & 1) + 3.5f, qj = 8.f * (float)(q >> 1) + 3.5f;
-    const float c1 = a1 + qi * f1.x + qj * f1.y;
-    const float c2 = a2 - qi * f1.y + qj * f1.x;
-    const bool sat = fabsf(c1) <= f1.z + reach && fabsf(c2) <= f1.w + reach;
-    bits |= (box && sat) ? (1u << q) : 0u;
-  }
-  return (__float_as_uint(band) & ~15u) | bits;
+  return 1e-6f * (16.f + fabsf(ax) + fabsf(ay) + fabsf(f0.z) + fabsf(f0.w) + f1.z + f1.w);
 }
 
-__device__ __forceinline__ bool cover_reaches(uint32_t word, int quad) { return (word >> quad) & 1u; }
-__device__ __forceinline__ float cover_band(uint32_t word) { return __uint_as_float(word & ~15u); }
+// The 64 pixels of the tile's 8x8 block `quad` that entry j covers (bit
+// 8 row + column), one entry per lane (after cover_setup), by the float test;
+// `near` receives the smallest margin to an edge among them. One lane per
+// entry shares an entry's set-up over its 64 tests and leaves the mask where
+// it is stored from: about 24 issue cycles an entry, where the wave testing
+// one entry with a lane per pixel took about 90 (uniform reads, ballot and
+// a store for each).
+__device__ __forceinline__ uint64_t cover_entry(const Stage& st, int j, int quad, float& near) {
+  const float4 f0 = st.f[0][j], f1 = st.f[1][j];
+  float p1[8], p2[8];  // the columns' part of (c1, c2)
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float fi = (float)(8 * (quad & 1) + i);
+    p1[i] = fmaf(fi, f1.x, f0.z);
+    p2[i] = fmaf(fi, -f1.y, f0.w);
+  }
+  near = 1e30f;
+  uint32_t out[2];
+#pragma unroll
+  for (int h = 1; h >= 0; --h) {
+    uint32_t bits = 0;  // the tests' sign bits (1: outside), the last pixel first
+    // a row at a time: unrolled further, the compiler keeps all 64 tests' values live
+#pragma unroll 1
+    for (int r = 3; r >= 0; --r) {
+      float fj = (float)(8 * (quad >> 1) + 4 * h + r);
+      asm("" : "+v"(fj));  // in a vector register: a scalar operand halves the rate of fp32 multiply-adds
+#pragma unroll
+      for (int i = 7; i >= 0; --i) {
+        const float c1 = fmaf(fj, f1.y, p1[i]), c2 = fmaf(fj, f1.x, p2[i]);
+        const float m = fminf(f1.z - fabsf(c1), f1.w - fabsf(c2));
+        near = fminf(near, fabsf(m));
+        bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(m), 31);
+      }
+    }
+    out[h] = ~bits;
+  }
+  return ((uint64_t)out[1] << 32) | out[0];
+}
 
-// The per-pixel test of entry j (after cover_setup; `word` its set-up word)
-// for the pixel at offset (fi, fj) from the tile's first pixel, centre (u, v).
-__device__ __forceinline__ bool covers(const Stage& st, uint32_t word, const double2* rectd, const int* sorted_rec,
-                                       int b, int j, float fi, float fj, float u, float v, bool inside) {
+// The same test of one entry j by the whole wave, one pixel per lane (offset
+// (fi, fj) from the tile's first pixel, centre (u, v)), with the pixels inside
+// the band decided in double.
+__device__ __forceinline__ bool covers(const Stage& st, float band, const double2* rectd, const int* sorted_rec,
+                                       int b, int j, float fi, float fj, float u, float v) {
   const float4 f0 = st.f[0][j], f1 = st.f[1][j];
   const float c1 = fmaf(fj, f1.y, fmaf(fi, f1.x, f0.z));
   const float c2 = fmaf(fj, f1.x, fmaf(fi, -f1.y, f0.w));
   const float m = fminf(f1.z - fabsf(c1), f1.w - fabsf(c2));
-  bool cov = inside && m >= 0.f;
-  const bool amb = inside && fabsf(m) < cover_band(word);
-  if (__ballot(amb) != 0) {
+  bool cov = m >= 0.f;
+  if (fabsf(m) < band) {
     const int rid = __builtin_amdgcn_readfirstlane(sorted_rec[b + j]);
     const double2 cd = rectd[(size_t)rid * 3], ed = rectd[(size_t)rid * 3 + 1], hd = rectd[(size_t)rid * 3 + 2];
-    if (amb) {
-      const double axd = (double)u - cd.x, ayd = (double)v - cd.y;
-      const double c1d = axd * ed.x + ayd * ed.y;
-      const double c2d = -axd * ed.y + ayd * ed.x;
-      cov = fabs(c1d) <= hd.x && fabs(c2d) <= hd.y;
-    }
+    const double axd = (double)u - cd.x, ayd = (double)v - cd.y;
+    const double c1d = axd * ed.x + ayd * ed.y;
+    const double c2d = -axd * ed.y + ayd * ed.x;
+    cov = fabs(c1d) <= hd.x && fabs(c2d) <= hd.y;
   }
   return cov;
 }
 
-// Mask walk without a queue: calls body(j, m) for every entry j of the staged
-// batch [b, b + nb) whose 64-bit coverage mask m for this wave's pixel block
-// `quad` is not zero, in list order (wave-uniform j and m).
+// 64 x 64 bit transpose over the wave: from the coverage masks of 64 entries
+// (lane = entry, bit = pixel) the words of 64 pixels (lane = pixel, bit =
+// entry), and back. Six exchanges with lane ^ s, s = 32, 16, .., 1: a lane
+// keeps the bits whose index agrees with its own in bit s and takes the others
+// from its partner, shifted by s. About 200 issue cycles.
+__device__ __forceinline__ uint64_t transpose_masks(uint64_t m, int lane) {
+  uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
+  {
+    // s = 32: the upper lanes' low words change places with the lower lanes' high words
+    const uint32_t give = lane & 32 ? lo : hi;
+    const uint32_t got = (uint32_t)__shfl_xor((int)give, 32, 64);
+    lo = lane & 32 ? got : lo;
+    hi = lane & 32 ? hi : got;
+  }
+  auto step = [&](uint32_t plo, uint32_t phi, int s, uint32_t mask) __attribute__((always_inline)) {
+    const uint32_t keep = lane & s ? ~mask : mask;
+    const uint32_t rot = lane & s ? (uint32_t)s : (uint32_t)(32 - s);
+    lo = (lo & keep) | (__builtin_amdgcn_alignbit(plo, plo, rot) & ~keep);
+    hi = (hi & keep) | (__builtin_amdgcn_alignbit(phi, phi, rot) & ~keep);
+  };
+  step((uint32_t)__builtin_amdgcn_ds_swizzle((int)lo, 0x401F), (uint32_t)__builtin_amdgcn_ds_swizzle((int)hi, 0x401F),
+       16, 0x0000FFFFu);
+  step((uint32_t)__builtin_amdgcn_mov_dpp((int)lo, 0x128, 0xF, 0xF, true),
+       (uint32_t)__builtin_amdgcn_mov_dpp((int)hi, 0x128, 0xF, 0xF, true), 8, 0x00FF00FFu);  // row_ror:8
+  step((uint32_t)__builtin_amdgcn_ds_swizzle((int)lo, 0x101F), (uint32_t)__builtin_amdgcn_ds_swizzle((int)hi, 0x101F),
+       4, 0x0F0F0F0Fu);
+  step((uint32_t)__builtin_amdgcn_mov_dpp((int)lo, 0x4E, 0xF, 0xF, true),
+       (uint32_t)__builtin_amdgcn_mov_dpp((int)hi, 0x4E, 0xF, 0xF, true), 2, 0x33333333u);  // quad_perm 2,3,0,1
+  step((uint32_t)__builtin_amdgcn_mov_dpp((int)lo, 0xB1, 0xF, 0xF, true),
+       (uint32_t)__builtin_amdgcn_mov_dpp((int)hi, 0xB1, 0xF, 0xF, true), 1, 0x55555555u);  // quad_perm 1,0,3,2
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// Walks of a staged batch [b, b + nb) by pixel words (lane = pixel, bit =
+// entry), 64 entries (a chunk) at a time. A wave takes all the batch's chunks
+// of consecutive entries; in a split block (see BlockWork) it takes every
+// fourth entry, one chunk a batch (`own4` >= 0: its index). A round takes one
+// entry from every lane that has entries left, each its own: the lane holds its
+// pixel's values and sums in its registers, so nothing is queued, broadcast or
+// sent back, and every pixel's sums run in list order.
+__device__ __forceinline__ int n_chunks(int nb, int own4) { return own4 < 0 ? (nb + 63) >> 6 : 1; }
+// Entry of the staged batch that bit (or lane) e of chunk c stands for.
+__device__ __forceinline__ int chunk_entry(int c, int e, int own4) { return own4 < 0 ? 64 * c + e : 4 * e + own4; }
+// Coverage masks of chunk c, one entry per lane.
+__device__ __forceinline__ uint64_t load_masks(const uint64_t* masks, int b, int nb, int quad, int own4, int c,
+                                               int lane) {
+  const int j = chunk_entry(c, lane, own4);
+  return j < nb ? masks[(size_t)(b + j) * 4 + quad] : 0ull;
+}
+// body(j) for the entries of this lane's word m of chunk c (no cross-lane
+// operations in it): 64 pairs take 1.38 rounds on the 500k-Gaussian 1080p scene,
+// for the pixels of a block have unequal counts.
 template <class Body>
-__device__ __forceinline__ void for_each_masked(const uint64_t* masks, int b, int nb, int quad, int lane,
-                                                Body&& body) {
-  uint64_t next = lane < nb ? masks[(size_t)(b + lane) * 4 + quad] : 0ull;
-  for (int j0 = 0; j0 < nb; j0 += 64) {
-    const uint64_t mk = next;  // the next 64 masks load while these are walked
-    next = j0 + 64 + lane < nb ? masks[(size_t)(b + j0 + 64 + lane) * 4 + quad] : 0ull;
-    uint64_t nz = __ballot(mk != 0);
-    while (nz) {
-      const int l = __builtin_ctzll(nz);
-      nz &= nz - 1;
-      body(j0 + l, (uint64_t)__shfl(mk, l, 64));
+__device__ __forceinline__ void word_rounds(uint64_t m, int c, int own4, Body&& body) {
+  while (m != 0) {
+    const int e = __builtin_ctzll(m);
+    m &= m - 1;
+    body(chunk_entry(c, e, own4));
+  }
+}
+// The rounds over the stored masks, for the lanes with `live`.
+template <class Body>
+__device__ __forceinline__ void for_each_own_entry(const uint64_t* masks, int b, int nb, int quad, int own4, int lane,
+                                                   bool live, Body&& body) {
+  const int nc = n_chunks(nb, own4);
+  uint64_t next = load_masks(masks, b, nb, quad, own4, 0, lane);
+  for (int c = 0; c < nc; ++c) {
+    const uint64_t w = transpose_masks(next, lane);
+    if (c + 1 < nc) next = load_masks(masks, b, nb, quad, own4, c + 1, lane);
+    word_rounds(live ? w : 0ull, c, own4, body);
+  }
+}
+
+// The same rounds for an evaluation that costs far more than queueing a pair:
+// a round with kDirectLanes lanes or more is evaluated as it stands, and the
+// pairs of the thinner rounds are queued and evaluated 64 at a time, one per
+// lane, their results sent back to the pixel's own lane. The queue is emptied at
+// the end of each chunk, so a pixel's results still arrive in list order. On the
+// 500k-Gaussian 1080p scene 86% of the pairs are evaluated directly, 97% of
+// their lanes at work; all rounds direct would leave 73% at work, all pairs
+// queued cost a push, thirteen broadcasts and an owner sum each.
+// eval(direct, on, j, p, own): one evaluation for the lanes with `on`, of entry
+// j at pixel lane p; direct (wave-uniform): p is the lane itself; otherwise
+// bits of `own` are the lanes whose results belong to this lane's pixel. All
+// lanes call it.
+constexpr int kDirectLanes = 48;
+template <class Eval>
+__device__ __forceinline__ void walk_pairs(WaveQueue& q, const uint64_t* masks, int b, int nb, int quad, int own4,
+                                           int lane, bool live, Eval&& eval) {
+  const int nc = n_chunks(nb, own4);
+  int c = -1;
+  uint64_t next = load_masks(masks, b, nb, quad, own4, 0, lane);
+  uint64_t m = 0;
+  QueueCursor qc;
+  queue_reset(qc);
+  for (;;) {
+    const uint64_t act = __ballot(m != 0);
+    const int n = __popcll(act);
+    if (n == 0 && qc.cnt == 0 && c + 1 < nc) {
+      const uint64_t w = transpose_masks(next, lane);
+      m = live ? w : 0ull;
+      ++c;
+      if (c + 1 < nc) next = load_masks(masks, b, nb, quad, own4, c + 1, lane);
+      continue;
+    }
+    const bool direct = n >= kDirectLanes;
+    int j = 0, p = lane;
+    bool on = m != 0;
+    if (on) {
+      j = chunk_entry(c, (int)__builtin_ctzll(m), own4);
+      m &= m - 1;
+    }
+    if (!direct) {
+      if (on) {
+        const int pos = qc.cnt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
+        q.item[pos] = (uint16_t)((j << 6) | lane);
+        // bit pos of (own_lo, own_hi), by masks: chains of 64-bit selects on
+        // the carry register issue five times slower than plain logic here
+        const uint64_t bit = 1ull << (pos & 63);
+        const uint64_t hi = 0ull - (uint64_t)(pos >> 6);
+        qc.own_lo |= bit & ~hi;
+        qc.own_hi |= bit & hi;
+      }
+      qc.cnt += n;
+      if (qc.cnt < 64 && (n != 0 || qc.cnt == 0)) {
+        if (n == 0) break;
+        continue;
+      }
+      __builtin_amdgcn_wave_barrier();
+      on = lane < qc.cnt;
+      const int it = on ? (int)q.item[lane] : lane;
+      j = it >> 6;
+      p = it & 63;
+    }
+    eval(direct, on, j, p, qc.own_lo);
+    if (!direct) {
+      if (qc.cnt > 64) {
+        queue_pop64(q, qc, lane);
+      } else {
+        queue_reset(qc);
+      }
     }
   }
 }
@@ -323,12 +458,23 @@ __device__ __forceinline__ RayG ray_params(const Stage& st, int j, float dx, flo
   return g;
 }
 
+// warp_y with its fused operations fixed. Small pivots of the pixel's Hankel
+// matrix magnify a moment's last bits, so the moments round the same way
+// whatever code surrounds them.
+__device__ __forceinline__ float warp_y_moment(const PixelBasis& b, float t, float dt) {
+  const float q = fmaf(0.8f, t, 1.f);
+  const float sq = fast_sqrt(q);
+  const float num = fmaf(b.p, b.p, (q + b.p) * q);
+  const float den = fmaf(q, sq, b.p15) * (b.p15 * (q * sq));
+  return b.amp * dt * num * fast_rcp(den);
+}
+
 // warped moments of one ray Gaussian, Eqs. 10-12 (t_f -> inf), in the pixel's
 // moment variable; the boundary term enters with '+' (App. C)
 template <int K>
 __device__ __forceinline__ void particle_moments(const RayG& g, const PixelBasis& pb, float tn, float* m) {
   float mus = fmaxf(g.mu, tn);
-  float ys = warp_y(pb, mus, mus - pb.tc);
+  float ys = warp_y_moment(pb, mus, mus - pb.tc);
   float yp = warp_dy(pb, mus);
   float gg = ys + yp * (g.mu - mus);
   float is = fast_rcp(g.sig);
@@ -356,7 +502,7 @@ __device__ __forceinline__ void particle_moments(const RayG& g, const PixelBasis
 template <int K>
 __device__ __forceinline__ void particle_moments_d(const RayG& g, const PixelBasis& pb, float tn, double* m) {
   float mus = fmaxf(g.mu, tn);
-  float ys = warp_y(pb, mus, mus - pb.tc);
+  float ys = warp_y_moment(pb, mus, mus - pb.tc);
   float yp = warp_dy(pb, mus);
   const double gg = (double)ys + (double)yp * (double)(g.mu - mus);
   float is = fast_rcp(g.sig);
@@ -389,12 +535,18 @@ __device__ __forceinline__ float phi_fn(float x, float d) {
   return fabsf(x) < kPhiSeries ? s : (1.f - d) * fast_rcp(x);
 }
 
+// x as it is: a product rounded here is not fused into a later sum
+__device__ __forceinline__ float rounded(float x) {
+  asm("" : "+v"(x));
+  return x;
+}
+
 // Interval edges of one Gaussian's quadrature (App. B sample spacing): edge
-// offsets, the clamp to the near bound, the moment variable y at each edge
-// and the particle density sigma_i there.
+// offsets, the clamp to the near bound, the moment variable y at each edge,
+// the interval lengths and the particle density sigma_i at each edge.
 template <int NQ>
 struct QEdges {
-  float off[NQ], y[NQ], sj[NQ], tau[NQ];
+  float off[NQ], y[NQ], sj[NQ], tau[NQ], delta[NQ - 1];
   bool cl[NQ];
 };
 
@@ -417,6 +569,45 @@ __device__ __forceinline__ void quad_edges(const RayG& g, const PixelBasis& pb, 
   }
 }
 
+// The same with the clamped edges' values formed only in waves that have one (the
+// first edge is the nearest, so it tells; most Gaussians lie beyond the near
+// bound).
+template <int NQ>
+__device__ __forceinline__ void quad_edges_far(const RayG& g, const PixelBasis& pb, float tn, const RenderArgs& a,
+                                           QEdges<NQ>& e) {
+  // the fused operations are fixed (rounded): the backward pass forms the same
+  // edges, and its moment adjoint magnifies their last bits
+  const float dtc = rounded(g.mu) - pb.tc;
+  const float ks = a.kappa * g.sig;
+  float t[NQ], dt[NQ];
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) {
+    e.off[j] = rounded(ks * a.xq[j]);
+    t[j] = fmaf(ks, a.xq[j], g.mu);
+    dt[j] = dtc + e.off[j];
+    e.sj[j] = g.omega * a.eq[j];
+    e.cl[j] = t[j] < tn;
+  }
+#pragma unroll
+  for (int j = 0; j + 1 < NQ; ++j) e.delta[j] = e.off[j + 1] - e.off[j];
+  if (__ballot(e.cl[0]) != 0) {
+    // every edge left of the near bound is moved onto it: one density there
+    const float rn = (tn - g.mu) * fast_rcp(g.sig);
+    const float en = g.omega * exp_neg_half(rn * rn);
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+      dt[j] = e.cl[j] ? (tn - pb.tc) : dt[j];
+      t[j] = e.cl[j] ? tn : t[j];
+      e.sj[j] = e.cl[j] ? en : e.sj[j];
+    }
+#pragma unroll
+    for (int j = 0; j + 1 < NQ; ++j)
+      e.delta[j] = e.cl[j + 1] ? 0.f : (e.cl[j] ? t[j + 1] - tn : e.delta[j]);
+  }
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) e.y[j] = warp_y(pb, t[j], dt[j]);
+}
+
 // Eq. 7 sum over the intervals, given the optical depth at every edge
 template <int NQ>
 __device__ __forceinline__ float quad_sum(const RayG& g, float tn, const QEdges<NQ>& e) {
@@ -428,6 +619,21 @@ __device__ __forceinline__ float quad_sum(const RayG& g, float tn, const QEdges<
     const float x = e.tau[j + 1] - e.tau[j];
     const float d = __expf(-x);
     q += T * delta * phi_fn(x, d) * e.sj[j];
+    T *= d;
+  }
+  return q;
+}
+
+// The same from quad_edges_far's interval lengths
+template <int NQ>
+__device__ __forceinline__ float quad_sum(const QEdges<NQ>& e) {
+  float q = 0.f;
+  float T = __expf(-e.tau[0]);  // transmittance at edge j, carried along the edges
+#pragma unroll
+  for (int j = 0; j + 1 < NQ; ++j) {
+    const float x = e.tau[j + 1] - e.tau[j];
+    const float d = __expf(-x);
+    q += T * e.delta[j] * phi_fn(x, d) * e.sj[j];
     T *= d;
   }
   return q;
@@ -461,10 +667,16 @@ __device__ __forceinline__ float pair_penalty(const RayG& g, float tn, const QEd
 template <int NH, int NQ>
 __device__ __forceinline__ float particle_quadrature(const RayG& g, const PixelBasis& pb, const LInv<NH>& L,
                                                      float m0, float tn, const RenderArgs& a, QEdges<NQ>& e) {
-  quad_edges<NQ>(g, pb, tn, a, e);
+  if constexpr (NH == 2)
+    quad_edges_far<NQ>(g, pb, tn, a, e);
+  else
+    quad_edges<NQ>(g, pb, tn, a, e);
 #pragma unroll
   for (int j = 0; j < NQ; ++j) e.tau[j] = m0 * bound_F<NH>(L, e.y[j], a.beta);
-  return quad_sum<NQ>(g, tn, e);
+  if constexpr (NH == 2)
+    return quad_sum<NQ>(e);
+  else
+    return quad_sum<NQ>(g, tn, e);
 }
 
 }  // namespace mb

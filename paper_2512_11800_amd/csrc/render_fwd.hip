@@ -9,7 +9,15 @@
 //   epilogue  Eq. 15 rescaling (Rescale pass).
 // Pass 0 tests coverage and stores, per list entry and wave, the 64-bit mask
 // of covered pixels; the later passes (and the backward kernel) walk the
-// masks instead. Covering pairs are evaluated compacted (see WaveQueue).
+// masks instead. Here the masks are transposed into one word of entries per
+// pixel: every lane walks its own pixel's entries (see word_rounds, walk_pairs).
+// The kernel is bound by VALU issue. With the pairs of all three passes queued in
+// (entry, pixel) order and their results summed by owner loops through LDS it
+// took 1.16 ms (K = 4), 1.95 ms (K = 6) at 500k Gaussians, 1920x1080, against
+// 0.90 and 1.62 ms: what went is the queueing, the broadcasts and the owner
+// loops. Every pixel's sums keep their order and every pair its arithmetic: the
+// image, the saved state and the moments are the same to the last bit (a
+// degenerate pixel's gradients magnify a changed bit by four decades).
 //
 // Variants (MODE):
 //   kModePlain    the path above;
@@ -79,8 +87,18 @@ __device__ __forceinline__ float std_query(float y, float mu, float sig) {
   return fminf(fmaxf((y - mu) / sig, -kMaxZ), kMaxZ);
 }
 
+// acc += m with m rounded first, not fused into the product that formed it
+__device__ __forceinline__ void add_rounded(double& acc, double m) {
+  asm("" : "+v"(m));
+  acc += m;
+}
+
 template <int K, int NQ, int MODE>
-__global__ __launch_bounds__(256) void k_render_fwd(RenderArgs a, CamSet cams) {
+__global__
+// waves per SIMD: five for K = 4 (0.90 ms against 0.92 ms with four, at the scene
+// above), four for K = 6 (1.62 against 1.75 ms with three)
+__launch_bounds__(256, K == 4 && MODE != kModeTrig ? 5 : (K == 6 && MODE == kModePlain ? 4 : 3))
+void k_render_fwd(RenderArgs a, CamSet cams) {
   constexpr int NH = K / 2;
   __shared__ Stage st;
   __shared__ long long s_base;
@@ -112,14 +130,11 @@ __global__ __launch_bounds__(256) void k_render_fwd(RenderArgs a, CamSet cams) {
   const size_t pix = ((size_t)ci * c.height + (inside ? py : 0)) * c.width + (inside ? px : 0);
 
   __shared__ WaveQueue wq[4];
-  __shared__ uint32_t reach[kBlock];  // per staged entry: its coverage set-up word (cover_setup)
-  // per-wave results of the queued pairs: 3 or K + 1 floats per pair in passes
-  // 0 and 1, q (r, g, b, 1) in pass 2
-  // (K = 8 and the trigonometric moments pass their moments in double:
-  // twice the room)
+  __shared__ float band[kBlock];  // per staged entry: the coverage test's rounding band (cover_setup)
+  // results of the queued pairs of pass 2: q (r, g, b, 1), consistency penalty
+  __shared__ __align__(16) float wres[4][5 * 64];
   constexpr bool kTrig = MODE == kModeTrig;
-  constexpr bool kDblMom = K >= 8 || kTrig;
-  __shared__ __align__(16) float wres[4][(K + 1) * 64 * (kDblMom ? 2 : 1)];
+  constexpr bool kDblMom = K >= 8 || kTrig;  // moments per pair in double
   WaveQueue& q = wq[wave];
   float* res = wres[wave];
   const int x0 = tx * kTile + (quad & 1) * 8, y0 = ty * kTile + (quad >> 1) * 8;
@@ -127,20 +142,12 @@ __global__ __launch_bounds__(256) void k_render_fwd(RenderArgs a, CamSet cams) {
   // order through the (then idle) staging buffer; every wave ends with the
   // same totals
   float* xch = reinterpret_cast<float*>(&st);
-  // the pair at queue position `lane` (entry j, pixel lane p); inactive lanes
-  // (lane >= n) get p = lane so the cross-lane reads stay uniform
-  auto item_of = [&](int n, int& j, int& p) __attribute__((always_inline)) {
-    const bool act = lane < n;
-    const int it = act ? (int)q.item[lane] : lane;
-    j = act ? (it >> 6) : 0;
-    p = it & 63;
-    return act;
+  // this lane's pixel against staged entry j
+  auto ray_own = [&](int j) __attribute__((always_inline)) {
+    return ray_params(st, j, u - st.f[0][j].x, v - st.f[0][j].y, lam);
   };
-  auto ray_of = [&](int j, int p, float lamp) __attribute__((always_inline)) {
-    const float dx = (float)(x0 + (p & 7)) + 0.5f - st.f[0][j].x;
-    const float dy = (float)(y0 + (p >> 3)) + 0.5f - st.f[0][j].y;
-    return ray_params(st, j, dx, dy, lamp);
-  };
+  // a list of one batch stays staged from pass 0 on
+  const bool staged = rg.y - rg.x <= kBlock;
 
   // ---- pass 0: coverage masks and the pixel's moment variable --------------
   // weighted depth statistics of the covering Gaussians (weight omega Sigma):
@@ -149,61 +156,41 @@ __global__ __launch_bounds__(256) void k_render_fwd(RenderArgs a, CamSet cams) {
   double sw = 0.0, swm = 0.0, swq = 0.0;
   int n_cov = 0;
   {
-    auto flush = [&](int n, uint64_t own) __attribute__((always_inline)) {
-      int j, p;
-      const bool act = item_of(n, j, p);
-      const float lamp = from_lane(lam, p);
-      if (act) {
-        RayG g = ray_of(j, p, lamp);
-        res[lane] = g.omega * g.sig;
-        res[64 + lane] = g.mu;
-        res[128 + lane] = g.sig;
-      }
-      __builtin_amdgcn_wave_barrier();
-      while (own) {
-        const int i = __builtin_ctzll(own);
-        own &= own - 1;
-        const double wgt = (double)res[i], mu = (double)res[64 + i], sg = (double)res[128 + i];
-        sw += wgt;
-        swm = fma(wgt, mu, swm);
-        swq = fma(wgt, fma(mu, mu, sg * sg), swq);
-      }
-      __builtin_amdgcn_wave_barrier();
-    };
+    const uint64_t inside_mask = __ballot(inside);
     for (int b = rg.x; b < rg.y; b += kBlock) {
       int nb = min(kBlock, rg.y - b);
       __syncthreads();
       load_batch(st, a.rec, a.sorted_rec, b, nb);
       // each thread reads back the record it staged itself
-      if (tid < nb) reach[tid] = cover_setup(st, tid, tx * kTile, ty * kTile);
+      if (tid < nb) band[tid] = cover_setup(st, tid, tx * kTile, ty * kTile);
       __syncthreads();
-      QueueCursor qc;
-      queue_reset(qc);
-      // entries whose rectangle's box misses this wave's 8x8 block cover none
-      // of its pixels: their mask is zero and the per-pixel test is skipped;
-      // the others are tested in list order
-      for (int j0 = 0; j0 < nb; j0 += 64) {
-        const int jl = j0 + lane;
-        const bool mine = jl < nb && (own4 < 0 || (jl & 3) == own4);
-        const bool near = mine && cover_reaches(reach[mine ? jl : 0], quad);
-        if (mine && !near) a.masks[(size_t)(b + jl) * 4 + quad] = 0ull;
-        uint64_t todo = __ballot(near);
-        while (todo) {
-          const int j = j0 + __builtin_ctzll(todo);
-          todo &= todo - 1;
-          const bool cov = covers(st, reach[j], a.rectd, a.sorted_rec, b, j, fi, fj, u, v, inside);
-          uint64_t mask = __ballot(cov);
-          if (lane == 0) a.masks[(size_t)(b + j) * 4 + quad] = mask;
-          if (mask == 0) continue;
-          n_cov += cov ? 1 : 0;
-          queue_push(q, qc, mask, cov, j, lane);
-          if (qc.cnt >= 64) {
-            flush(64, qc.own_lo);
-            queue_pop64(q, qc, lane);
-          }
+      const int nc = n_chunks(nb, own4);
+      for (int ch = 0; ch < nc; ++ch) {
+        const int jl = chunk_entry(ch, lane, own4);
+        const bool mine = jl < nb;
+        const int jr = mine ? jl : 0;
+        float near;
+        uint64_t mask = cover_entry(st, jr, quad, near);
+        uint64_t amb = __ballot(mine && near < band[jr]);
+        while (amb) {
+          const int l = __builtin_ctzll(amb);
+          amb &= amb - 1;
+          const int j = chunk_entry(ch, l, own4);
+          const uint64_t exact = __ballot(covers(st, band[j], a.rectd, a.sorted_rec, b, j, fi, fj, u, v));
+          mask = lane == l ? exact : mask;
         }
+        mask = mine ? mask & inside_mask : 0ull;
+        if (mine) a.masks[(size_t)(b + jl) * 4 + quad] = mask;
+        const uint64_t word = transpose_masks(mask, lane);
+        n_cov += __popcll(word);
+        word_rounds(word, ch, own4, [&](int j) __attribute__((always_inline)) {
+          const RayG g = ray_own(j);
+          const double wgt = (double)(g.omega * g.sig), mu = (double)g.mu, sg = (double)g.sig;
+          sw += wgt;
+          swm = fma(wgt, mu, swm);
+          swq = fma(wgt, fma(mu, mu, sg * sg), swq);
+        });
       }
-      if (qc.cnt > 0) flush(qc.cnt, qc.own_lo);
     }
   }
   if (split) {
@@ -245,58 +232,32 @@ __global__ __launch_bounds__(256) void k_render_fwd(RenderArgs a, CamSet cams) {
 #pragma unroll
   for (int k = 0; k <= K; ++k) acc[k] = 0.0;
   {
-    auto flush = [&](int n, uint64_t own) __attribute__((always_inline)) {
-      int j, p;
-      const bool act = item_of(n, j, p);
-      PixelBasis pp;
-      pp.tc = from_lane(pb.tc, p);
-      pp.p = from_lane(pb.p, p);
-      pp.p15 = from_lane(pb.p15, p);
-      pp.amp = from_lane(pb.amp, p);
-      const float lamp = from_lane(lam, p);
-      double* resd = reinterpret_cast<double*>(res);
-      if (act) {
-        RayG g = ray_of(j, p, lamp);
+    for (int b = rg.x; b < rg.y; b += kBlock) {
+      int nb = min(kBlock, rg.y - b);
+      if (!staged) {
+        __syncthreads();
+        load_batch_covered(st, a.rec, a.sorted_rec, a.masks, bw.quad, b, nb);
+        __syncthreads();
+      }
+      for_each_own_entry(a.masks, b, nb, quad, own4, lane, true, [&](int j) __attribute__((always_inline)) {
+        const RayG g = ray_own(j);
         if constexpr (kTrig) {
           double m[K + 1];
           particle_trig_moments_d<NH>(g, tn, m);
 #pragma unroll
-          for (int k = 0; k <= K; ++k) resd[k * 64 + lane] = m[k];
+          for (int k = 0; k <= K; ++k) add_rounded(acc[k], m[k]);
         } else if constexpr (kDblMom) {
           double m[K + 1];
-          particle_moments_d<K>(g, pp, tn, m);
+          particle_moments_d<K>(g, pb, tn, m);
 #pragma unroll
-          for (int k = 0; k <= K; ++k) resd[k * 64 + lane] = m[k];
+          for (int k = 0; k <= K; ++k) add_rounded(acc[k], m[k]);
         } else {
           float m[K + 1];
-          particle_moments<K>(g, pp, tn, m);
+          particle_moments<K>(g, pb, tn, m);
 #pragma unroll
-          for (int k = 0; k <= K; ++k) res[k * 64 + lane] = m[k];
+          for (int k = 0; k <= K; ++k) acc[k] += (double)m[k];
         }
-      }
-      __builtin_amdgcn_wave_barrier();
-      while (own) {
-        const int i = __builtin_ctzll(own);
-        own &= own - 1;
-#pragma unroll
-        for (int k = 0; k <= K; ++k) acc[k] += kDblMom ? resd[k * 64 + i] : (double)res[k * 64 + i];
-      }
-      __builtin_amdgcn_wave_barrier();
-    };
-    for (int b = rg.x; b < rg.y; b += kBlock) {
-      int nb = min(kBlock, rg.y - b);
-      __syncthreads();
-      load_batch_covered(st, a.rec, a.sorted_rec, a.masks, bw.quad, b, nb);
-      __syncthreads();
-      QueueCursor qc;
-      queue_reset(qc);
-      queue_from_masks<true>(q, qc, a.masks, b, nb, quad, own4, lane, ~0ull,
-                       [&]() __attribute__((always_inline)) {
-                         flush(64, qc.own_lo);
-                         queue_pop64(q, qc, lane);
-                       },
-                       [](int) {});
-      if (qc.cnt > 0) flush(qc.cnt, qc.own_lo);
+      });
     }
   }
 
@@ -326,22 +287,23 @@ __global__ __launch_bounds__(256) void k_render_fwd(RenderArgs a, CamSet cams) {
   // (about m0 times a colour) is negligible, and its moment vector is too close
   // to the float32 underflow range to define a measure
   const bool live = acc[0] > kMinDepth;
-  LInv<NH> L;
+  LInv<NH> L = {};
+  Orth<MODE == kModeTabPlain ? NH : 2> orth = {};
   TrigLInv<kTrig ? NH : 1> TL;
   bool fallback = false;
   if constexpr (kTrig) {
     if (live) fallback = trig_factor<NH>(acc, TL) != 0.0;
+  } else if constexpr (MODE != kModeEmit && MODE != kModeTabSur) {
+    if (live) {
+      double bn[K + 1], bmix[K + 1];
+      bn[0] = 1.0;
 #pragma unroll
-    for (int i = 0; i < (NH + 1) * (NH + 2) / 2; ++i) L.l[i] = 0.f;
-  } else if (live && MODE != kModeEmit && MODE != kModeTabSur) {
-    double bn[K + 1], bmix[K + 1];
-    bn[0] = 1.0;
-#pragma unroll
-    for (int k = 1; k <= K; ++k) bn[k] = acc[k] / acc[0];
-    fallback = hankel_factor<NH>(bn, L, bmix) != 0.0;
-  } else {
-#pragma unroll
-    for (int i = 0; i < (NH + 1) * (NH + 2) / 2; ++i) L.l[i] = 0.f;
+      for (int k = 1; k <= K; ++k) bn[k] = acc[k] / acc[0];
+      if constexpr (MODE == kModeTabPlain)
+        fallback = hankel_orth<NH>(bn, orth) != 0.0;
+      else
+        fallback = hankel_factor<NH>(bn, L, bmix) != 0.0;
+    }
   }
 
   float feat[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -377,7 +339,7 @@ __global__ __launch_bounds__(256) void k_render_fwd(RenderArgs a, CamSet cams) {
         const float dz = 2.f * kTabZ / (float)(a.tab_nodes - 1);
         float* tp = a.tab + pix * a.tab_nodes;
         for (int g = 0; g < a.tab_nodes; ++g)
-          tp[g] = live ? bound_F<NH>(L, smu + ssig * (-kTabZ + dz * (float)g), a.beta) : 0.f;
+          tp[g] = live ? orth_F<NH>(orth, fmaf(orth.l2, smu + ssig * (-kTabZ + dz * (float)g), orth.l1), a.beta) : 0.f;
       }
     }
     return;
@@ -440,126 +402,131 @@ __global__ __launch_bounds__(256) void k_render_fwd(RenderArgs a, CamSet cams) {
       load_batch(st, a.rec, a.sorted_rec, b, nb);
       __syncthreads();
       // the pairs of the coverage masks pass 0 stored (their count is n_cov)
-      for_each_masked(a.masks, b, nb, quad, lane, [&](int j, uint64_t m) __attribute__((always_inline)) {
-        if (inside && live && ((m >> lane) & 1ull)) {
-          const float dx = u - st.f[0][j].x, dy = v - st.f[0][j].y;
-          RayG g = ray_params(st, j, dx, dy, lam);
-          QEdges<NQ> e;
-          quad_edges<NQ>(g, pb, tn, a, e);
-          if (qbase >= 0) {
+      for_each_own_entry(a.masks, b, nb, quad, own4, lane, inside && live, [&](int j) __attribute__((always_inline)) {
+        const RayG g = ray_own(j);
+        QEdges<NQ> e;
+        quad_edges<NQ>(g, pb, tn, a, e);
+        if (qbase >= 0) {
 #pragma unroll
-            for (int k = 0; k < NQ; ++k) {
-              const long long qi = qbase + (long long)i_pair * NQ + k;
-              a.q_z[qi] = std_query(e.y[k], smu, ssig);
-              a.q_pix[qi] = (int)pix;
-            }
+          for (int k = 0; k < NQ; ++k) {
+            const long long qi = qbase + (long long)i_pair * NQ + k;
+            a.q_z[qi] = std_query(e.y[k], smu, ssig);
+            a.q_pix[qi] = (int)pix;
           }
-          ++i_pair;
         }
+        ++i_pair;
       });
     }
     return;
   } else {
     float4* cb = reinterpret_cast<float4*>(res);  // [64]
     float* cpen = res + 256;                       // [64] consistency penalty
-    const uint64_t live_mask = __ballot(inside && live);
-    // evaluate queue positions [0, n) (one per lane), then add the results of
-    // this lane's own positions (bits of `own`) in order
-    auto flush = [&](int n, uint64_t own, int b) __attribute__((always_inline)) {
-      const bool act = lane < n;
-      const int it = act ? (int)q.item[lane] : lane;
-      const int j = act ? (it >> 6) : 0;
-      const int p = it & 63;
-      PixelBasis pp;
-      pp.tc = from_lane(pb.tc, p);
-      pp.p = from_lane(pb.p, p);
-      pp.p15 = from_lane(pb.p15, p);
-      pp.amp = from_lane(pb.amp, p);
-      LInv<NH> Lp;
-      TrigLInv<kTrig ? NH : 1> TLp;
-      if constexpr (kTrig) {
-#pragma unroll
-        for (int i = 0; i < (NH + 1) * (NH + 2) / 2; ++i) {
-          TLp.re[i] = from_lane(TL.re[i], p);
-          TLp.im[i] = from_lane(TL.im[i], p);
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < (NH + 1) * (NH + 2) / 2; ++i) Lp.l[i] = from_lane(L.l[i], p);
+    for (int b = rg.x; b < rg.y; b += kBlock) {
+      int nb = min(kBlock, rg.y - b);
+      if (!staged) {
+        __syncthreads();
+        load_batch_covered(st, a.rec, a.sorted_rec, a.masks, bw.quad, b, nb);
+        __syncthreads();
       }
-      const float m0p = from_lane(m0, p), lamp = from_lane(lam, p);
-      float featp[6], smup = 0.f, ssigp = 1.f;
-      if constexpr (MODE == kModeHarvest) {
+      walk_pairs(q, a.masks, b, nb, quad, own4, lane, inside && live,
+                 [&](bool direct, bool on, int j, int p, uint64_t own) __attribute__((always_inline)) {
+        // the pixel's values: the lane's own, or those of pixel lane p
+        PixelBasis pp = pb;
+        LInv<NH> Lp = L;
+        TrigLInv<kTrig ? NH : 1> TLp = TL;
+        float m0p = m0, lamp = lam, up = u, vp = v;
+        float featp[6], smup = smu, ssigp = ssig;
 #pragma unroll
-        for (int f = 0; f < 6; ++f) featp[f] = from_lane(feat[f], p);
-        smup = from_lane(smu, p);
-        ssigp = from_lane(ssig, p);
-      }
-      if (act) {
-        const int ppx = x0 + (p & 7), ppy = y0 + (p >> 3);
-        const float dx = (float)ppx + 0.5f - st.f[0][j].x;
-        const float dy = (float)ppy + 0.5f - st.f[0][j].y;
-        RayG g = ray_params(st, j, dx, dy, lamp);
-        QEdges<NQ> e;
-        float qv;
-        if constexpr (kTrig) {
-          qv = particle_quadrature_trig<NH, NQ>(g, TLp, m0p, tn, a, e);
-        } else {
-          qv = particle_quadrature<NH, NQ>(g, pp, Lp, m0p, tn, a, e);
+        for (int f = 0; f < 6; ++f) featp[f] = feat[f];
+        if (!direct) {
+          m0p = from_lane(m0, p);
+          if constexpr (kTrig) {
+#pragma unroll
+            for (int i = 0; i < (NH + 1) * (NH + 2) / 2; ++i) {
+              TLp.re[i] = from_lane(TL.re[i], p);
+              TLp.im[i] = from_lane(TL.im[i], p);
+            }
+          } else {
+            pp.tc = from_lane(pb.tc, p);
+            pp.p = from_lane(pb.p, p);
+            pp.p15 = from_lane(pb.p15, p);
+            pp.amp = from_lane(pb.amp, p);
+#pragma unroll
+            for (int i = 0; i < (NH + 1) * (NH + 2) / 2; ++i) Lp.l[i] = from_lane(L.l[i], p);
+          }
+          lamp = from_lane(lam, p);
+          up = (float)(x0 + (p & 7)) + 0.5f;
+          vp = (float)(y0 + (p >> 3)) + 0.5f;
+          if constexpr (MODE == kModeHarvest) {
+#pragma unroll
+            for (int f = 0; f < 6; ++f) featp[f] = from_lane(feat[f], p);
+            smup = from_lane(smu, p);
+            ssigp = from_lane(ssig, p);
+          }
         }
-        if constexpr (MODE == kModeHarvest) {
-          const uint32_t rid = (uint32_t)a.sorted_rec[b + j];
-          const size_t pixp = ((size_t)ci * c.height + ppy) * c.width + ppx;
+        float4 c4 = make_float4(0.f, 0.f, 0.f, 0.f);
+        float pen = 0.f;
+        if (on) {
+          const RayG g = ray_params(st, j, up - st.f[0][j].x, vp - st.f[0][j].y, lamp);
+          QEdges<NQ> e;
+          float qv;
+          if constexpr (kTrig) {
+            qv = particle_quadrature_trig<NH, NQ>(g, TLp, m0p, tn, a, e);
+          } else {
+            qv = particle_quadrature<NH, NQ>(g, pp, Lp, m0p, tn, a, e);
+          }
+          if constexpr (MODE == kModeHarvest) {
+            const uint32_t rid = (uint32_t)a.sorted_rec[b + j];
+            const size_t pixp = ((size_t)ci * c.height + (y0 + (p >> 3))) * c.width + (x0 + (p & 7));
 #pragma unroll
-          for (int k = 0; k < NQ; ++k) {
-            const uint32_t h = mix_hash(a.seed, (uint32_t)pixp, rid * NQ + k);
-            if ((float)(h >> 8) * (1.f / 16777216.f) < a.harvest_rate) {
-              const int slot = atomicAdd(a.harvest_count, 1);
-              if (slot < a.harvest_cap) {
-                float* o = a.harvest + (size_t)slot * kHarvestStride;
+            for (int k = 0; k < NQ; ++k) {
+              const uint32_t h = mix_hash(a.seed, (uint32_t)pixp, rid * NQ + k);
+              if ((float)(h >> 8) * (1.f / 16777216.f) < a.harvest_rate) {
+                const int slot = atomicAdd(a.harvest_count, 1);
+                if (slot < a.harvest_cap) {
+                  float* o = a.harvest + (size_t)slot * kHarvestStride;
 #pragma unroll
-                for (int f = 0; f < 6; ++f) o[f] = featp[f];
-                o[6] = std_query(e.y[k], smup, ssigp);
-                o[7] = m0p;
-                o[8] = expf(-e.tau[k]);
-                o[9] = __uint_as_float(h);
-                o[10] = __int_as_float((int)pixp);
-                o[11] = __int_as_float((int)(rid * NQ + k));
+                  for (int f = 0; f < 6; ++f) o[f] = featp[f];
+                  o[6] = std_query(e.y[k], smup, ssigp);
+                  o[7] = m0p;
+                  o[8] = expf(-e.tau[k]);
+                  o[9] = __uint_as_float(h);
+                  o[10] = __int_as_float((int)pixp);
+                  o[11] = __int_as_float((int)(rid * NQ + k));
+                }
               }
             }
           }
+          const float4 f5 = st.f[5][j];
+          c4 = make_float4(qv * f5.y, qv * f5.z, qv * f5.w, qv);
+          if (want_pen) pen = pair_penalty<NQ>(g, tn, e, a);
         }
-        float4 f5 = st.f[5][j];
-        cb[lane] = make_float4(qv * f5.y, qv * f5.z, qv * f5.w, qv);
-        if (want_pen) cpen[lane] = pair_penalty<NQ>(g, tn, e, a);
-      }
-      __builtin_amdgcn_wave_barrier();
-      while (own) {
-        const int i = __builtin_ctzll(own);
-        own &= own - 1;
-        const float4 c4 = cb[i];
-        sr += c4.x;
-        sg += c4.y;
-        sb += c4.z;
-        so += c4.w;
-        if (want_pen) spen += cpen[i];
-      }
-      __builtin_amdgcn_wave_barrier();
-    };
-    for (int b = rg.x; b < rg.y; b += kBlock) {
-      int nb = min(kBlock, rg.y - b);
-      __syncthreads();
-      load_batch_covered(st, a.rec, a.sorted_rec, a.masks, bw.quad, b, nb);
-      __syncthreads();
-      QueueCursor qc;
-      queue_reset(qc);
-      queue_from_masks<true>(q, qc, a.masks, b, nb, quad, own4, lane, live_mask,
-                       [&]() __attribute__((always_inline)) {
-                         flush(64, qc.own_lo, b);
-                         queue_pop64(q, qc, lane);
-                       },
-                       [](int) {});
-      if (qc.cnt > 0) flush(qc.cnt, qc.own_lo, b);
+        if (direct) {
+          // zero in the lanes without a pair; rounded, not fused into the sums
+          // (as the queued results are)
+          asm("" : "+v"(c4.x), "+v"(c4.y), "+v"(c4.z), "+v"(pen));
+          sr += c4.x;
+          sg += c4.y;
+          sb += c4.z;
+          so += c4.w;
+          spen += pen;
+        } else {
+          cb[lane] = c4;
+          if (want_pen) cpen[lane] = pen;
+          __builtin_amdgcn_wave_barrier();
+          while (own) {
+            const int i = __builtin_ctzll(own);
+            own &= own - 1;
+            const float4 o4 = cb[i];
+            sr += o4.x;
+            sg += o4.y;
+            sb += o4.z;
+            so += o4.w;
+            if (want_pen) spen += cpen[i];
+          }
+          __builtin_amdgcn_wave_barrier();
+        }
+      });
     }
   }
 
@@ -637,29 +604,27 @@ __global__ __launch_bounds__(256) void k_render_consume(RenderArgs a, CamSet cam
     load_batch(st, a.rec, a.sorted_rec, b, nb);
     __syncthreads();
     // the pairs of the forward pass's coverage masks, in the emit pass's order
-    for_each_masked(a.masks, b, nb, wave, lane, [&](int j, uint64_t m) __attribute__((always_inline)) {
-      if (active && ((m >> lane) & 1ull)) {
-        const float dx = u - st.f[0][j].x, dy = v - st.f[0][j].y;
-        RayG g = ray_params(st, j, dx, dy, lam);
-        QEdges<NQ> e;
-        quad_edges<NQ>(g, pb, tn, a, e);
-        const float* fq = a.q_f + qbase + (long long)i_pair * NQ;
-        // the bounds the surrogate stands for grow with depth: its optical
-        // depth along the edges is made non-decreasing (running maximum; a
-        // later edge takes over only when strictly larger)
+    for_each_own_entry(a.masks, b, nb, wave, -1, lane, active, [&](int j) __attribute__((always_inline)) {
+      const float dx = u - st.f[0][j].x, dy = v - st.f[0][j].y;
+      RayG g = ray_params(st, j, dx, dy, lam);
+      QEdges<NQ> e;
+      quad_edges<NQ>(g, pb, tn, a, e);
+      const float* fq = a.q_f + qbase + (long long)i_pair * NQ;
+      // the bounds the surrogate stands for grow with depth: its optical
+      // depth along the edges is made non-decreasing (running maximum; a
+      // later edge takes over only when strictly larger)
 #pragma unroll
-        for (int k = 0; k < NQ; ++k) {
-          const float tk = m0 * fq[k];
-          e.tau[k] = (k == 0 || tk > e.tau[k > 0 ? k - 1 : 0]) ? tk : e.tau[k > 0 ? k - 1 : 0];
-        }
-        float q = quad_sum<NQ>(g, tn, e);
-        float4 f5 = st.f[5][j];
-        sr += q * f5.y;
-        sg += q * f5.z;
-        sb += q * f5.w;
-        so += q;
-        ++i_pair;
+      for (int k = 0; k < NQ; ++k) {
+        const float tk = m0 * fq[k];
+        e.tau[k] = (k == 0 || tk > e.tau[k > 0 ? k - 1 : 0]) ? tk : e.tau[k > 0 ? k - 1 : 0];
       }
+      float q = quad_sum<NQ>(g, tn, e);
+      float4 f5 = st.f[5][j];
+      sr += q * f5.y;
+      sg += q * f5.z;
+      sb += q * f5.w;
+      so += q;
+      ++i_pair;
     });
   }
   if (!inside) return;
@@ -709,72 +674,72 @@ __global__ __launch_bounds__(256) void k_render_consume_tab(RenderArgs a, CamSet
   const PixelBasis pb = make_basis(inside ? pf[7] : tn, inside ? pf[8] : 1.f, tn);
   const float smu = inside ? pf[10] : 0.f, isig = inside ? 1.f / pf[11] : 1.f;
   const float ucoef = (float)(a.tab_nodes - 1) / (2.f * kTabZ);
-  const uint64_t active_mask = __ballot(active);
   WaveQueue& q = wq[wave];
   float4* res = wres[wave];
   float sr = 0.f, sg = 0.f, sb = 0.f, so = 0.f;
-  // as the quadrature pass of k_render_fwd: covering pairs evaluated 64 at a
-  // time, one per lane, the results added by the pixel's own lane in list order
-  auto flush = [&](int n, uint64_t own) __attribute__((always_inline)) {
-    const bool act = lane < n;
-    const int it = act ? (int)q.item[lane] : lane;
-    const int j = act ? (it >> 6) : 0;
-    const int p = it & 63;
-    PixelBasis pp;
-    pp.tc = from_lane(pb.tc, p);
-    pp.p = from_lane(pb.p, p);
-    pp.p15 = from_lane(pb.p15, p);
-    pp.amp = from_lane(pb.amp, p);
-    const float m0p = from_lane(m0, p), lamp = from_lane(lam, p);
-    const float smup = from_lane(smu, p), isigp = from_lane(isig, p);
-    if (act) {
-      const int ppx = x0 + (p & 7), ppy = y0 + (p >> 3);
-      const float dx = (float)ppx + 0.5f - st.f[0][j].x;
-      const float dy = (float)ppy + 0.5f - st.f[0][j].y;
-      RayG g = ray_params(st, j, dx, dy, lamp);
-      QEdges<NQ> e;
-      quad_edges<NQ>(g, pp, tn, a, e);
-      const float* tp = a.tab + (((size_t)ci * c.height + ppy) * c.width + ppx) * a.tab_nodes;
-#pragma unroll
-      for (int k = 0; k < NQ; ++k) {
-        const float z = fminf(fmaxf((e.y[k] - smup) * isigp, -kTabZ), kTabZ);
-        const float uu = (z + kTabZ) * ucoef;
-        const int i0 = min((int)uu, a.tab_nodes - 2);
-        const float fr = uu - (float)i0;
-        const float f = fmaf(fr, tp[i0 + 1] - tp[i0], tp[i0]);
-        const float tk = m0p * f;
-        e.tau[k] = (k == 0 || tk > e.tau[k > 0 ? k - 1 : 0]) ? tk : e.tau[k > 0 ? k - 1 : 0];
-      }
-      const float qv = quad_sum<NQ>(g, tn, e);
-      const float4 f5 = st.f[5][j];
-      res[lane] = make_float4(qv * f5.y, qv * f5.z, qv * f5.w, qv);
-    }
-    __builtin_amdgcn_wave_barrier();
-    while (own) {
-      const int i = __builtin_ctzll(own);
-      own &= own - 1;
-      const float4 c4 = res[i];
-      sr += c4.x;
-      sg += c4.y;
-      sb += c4.z;
-      so += c4.w;
-    }
-    __builtin_amdgcn_wave_barrier();
-  };
   for (int b = rg.x; b < rg.y; b += kBlock) {
     int nb = min(kBlock, rg.y - b);
     __syncthreads();
     load_batch_covered(st, a.rec, a.sorted_rec, a.masks, -1, b, nb);
     __syncthreads();
-    QueueCursor qc;
-    queue_reset(qc);
-    queue_from_masks<true>(q, qc, a.masks, b, nb, wave, -1, lane, active_mask,
-                           [&]() __attribute__((always_inline)) {
-                             flush(64, qc.own_lo);
-                             queue_pop64(q, qc, lane);
-                           },
-                           [](int) {});
-    if (qc.cnt > 0) flush(qc.cnt, qc.own_lo);
+    // as the quadrature pass of k_render_fwd
+    walk_pairs(q, a.masks, b, nb, wave, -1, lane, active,
+               [&](bool direct, bool on, int j, int p, uint64_t own) __attribute__((always_inline)) {
+      PixelBasis pp = pb;
+      float m0p = m0, lamp = lam, smup = smu, isigp = isig;
+      if (!direct) {
+        pp.tc = from_lane(pb.tc, p);
+        pp.p = from_lane(pb.p, p);
+        pp.p15 = from_lane(pb.p15, p);
+        pp.amp = from_lane(pb.amp, p);
+        m0p = from_lane(m0, p);
+        lamp = from_lane(lam, p);
+        smup = from_lane(smu, p);
+        isigp = from_lane(isig, p);
+      }
+      float4 c4 = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (on) {
+        const int ppx = x0 + (p & 7), ppy = y0 + (p >> 3);
+        const float dx = (float)ppx + 0.5f - st.f[0][j].x;
+        const float dy = (float)ppy + 0.5f - st.f[0][j].y;
+        RayG g = ray_params(st, j, dx, dy, lamp);
+        QEdges<NQ> e;
+        quad_edges<NQ>(g, pp, tn, a, e);
+        const float* tp = a.tab + (((size_t)ci * c.height + ppy) * c.width + ppx) * a.tab_nodes;
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) {
+          const float z = fminf(fmaxf((e.y[k] - smup) * isigp, -kTabZ), kTabZ);
+          const float uu = (z + kTabZ) * ucoef;
+          const int i0 = min((int)uu, a.tab_nodes - 2);
+          const float fr = uu - (float)i0;
+          const float f = fmaf(fr, tp[i0 + 1] - tp[i0], tp[i0]);
+          const float tk = m0p * f;
+          e.tau[k] = (k == 0 || tk > e.tau[k > 0 ? k - 1 : 0]) ? tk : e.tau[k > 0 ? k - 1 : 0];
+        }
+        const float qv = quad_sum<NQ>(g, tn, e);
+        const float4 f5 = st.f[5][j];
+        c4 = make_float4(qv * f5.y, qv * f5.z, qv * f5.w, qv);
+      }
+      if (direct) {
+        sr += c4.x;
+        sg += c4.y;
+        sb += c4.z;
+        so += c4.w;
+      } else {
+        res[lane] = c4;
+        __builtin_amdgcn_wave_barrier();
+        while (own) {
+          const int i = __builtin_ctzll(own);
+          own &= own - 1;
+          const float4 o4 = res[i];
+          sr += o4.x;
+          sg += o4.y;
+          sb += o4.z;
+          so += o4.w;
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    });
   }
   if (!inside) return;
   float alpha = -expm1f(-m0);

@@ -1,0 +1,37 @@
+"""The forward kernel's walk of a tile's list by pixel words: list lengths at the
+edges of its 64-entry chunks, 256-entry batches and the heavy-tile split (512),
+with every pixel covered (all rounds full) and with coverage of every kind (thin
+rounds queued), on ragged images, against the oracle."""
+import pytest
+import torch
+
+import oracle
+import workloads as W
+from tests.gpu_helpers import compare, gpu_render, log, proxy_error, tolerances
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 256, 257, 512, 513, 700])
+@pytest.mark.parametrize("full,k_mom", [(True, 4), (False, 4), (False, 6), (False, 8)])
+def test_list_lengths_match_oracle(n, full, k_mom):
+    scene = W.uniform_scene(n, seed=n, extent=0.25, log_scale_mean=-2.5)
+    cam = W.camera_on_axis(2.0, 21, 18)
+    opts = W.Options(n_moments=k_mom, full_coverage=full)
+    img, saved, st = gpu_render(scene, [cam], opts)
+    tol_m, tol_o = (0.0, 0.0) if full else tolerances(proxy_error(scene, cam, opts))
+    ref = oracle.render_image(scene, cam, opts, margin_tol=tol_m, orient_eps=tol_o)
+    log(f"[walk] n {n} full {full} K {k_mom}: {st.n_entries} entries, {ref['n_pairs']} pairs")
+    mx, _ = compare(img[0].reshape(-1, 3), ref, f"walk n={n}", gpu_saved=saved[0].reshape(-1, 8))
+    assert mx <= 1e-4  # the parity bar
+
+
+def test_walk_covers_each_pair_once():
+    """saved[7] counts the covering Gaussians; with full coverage that is every one."""
+    import paper_2512_11800_amd as M
+    for n in (5, 64, 129, 300, 530):
+        scene = W.uniform_scene(n, seed=3, extent=0.25)
+        g = M.Gaussians.from_scene(scene)
+        _, saved, _ = M.render_forward(g, [W.camera_on_axis(2.0, 17, 33)], W.Options(full_coverage=True))
+        c = saved[..., 7]
+        assert torch.equal(torch.where(c < 0, -c - 1, c), torch.full_like(c, float(n)))
