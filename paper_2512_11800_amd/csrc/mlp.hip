@@ -10,7 +10,9 @@
 //   layer 2  Z2[64x64] = H1[64x64] W2^T,   H1 = bf16(GELU(Z1 + b1));
 //   layer 3  out = GELU(Z2 + b2) . w3 + b3, reduced through LDS;
 // and the training step adds dW2 = dZ2^T H1, dH1 = dZ2 W2, dW1 = dZ1^T X on
-// the same instruction. MFMA operand layout (wave64, 32x32x16): lane l holds
+// the same instruction. The inference kernels form the transposed products
+// (weights times activations, see RegMlp) with the activations in registers from
+// layer to layer. MFMA operand layout (wave64, 32x32x16): lane l holds
 // A[l % 32][8 (l / 32) + e] and B[8 (l / 32) + e][l % 32], e = 0..7, and
 // accumulator element r of lane l is C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
 #include "kernels.h"
@@ -119,15 +121,8 @@ __global__ __launch_bounds__(256) void k_mlp_pack(const float* th, MlpPacked* p)
   }
 }
 
-// LDS working sets of one wave. The layer-3 row sums reuse the H1 (or dZ2)
+// LDS working set of one training wave. The layer-3 row sums reuse the dZ2
 // storage once the matrix-core reads of it are complete (barrier between).
-struct FwdLds {
-  uint16_t x[64][kXStride];  // inputs, hi/lo bf16
-  union {
-    uint16_t h1[64][kH + 8];  // H1 [q][k] (rows padded against bank conflicts)
-    float s[64][33];          // layer-3 partial sums [q][column]
-  };
-};
 struct TrainLds {
   uint16_t x[64][kXStride];
   uint16_t xt[32][64 + 8];   // X^T [k][q], rows 16..31 zero
@@ -241,228 +236,412 @@ __device__ __forceinline__ float mlp_forward_wave(L& w, const MlpPacked& P, int 
 
 __device__ __forceinline__ float sigmoid(float x) { return fast_rcp(1.f + __expf(-x)); }
 
-__global__ __launch_bounds__(256) void k_mlp_forward(const MlpPacked* gp, const float* x, int64_t n, float* f_out) {
-  __shared__ MlpPacked P;
-  __shared__ FwdLds ws[4];
-  {
-    const float4* src = reinterpret_cast<const float4*>(gp);
-    float4* dst = reinterpret_cast<float4*>(&P);
-    for (int i = threadIdx.x; i < (int)(sizeof(MlpPacked) / 16); i += blockDim.x) dst[i] = src[i];
+// ---------------------------------------------------------------------------
+// Inference with the activations in registers. A wave takes 64 queries as two
+// tiles of 32 and forms the transposed products Z^T = W H^T: lane l then holds
+// the column of query l % 32, accumulator element r its neuron 8 (r / 4) +
+// 4 (l / 32) + r % 4. Rounded to bf16 pairs, eight consecutive elements of a
+// lane are half a k-block of the next layer's B operand; exchanging the middle
+// quarters between the wave's halves (permlane32_swap) puts them in the operand's
+// order, so H1 never visits LDS. The weights stay in registers for all of a
+// wave's queries. Each product and sum keeps the order of the row-wise form, so
+// the outputs do not depend on the form.
+//
+// Bound by the GELUs on the vector unit: 64 evaluations of about 34 issue cycles
+// per lane and tile (16 of them the two transcendentals), of 2700 a tile in all,
+// beside 10 matrix instructions of 32 cycles on the matrix pipe. Measured, with
+// H1 and the weights passed through LDS before: 68.4 M nodes of tables
+// 3.95 -> 3.05 ms, the query list of a surrogate step (960 x 540) 581 -> 462 us.
+// Two to four waves a SIMD and one or two tiles a step time alike within 5%.
+// ---------------------------------------------------------------------------
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));  // nearest even
+}
+// a's upper half-wave changes places with b's lower one
+__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+  uint32_t u = __float_as_uint(a), v = __float_as_uint(b);
+  swap_halves(u, v);
+  a = __uint_as_float(u);
+  b = __uint_as_float(v);
+}
+
+struct RegWeights {
+  bf16x8 w1[2], w2[2][4];  // A operands: neurons 32 t + l % 32, k-block
+};
+
+__device__ __forceinline__ bf16x8 global_bf16x8(const uint16_t* p) { return *reinterpret_cast<const bf16x8*>(p); }
+
+__device__ __forceinline__ RegWeights load_weights(const MlpPacked* P, int lane) {
+  RegWeights w;
+  const int lr = lane & 31, hk = 8 * (lane >> 5);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    w.w1[t] = global_bf16x8(&P->w1[32 * t + lr][hk]);
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) w.w2[t][kt] = global_bf16x8(&P->w2[32 * t + lr][16 * kt + hk]);
+  }
+  return w;
+}
+
+// B operand of layer 1 for this lane's query (its kIn inputs v): k = 0..6 the
+// bf16 values, 7..13 what they leave of the inputs, 14, 15 zero
+__device__ __forceinline__ bf16x8 input_operand(const float* v, int lane) {
+  float lo[kIn];
+  uint32_t hi[4];
+#pragma unroll
+  for (int k = 0; k < kIn; k += 2) {
+    const float v1 = k + 1 < kIn ? v[k + 1] : 0.f;
+    hi[k / 2] = pack_bf16(v[k], v1);
+    lo[k] = v[k] - __uint_as_float(hi[k / 2] << 16);
+    if (k + 1 < kIn) lo[k + 1] = v1 - __uint_as_float(hi[k / 2] & 0xffff0000u);
+  }
+  const uint32_t l0 = pack_bf16(lo[0], 0.f);
+  const bool up = lane >= 32;
+  uint4 o;
+  o.x = up ? pack_bf16(lo[1], lo[2]) : hi[0];
+  o.y = up ? pack_bf16(lo[3], lo[4]) : hi[1];
+  o.z = up ? pack_bf16(lo[5], lo[6]) : hi[2];
+  o.w = up ? 0u : (hi[3] | (l0 << 16));
+  return __builtin_bit_cast(bf16x8, o);
+}
+
+// the bf16 B operands of the next product from this lane's 64-neuron column
+// z[2] (elements as above)
+__device__ __forceinline__ void column_operand(const f32x16* z, bf16x8* op) {
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      uint4 o;
+      o.x = pack_bf16(z[t][8 * s + 0], z[t][8 * s + 1]);
+      o.y = pack_bf16(z[t][8 * s + 2], z[t][8 * s + 3]);
+      o.z = pack_bf16(z[t][8 * s + 4], z[t][8 * s + 5]);
+      o.w = pack_bf16(z[t][8 * s + 6], z[t][8 * s + 7]);
+      swap_halves(o.x, o.z);
+      swap_halves(o.y, o.w);
+      op[2 * t + s] = __builtin_bit_cast(bf16x8, o);
+    }
+}
+
+// Layers 1 and 2 of a tile's 32 queries and the terms of layer 3: s[r] = the
+// output terms of neurons n and n + 32 for n = 8 (r / 4) + 4 (l / 32) + r % 4.
+// GRAD: d1, d2 receive GELU' at the two layers.
+struct RowConsts {
+  float b1[kH], b2[kH], w3[kH];
+};
+template <bool GRAD>
+__device__ __forceinline__ void mlp_tile(const RegWeights& w, const RowConsts& c, bf16x8 x, int lane, float* s,
+                                         f32x16* d1, f32x16* d2) {
+  const int h4 = 4 * (lane >> 5);
+  f32x16 z[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    z[t] = mfma(w.w1[t], x, f32x16{});
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 b = *reinterpret_cast<const float4*>(&c.b1[32 * t + 8 * g + h4]);
+      const float bb[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float d;
+        z[t][4 * g + j] = gelu_d(z[t][4 * g + j] + bb[j], d);
+        if constexpr (GRAD) d1[t][4 * g + j] = d;
+      }
+    }
+  }
+  bf16x8 op[4];
+  column_operand(z, op);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    z[t] = f32x16{};
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) z[t] = mfma(w.w2[t][kt], op[kt], z[t]);
+  }
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 b = *reinterpret_cast<const float4*>(&c.b2[32 * t + 8 * g + h4]);
+      const float4 q = *reinterpret_cast<const float4*>(&c.w3[32 * t + 8 * g + h4]);
+      const float bb[4] = {b.x, b.y, b.z, b.w}, qq[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float d;
+        const float a = gelu_d(z[t][4 * g + j] + bb[j], d);
+        if constexpr (GRAD) d2[t][4 * g + j] = d;
+        s[4 * g + j] = t == 0 ? a * qq[j] : fmaf(a, qq[j], s[4 * g + j]);
+      }
+    }
+}
+
+// the output pre-activation from a query's 32 terms in neuron order: lo[r] of the
+// neurons with an even quarter, hi[r] of the others
+__device__ __forceinline__ float sum_terms(float b3, const float* lo, const float* hi) {
+  float out = b3;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) out += lo[4 * g + j];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) out += hi[4 * g + j];
+  }
+  return out;
+}
+
+__device__ __forceinline__ void stage_consts(RowConsts& c, const MlpPacked* P) {
+  for (int i = threadIdx.x; i < kH; i += blockDim.x) {
+    c.b1[i] = P->b1[i];
+    c.b2[i] = P->b2[i];
+    c.w3[i] = P->w3[i];
   }
   __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  FwdLds& w = ws[wave];
-  const int64_t chunks = (n + 63) / 64;
-  const int64_t per_block = ((chunks + gridDim.x - 1) / gridDim.x + 3) / 4 * 4;  // uniform per block
-  for (int64_t it = 0; it < per_block; it += 4) {
-    int64_t chunk = (int64_t)blockIdx.x * per_block + it + wave;
-    int64_t q = chunk * 64 + lane;
-    bool valid = q < n;
-    float m0;
-    load_inputs(w, x, q, valid, lane, m0);
-    __syncthreads();
-    f32x16 z1[2][2], z2[2][2];
-    float out = mlp_forward_wave(w, P, lane, z1, z2);
-    if (valid) f_out[q] = sigmoid(out);
+}
+
+// F of the n queries, 64 a wave and step. A source (q, step) stands at query q,
+// loads its inputs (zeros beyond the list) and moves on by step.
+template <class Source, class Output>
+__device__ __forceinline__ void mlp_queries(const MlpPacked* P, int64_t n, const Source& src, Output&& output) {
+  __shared__ __align__(16) RowConsts c;
+  stage_consts(c, P);
+  const int lane = threadIdx.x & 63, lr = lane & 31;
+  const RegWeights w = load_weights(P, lane);
+  const float b3 = P->b3;
+  const int64_t step = (int64_t)gridDim.x * (blockDim.x >> 6) * 64;
+  int64_t q0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 64;
+  if (q0 >= n) return;
+  Source in[2] = {src, src};
+  float v[2][kIn];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    in[t].start(q0 + 32 * t + lr, step);
+    in[t].load(v[t]);
+  }
+  for (; q0 < n; q0 += step) {
+    const bf16x8 x[2] = {input_operand(v[0], lane), input_operand(v[1], lane)};
+    if (q0 + step < n) {  // the next step's inputs load behind this one's arithmetic
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        in[t].advance();
+        in[t].load(v[t]);
+      }
+    }
+    float s[2][16];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      asm volatile("" ::: "memory");  // the constants are read anew, not kept in 96 registers
+      mlp_tile<false>(w, c, x[t], lane, s[t], nullptr, nullptr);
+    }
+    // tile 0's queries to the lower half-wave, tile 1's to the upper
+#pragma unroll
+    for (int r = 0; r < 16; ++r) swap_halves(s[0][r], s[1][r]);
+    const int64_t q = q0 + lane;
+    const float f = sigmoid(sum_terms(b3, s[0], s[1]));
+    if (q < n) output(q, f);
   }
 }
 
-// The same network on the render's query list: the inputs of query i are the
-// six features of pixel q_pix[i] and the standardised query q_z[i]. The
-// number of queries is read on the device (the render pass appends them).
-__global__ __launch_bounds__(256) void k_mlp_forward_gather(const MlpPacked* gp, const float* pixfeat, const int* q_pix,
-                                                            const float* q_z, const unsigned long long* q_count,
-                                                            int64_t q_cap, int64_t n_pix, float* f_out) {
-  __shared__ MlpPacked P;
-  __shared__ FwdLds ws[4];
+struct RowSource {  // x [n][8]: a fit's rows
+  const float* x;
+  int64_t n, q = 0, by = 0;
+  __device__ RowSource(const float* x_, int64_t n_) : x(x_), n(n_) {}
+  __device__ __forceinline__ void start(int64_t q_, int64_t step) {
+    q = q_;
+    by = step;
+  }
+  __device__ __forceinline__ void advance() { q += by; }
+  __device__ __forceinline__ void load(float* v) const {
+    const bool valid = q < n;
+    const float* r = x + (valid ? q : 0) * 8;
+#pragma unroll
+    for (int k = 0; k < kIn; ++k) v[k] = valid ? r[k] : 0.f;
+  }
+};
+
+// the render's query list: the six features of pixel pix[q] (slots of a list that
+// overflowed may hold no query: their pixel index is kept inside the image, their
+// outputs are never read) and the standardised query z[q]
+struct GatherSource {
+  const float* feat;
+  const int* pix;
+  const float* z;
+  int64_t n_pix, n, q = 0, by = 0;
+  __device__ GatherSource(const float* feat_, const int* pix_, const float* z_, int64_t n_pix_, int64_t n_)
+      : feat(feat_), pix(pix_), z(z_), n_pix(n_pix_), n(n_) {}
+  __device__ __forceinline__ void start(int64_t q_, int64_t step) {
+    q = q_;
+    by = step;
+  }
+  __device__ __forceinline__ void advance() { q += by; }
+  __device__ __forceinline__ void load(float* v) const {
+    const bool valid = q < n;
+    int64_t p = valid ? (int64_t)pix[q] : 0;
+    p = (p >= 0 && p < n_pix) ? p : 0;
+    const float* f = feat + p * kPixFeat;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[k] = valid ? f[k] : 0.f;
+    v[6] = valid ? z[q] : 0.f;
+  }
+};
+
+// the nodes of every pixel's table: entry q = p n_nodes + g takes the features of
+// pixel p and the standardised query -kTabZ + g 2 kTabZ / (n_nodes - 1)
+struct TableSource {
+  const float* feat;
+  int64_t n_pix, p = 0, dp = 0;
+  int n_nodes, g = 0, dg = 0;
+  float dz;
+  __device__ TableSource(const float* feat_, int64_t n_pix_, int n_nodes_)
+      : feat(feat_), n_pix(n_pix_), n_nodes(n_nodes_), dz(2.f * kTabZ / (float)(n_nodes_ - 1)) {}
+  __device__ __forceinline__ void start(int64_t q, int64_t step) {
+    p = q / n_nodes;
+    g = (int)(q - p * n_nodes);
+    dp = step / n_nodes;
+    dg = (int)(step - dp * n_nodes);
+  }
+  __device__ __forceinline__ void advance() {
+    p += dp;
+    g += dg;
+    if (g >= n_nodes) {
+      g -= n_nodes;
+      ++p;
+    }
+  }
+  __device__ __forceinline__ void load(float* v) const {
+    const bool valid = p < n_pix;
+    const float* f = feat + (valid ? p : 0) * kPixFeat;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) v[k] = valid ? f[k] : 0.f;
+    v[6] = -kTabZ + dz * (float)g;
+  }
+};
+
+__global__ __launch_bounds__(256, 3) void k_mlp_forward(const MlpPacked* P, const float* x, int64_t n, float* f_out) {
+  mlp_queries(P, n, RowSource(x, n), [&](int64_t q, float f) __attribute__((always_inline)) { f_out[q] = f; });
+}
+
+// The number of queries is read on the device (the render pass appends them).
+__global__ __launch_bounds__(256, 3) void k_mlp_forward_gather(const MlpPacked* P, const float* pixfeat,
+                                                               const int* q_pix, const float* q_z,
+                                                               const unsigned long long* q_count, int64_t q_cap,
+                                                               int64_t n_pix, float* f_out) {
   const unsigned long long cnt = *q_count;
   const int64_t n = cnt < (unsigned long long)q_cap ? (int64_t)cnt : q_cap;
-  if (n == 0) return;
-  {
-    const float4* src = reinterpret_cast<const float4*>(gp);
-    float4* dst = reinterpret_cast<float4*>(&P);
-    for (int i = threadIdx.x; i < (int)(sizeof(MlpPacked) / 16); i += blockDim.x) dst[i] = src[i];
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  FwdLds& w = ws[wave];
-  const int64_t chunks = (n + 63) / 64;
-  const int64_t per_block = ((chunks + gridDim.x - 1) / gridDim.x + 3) / 4 * 4;
-  for (int64_t it = 0; it < per_block; it += 4) {
-    int64_t q = ((int64_t)blockIdx.x * per_block + it + wave) * 64 + lane;
-    bool valid = q < n;
-    float v[kIn];
-    // slots of a list that overflowed may hold no query: keep their pixel
-    // index inside the image (their outputs are never read)
-    int64_t p = valid ? (int64_t)q_pix[q] : 0;
-    p = (p >= 0 && p < n_pix) ? p : 0;
-    const float* pf = pixfeat + (size_t)p * kPixFeat;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) v[k] = valid ? pf[k] : 0.f;
-    v[6] = valid ? q_z[q] : 0.f;
-    stage_inputs(w, v, lane);
-    __syncthreads();
-    f32x16 z1[2][2], z2[2][2];
-    float out = mlp_forward_wave(w, P, lane, z1, z2);
-    if (valid) f_out[q] = sigmoid(out);
-  }
+  mlp_queries(P, n, GatherSource(pixfeat, q_pix, q_z, n_pix, n),
+              [&](int64_t q, float f) __attribute__((always_inline)) { f_out[q] = f; });
 }
 
-// The network at the nodes of every pixel's table (the tabulated schedule):
-// entry q = p * n_nodes + g takes the six features of pixel p and the
-// standardised query z_g = -kTabZ + g 2 kTabZ / (n_nodes - 1).
-__global__ __launch_bounds__(256) void k_mlp_table(const MlpPacked* gp, const float* pixfeat, int64_t n_pix,
-                                                   int n_nodes, float* tab) {
-  __shared__ MlpPacked P;
-  __shared__ FwdLds ws[4];
-  const int64_t n = n_pix * n_nodes;
-  {
-    const float4* src = reinterpret_cast<const float4*>(gp);
-    float4* dst = reinterpret_cast<float4*>(&P);
-    for (int i = threadIdx.x; i < (int)(sizeof(MlpPacked) / 16); i += blockDim.x) dst[i] = src[i];
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  FwdLds& w = ws[wave];
-  const float dz = 2.f * kTabZ / (float)(n_nodes - 1);
-  const int64_t chunks = (n + 63) / 64;
-  const int64_t per_block = ((chunks + gridDim.x - 1) / gridDim.x + 3) / 4 * 4;
-  for (int64_t it = 0; it < per_block; it += 4) {
-    const int64_t q = ((int64_t)blockIdx.x * per_block + it + wave) * 64 + lane;
-    const bool valid = q < n;
-    const int64_t p = valid ? q / n_nodes : 0;
-    const int g = valid ? (int)(q - p * n_nodes) : 0;
-    const float* pf = pixfeat + (size_t)p * kPixFeat;
-    float v[kIn];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) v[k] = valid ? pf[k] : 0.f;
-    v[6] = -kTabZ + dz * (float)g;
-    stage_inputs(w, v, lane);
-    __syncthreads();
-    f32x16 z1[2][2], z2[2][2];
-    float out = mlp_forward_wave(w, P, lane, z1, z2);
-    if (valid) tab[q] = sigmoid(out);
-  }
+// tab [n_pix][n_nodes]: the tabulated schedule's F
+__global__ __launch_bounds__(256, 3) void k_mlp_table(const MlpPacked* P, const float* pixfeat, int64_t n_pix,
+                                                      int n_nodes, float* tab) {
+  mlp_queries(P, n_pix * n_nodes, TableSource(pixfeat, n_pix, n_nodes),
+              [&](int64_t q, float f) __attribute__((always_inline)) { tab[q] = f; });
 }
 
 // F and its gradient dF/dx with respect to the 7 inputs for every query of
-// the render's list (for the backward pass through the surrogate): the
-// forward pass as above, then dZ2 = F (1 - F) w3 GELU'(Z2) (bf16) on the
-// matrix cores against W2, dZ1 = dH1 GELU'(Z1) (bf16, staged by rows) and
-// dx = dZ1 W1 on the vector unit. Two waves per workgroup; the H1 storage is
-// reused for dZ2 and then dZ1. out: [cap][8] = F, dF/dx_0..6.
-struct GradInLds {
-  uint16_t x[64][kXStride];
-  union {
-    uint16_t h1[64][kH + 8];
-    float s[64][33];
-    uint16_t dz[64][kH + 8];
-  };
-  float dout[64];
-};
-
-__global__ __launch_bounds__(128) void k_mlp_input_grad_gather(const MlpPacked* gp, const float* pixfeat,
+// the render's list (for the backward pass through the surrogate): the forward
+// tile with its GELU' kept, then dZ2 = F (1 - F) w3 GELU'(Z2) (bf16) against W2
+// and dZ1 = dH1 GELU'(Z1) (bf16) as the forward's transposed products, and
+// dx = dZ1 W1 on the vector unit: the halves of the wave exchange their neurons,
+// the lower sums dx_0..2, the upper dx_3..6. out: [cap][8] = F, dF/dx_0..6.
+// Bound by vector issue, 5300 cycles per 32 queries (GELU' adds 8 fused
+// operations to each GELU, dx 256): 2277 -> 1062 us for the queries of a surrogate
+// step (960 x 540), where the activations and both layers' products passed through
+// LDS before and each GELU was evaluated twice.
+__global__ __launch_bounds__(256, 2) void k_mlp_input_grad_gather(const MlpPacked* P, const float* pixfeat,
                                                                const int* q_pix, const float* q_z,
                                                                const unsigned long long* q_count, int64_t q_cap,
                                                                int64_t n_pix, float* out_g) {
-  __shared__ MlpPacked P;
-  __shared__ GradInLds ws[2];
+  __shared__ __align__(16) RowConsts c;
+  __shared__ __align__(16) uint16_t w2t[kH][kH + 8];  // W2^T, rows apart in the banks
+  __shared__ __align__(16) float w1g[kH][8];  // W1 rows by neuron: 0, dx_0..2 | dx_3..6
   const unsigned long long cnt = *q_count;
   const int64_t n = cnt < (unsigned long long)q_cap ? (int64_t)cnt : q_cap;
-  if (n == 0) return;
-  {
-    const float4* src = reinterpret_cast<const float4*>(gp);
-    float4* dst = reinterpret_cast<float4*>(&P);
-    for (int i = threadIdx.x; i < (int)(sizeof(MlpPacked) / 16); i += blockDim.x) dst[i] = src[i];
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int lr = lane & 31, hk = 8 * (lane >> 5);
-  GradInLds& w = ws[wave];
-  const int64_t chunks = (n + 63) / 64;
-  const int64_t per_block = ((chunks + gridDim.x - 1) / gridDim.x + 1) / 2 * 2;
-  for (int64_t it = 0; it < per_block; it += 2) {
-    int64_t q = ((int64_t)blockIdx.x * per_block + it + wave) * 64 + lane;
-    bool valid = q < n;
-    float v[kIn];
-    int64_t p = valid ? (int64_t)q_pix[q] : 0;
-    p = (p >= 0 && p < n_pix) ? p : 0;
-    const float* pf = pixfeat + (size_t)p * kPixFeat;
+  for (int i = threadIdx.x; i < kH * kH / 8; i += blockDim.x)
+    *reinterpret_cast<bf16x8*>(&w2t[i / 8][8 * (i % 8)]) = global_bf16x8(&P->w2t[i / 8][8 * (i % 8)]);
+  for (int i = threadIdx.x; i < kH * 8; i += blockDim.x) w1g[i >> 3][i & 7] = (i & 7) ? P->w1f[(i & 7) - 1][i >> 3] : 0.f;
+  stage_consts(c, P);
+  const int lane = threadIdx.x & 63, lr = lane & 31, half = lane >> 5;
+  const RegWeights w = load_weights(P, lane);
+  const float b3 = P->b3;
+  const int64_t step = (int64_t)gridDim.x * (blockDim.x >> 6) * 32;
+  int64_t q0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 32;
+  if (q0 >= n) return;
+  GatherSource in(pixfeat, q_pix, q_z, n_pix, n);
+  float v[kIn];
+  in.start(q0 + lr, step);
+  in.load(v);
+  for (; q0 < n; q0 += step) {
+    const bf16x8 x = input_operand(v, lane);
+    if (q0 + step < n) {
+      in.advance();
+      in.load(v);
+    }
+    float s[16], t[16];
+    f32x16 d1[2], d2[2];
+    asm volatile("" ::: "memory");  // the constants are read anew, not kept in registers
+    mlp_tile<true>(w, c, x, lane, s, d1, d2);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) v[k] = valid ? pf[k] : 0.f;
-    v[6] = valid ? q_z[q] : 0.f;
-    stage_inputs(w, v, lane);
-    __syncthreads();
-    f32x16 z1[2][2], z2[2][2];
-    float out = mlp_forward_wave(w, P, lane, z1, z2);
-    const float f = sigmoid(out);
-    w.dout[lane] = f * (1.f - f);
-    __syncthreads();
-    // dZ2 = dF/dout w3 GELU'(Z2), bf16, rows [q][n]
+    for (int r = 0; r < 16; ++r) {  // both halves end with all of the query's terms
+      t[r] = s[r];
+      swap_halves(s[r], t[r]);
+    }
+    const float f = sigmoid(sum_terms(b3, s, t));
+    const float dout = f * (1.f - f);
+    // dZ2, then dH1^T = W2^T dZ2^T
+    f32x16 dz[2];
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        int n2 = 32 * nt + lr;
+      for (int g = 0; g < 4; ++g) {
+        const float4 q = *reinterpret_cast<const float4*>(&c.w3[32 * m + 8 * g + 4 * half]);
+        const float qq[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          int qq = 32 * mt + c_row(r, lane);
-          float d;
-          gelu_d(z2[mt][nt][r], d);
-          w.dz[qq][n2] = bf16_bits(w.dout[qq] * P.w3[n2] * d);
+        for (int j = 0; j < 4; ++j) dz[m][4 * g + j] = dout * qq[j] * d2[m][4 * g + j];
+      }
+    bf16x8 op[4];
+    column_operand(dz, op);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      dz[m] = f32x16{};
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) dz[m] = mfma(lds_bf16x8(&w2t[32 * m + lr][16 * kt + 8 * half]), op[kt], dz[m]);
+    }
+    // dZ1 (bf16) and dx, neuron by neuron
+    float gx[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        uint32_t a[2], b[2];  // neurons 8 g + 4 half + (0, 1), (2, 3), then those of both halves
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          a[j] = pack_bf16(dz[m][4 * g + 2 * j] * d1[m][4 * g + 2 * j],
+                           dz[m][4 * g + 2 * j + 1] * d1[m][4 * g + 2 * j + 1]);
+          b[j] = a[j];
+          swap_halves(a[j], b[j]);
+        }
+        const uint32_t u[4] = {a[0], a[1], b[0], b[1]};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float dzv = __uint_as_float((e & 1) ? (u[e >> 1] & 0xffff0000u) : (u[e >> 1] << 16));
+          const float4 wr = *reinterpret_cast<const float4*>(&w1g[32 * m + 8 * g + e][4 * half]);
+          gx[0] = fmaf(dzv, wr.x, gx[0]);
+          gx[1] = fmaf(dzv, wr.y, gx[1]);
+          gx[2] = fmaf(dzv, wr.z, gx[2]);
+          gx[3] = fmaf(dzv, wr.w, gx[3]);
         }
       }
-    __syncthreads();
-    // dH1 = dZ2 W2
-    f32x16 dh1[2][2];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        f32x16 acc = {};
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
-          acc = mfma(lds_bf16x8(&w.dz[32 * mt + lr][16 * kt + hk]), lds_bf16x8(&P.w2t[32 * nt + lr][16 * kt + hk]),
-                     acc);
-        dh1[mt][nt] = acc;
-      }
-    __syncthreads();
-    // dZ1 = dH1 GELU'(Z1), bf16, rows [q][n]
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        int n1 = 32 * nt + lr;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          int qq = 32 * mt + c_row(r, lane);
-          float d;
-          gelu_d(z1[mt][nt][r], d);
-          w.dz[qq][n1] = bf16_bits(dh1[mt][nt][r] * d);
-        }
-      }
-    __syncthreads();
-    // dx_k = sum_n dZ1[q][n] W1[n][k] for this lane's query
-    float g[kIn];
-#pragma unroll
-    for (int k = 0; k < kIn; ++k) g[k] = 0.f;
-#pragma unroll
-    for (int n8 = 0; n8 < kH; n8 += 8) {
-      bf16x8 row = lds_bf16x8(&w.dz[lane][n8]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float dzv = (float)row[e];
-#pragma unroll
-        for (int k = 0; k < kIn; ++k) g[k] += dzv * P.w1f[k][n8 + e];
-      }
-    }
-    if (valid) {
-      float* o = out_g + q * 8;
-      o[0] = f;
-#pragma unroll
-      for (int k = 0; k < kIn; ++k) o[1 + k] = g[k];
-    }
-    __syncthreads();
+    const int64_t q = q0 + lr;
+    if (q < n) reinterpret_cast<float4*>(out_g + q * 8)[half] = make_float4(half ? gx[0] : f, gx[1], gx[2], gx[3]);
   }
 }
 
@@ -711,7 +890,7 @@ hipError_t launch_mlp_input_grad_gather(const void* packed, const float* pixfeat
                                         const float* q_z, const unsigned long long* q_count, int64_t q_cap,
                                         float* out_g, hipStream_t s) {
   if (q_cap <= 0 || n_pix <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_mlp_input_grad_gather, dim3(mlp_grid(q_cap, 2)), dim3(128), 0, s, (const MlpPacked*)packed,
+  hipLaunchKernelGGL(k_mlp_input_grad_gather, dim3(mlp_grid(q_cap, 4)), dim3(256), 0, s, (const MlpPacked*)packed,
                      pixfeat, q_pix, q_z, q_count, q_cap, n_pix, out_g);
   return hipGetLastError();
 }

@@ -34,3 +34,16 @@ def test_loss_grad_over_batch_sizes(n):
     log(f"[mlp] n={n} loss gpu={loss:.6e} ref={lref:.6e} worst grad rel={worst:.2e}")
     assert loss == pytest.approx(lref, rel=1e-3 if n < 100 else 1e-4)
     assert worst < tol
+
+
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 255, 257, 4097])
+def test_forward_does_not_depend_on_the_place(n):
+    """A query's output is the same bits in whichever tile, half and step of a
+    wave it falls: the first n of a long list, alone, and in reverse order."""
+    from paper_2512_11800_amd import surrogate as G
+    theta = torch.tensor(S.init_params(6).astype(np.float32), device="cuda")
+    x = torch.tensor(_batch(200_000, 11)[0], device="cuda")
+    packed = G.mlp_pack(theta)
+    full = G.mlp_forward(packed, x)
+    assert torch.equal(G.mlp_forward(packed, x[:n].contiguous()), full[:n])
+    assert torch.equal(G.mlp_forward(packed, x[:n].flip(0).contiguous()), full[:n].flip(0))
