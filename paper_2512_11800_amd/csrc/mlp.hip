@@ -3,18 +3,17 @@
 // depth m_0 F) with bf16 weights and activations and fp32 accumulation.
 //
 // Every layer is a dense contraction and runs on the matrix cores
-// (v_mfma_f32_32x32x16_bf16), 64 queries per wave:
-//   layer 1  Z1[64x64] = X[64x16] W1p^T,   X = (x_hi, x_lo) split of the 7 fp32
+// (v_mfma_f32_32x32x16_bf16), a tile of 32 queries per wave, as the transposed
+// products (weights times activations):
+//   layer 1  Z1^T[64x32] = W1p X^T,   X = (x_hi, x_lo) split of the 7 fp32
 //            inputs into bf16 pairs (W1p repeats W1 for both halves), so the
 //            inputs keep ~16 mantissa bits;
-//   layer 2  Z2[64x64] = H1[64x64] W2^T,   H1 = bf16(GELU(Z1 + b1));
-//   layer 3  out = GELU(Z2 + b2) . w3 + b3, reduced through LDS;
-// and the training step adds dW2 = dZ2^T H1, dH1 = dZ2 W2, dW1 = dZ1^T X on
-// the same instruction. The inference kernels form the transposed products
-// (weights times activations, see RegMlp) with the activations in registers from
-// layer to layer. MFMA operand layout (wave64, 32x32x16): lane l holds
-// A[l % 32][8 (l / 32) + e] and B[8 (l / 32) + e][l % 32], e = 0..7, and
-// accumulator element r of lane l is C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
+//   layer 2  Z2^T[64x32] = W2 H1^T,   H1 = bf16(GELU(Z1 + b1));
+//   layer 3  out = GELU(Z2 + b2) . w3 + b3, summed in neuron order;
+// and the training step adds dH1^T = W2^T dZ2^T, dW2 = dZ2^T H1 and dW1 = dZ1^T X.
+// MFMA operand layout (wave64, 32x32x16): lane l holds A[l % 32][8 (l / 32) + e]
+// and B[8 (l / 32) + e][l % 32], e = 0..7, and accumulator element r of lane l is
+// C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
 #include "kernels.h"
 
 namespace mb {
@@ -33,7 +32,7 @@ constexpr int O_B2 = O_W2 + kH * kH;  // [64]
 constexpr int O_W3 = O_B2 + kH;       // [64]
 constexpr int O_B3 = O_W3 + kH;       // [1]
 constexpr int kParams = O_B3 + 1;     // 4737
-// per-wave gradient partial layout (dW1 kept unfolded over the hi/lo halves)
+// layout of a row of partial gradients (dW1 kept unfolded over the hi/lo halves)
 constexpr int Q_W1 = 0;               // [64][16]
 constexpr int Q_B1 = Q_W1 + kH * 16;
 constexpr int Q_W2 = Q_B1 + kH;
@@ -96,150 +95,38 @@ __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
 __device__ __forceinline__ int c_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 
 // ---------------------------------------------------------------------------
+// Bound by its launch: 16 blocks, one element a thread and array.
 __global__ __launch_bounds__(256) void k_mlp_pack(const float* th, MlpPacked* p) {
-  for (int i = threadIdx.x; i < kH * kXStride; i += blockDim.x) {
+  const int t0 = blockIdx.x * blockDim.x + threadIdx.x, dt = gridDim.x * blockDim.x;
+  for (int i = t0; i < kH * kXStride; i += dt) {
     int n = i / kXStride, k = i % kXStride;
     float v = k < kIn ? th[O_W1 + n * kIn + k] : (k < 2 * kIn ? th[O_W1 + n * kIn + k - kIn] : 0.f);
     p->w1[n][k] = bf16_bits(v);
   }
-  for (int i = threadIdx.x; i < kH * kH; i += blockDim.x) {
+  for (int i = t0; i < kH * kH; i += dt) {
     int n = i / kH, k = i % kH;
     uint16_t b = bf16_bits(th[O_W2 + i]);
     p->w2[n][k] = b;
     p->w2t[k][n] = b;
   }
-  for (int i = threadIdx.x; i < kH; i += blockDim.x) {
+  for (int i = t0; i < kH; i += dt) {
     p->w3[i] = bf16_float(bf16_bits(th[O_W3 + i]));
     p->b1[i] = th[O_B1 + i];
     p->b2[i] = th[O_B2 + i];
   }
-  if (threadIdx.x == 0) p->b3 = th[O_B3];
-  for (int i = threadIdx.x; i < 63; i += blockDim.x) p->pad[i] = 0.f;
-  for (int i = threadIdx.x; i < kH * kIn; i += blockDim.x) {
+  if (t0 == 0) p->b3 = th[O_B3];
+  for (int i = t0; i < 63; i += dt) p->pad[i] = 0.f;
+  for (int i = t0; i < kH * kIn; i += dt) {
     int n = i / kIn, k = i % kIn;
     p->w1f[k][n] = bf16_float(bf16_bits(th[O_W1 + i]));
   }
 }
 
-// LDS working set of one training wave. The layer-3 row sums reuse the dZ2
-// storage once the matrix-core reads of it are complete (barrier between).
-struct TrainLds {
-  uint16_t x[64][kXStride];
-  uint16_t xt[32][64 + 8];   // X^T [k][q], rows 16..31 zero
-  uint16_t h1[64][kH + 8];
-  uint16_t h1t[kH][64 + 8];  // H1^T [k][q]
-  union {
-    uint16_t dz[64][kH + 8];  // dZ2 [q][n]
-    float s[64][33];
-  };
-  uint16_t dzt[kH][64 + 8];  // dZ2^T [n][q], later dZ1^T
-  float dout[64];
-};
-
-// stage the wave's 64 input vectors (v: this lane's kIn inputs) as bf16 pairs
-template <class L>
-__device__ __forceinline__ void stage_inputs(L& w, const float* v, int lane) {
-  uint16_t hi[kIn], lo[kIn];
-#pragma unroll
-  for (int k = 0; k < kIn; ++k) {
-    hi[k] = bf16_bits(v[k]);
-    lo[k] = bf16_bits(v[k] - bf16_float(hi[k]));
-  }
-#pragma unroll
-  for (int k = 0; k < kXStride; ++k) {
-    uint16_t b = k < kIn ? hi[k] : (k < 2 * kIn ? lo[k - kIn] : (uint16_t)0);
-    w.x[lane][k] = b;
-    if constexpr (sizeof(L) == sizeof(TrainLds)) w.xt[k][lane] = b;
-  }
-  if constexpr (sizeof(L) == sizeof(TrainLds))
-#pragma unroll
-    for (int k = kXStride; k < 32; ++k) w.xt[k][lane] = 0;
-}
-
-template <class L>
-__device__ __forceinline__ void load_inputs(L& w, const float* x, int64_t q, bool valid, int lane, float& m0) {
-  float v[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) v[k] = valid ? x[q * 8 + k] : 0.f;
-  m0 = v[7];
-  stage_inputs(w, v, lane);
-}
-
-// layers 1-3 for the wave's 64 queries; returns the output pre-activation of
-// query `lane` and leaves the Z1/Z2 tiles (and H1, H1^T) for the backward pass
-template <class L>
-__device__ __forceinline__ float mlp_forward_wave(L& w, const MlpPacked& P, int lane, f32x16 z1[2][2],
-                                                  f32x16 z2[2][2]) {
-  constexpr bool kTrain = sizeof(L) == sizeof(TrainLds);
-  const int lr = lane & 31, hk = 8 * (lane >> 5);
-  // layer 1
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      f32x16 acc = {};
-      acc = mfma(lds_bf16x8(&w.x[32 * mt + lr][hk]), lds_bf16x8(&P.w1[32 * nt + lr][hk]), acc);
-      z1[mt][nt] = acc;
-    }
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      int n = 32 * nt + lr;
-      float b = P.b1[n];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        int q = 32 * mt + c_row(r, lane);
-        float zz = z1[mt][nt][r] + b;
-        z1[mt][nt][r] = zz;
-        uint16_t hb = bf16_bits(gelu(zz));
-        w.h1[q][n] = hb;
-        if constexpr (kTrain) w.h1t[n][q] = hb;
-      }
-    }
-  __syncthreads();
-  // layer 2
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      f32x16 acc = {};
-#pragma unroll
-      for (int kt = 0; kt < 4; ++kt)
-        acc = mfma(lds_bf16x8(&w.h1[32 * mt + lr][16 * kt + hk]), lds_bf16x8(&P.w2[32 * nt + lr][16 * kt + hk]), acc);
-      z2[mt][nt] = acc;
-    }
-  __syncthreads();
-  // layer 3: per-lane partial sums over its two columns, reduced through LDS
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float s = 0.f;
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        int n = 32 * nt + lr;
-        float zz = z2[mt][nt][r] + P.b2[n];
-        z2[mt][nt][r] = zz;
-        s += gelu(zz) * P.w3[n];
-      }
-      w.s[32 * mt + c_row(r, lane)][lr] = s;
-    }
-  }
-  __syncthreads();
-  float out = P.b3;
-#pragma unroll
-  for (int c = 0; c < 32; ++c) out += w.s[lane][c];
-  __syncthreads();
-  return out;
-}
-
 __device__ __forceinline__ float sigmoid(float x) { return fast_rcp(1.f + __expf(-x)); }
 
 // ---------------------------------------------------------------------------
-// Inference with the activations in registers. A wave takes 64 queries as two
-// tiles of 32 and forms the transposed products Z^T = W H^T: lane l then holds
-// the column of query l % 32, accumulator element r its neuron 8 (r / 4) +
+// The activations stay in registers from layer to layer (inference takes two tiles
+// of 32 queries a wave and step): lane l holds the column of query l % 32, accumulator element r its neuron 8 (r / 4) +
 // 4 (l / 32) + r % 4. Rounded to bf16 pairs, eight consecutive elements of a
 // lane are half a k-block of the next layer's B operand; exchanging the middle
 // quarters between the wave's halves (permlane32_swap) puts them in the operand's
@@ -334,13 +221,15 @@ __device__ __forceinline__ void column_operand(const f32x16* z, bf16x8* op) {
 
 // Layers 1 and 2 of a tile's 32 queries and the terms of layer 3: s[r] = the
 // output terms of neurons n and n + 32 for n = 8 (r / 4) + 4 (l / 32) + r % 4.
-// GRAD: d1, d2 receive GELU' at the two layers.
+// KEEP 1: d1, d2 receive GELU' at the two layers; 2: also h1 the bf16 operand of
+// layer 2 and h2 the activations of layer 2.
 struct RowConsts {
   float b1[kH], b2[kH], w3[kH];
 };
-template <bool GRAD>
+template <int KEEP>
 __device__ __forceinline__ void mlp_tile(const RegWeights& w, const RowConsts& c, bf16x8 x, int lane, float* s,
-                                         f32x16* d1, f32x16* d2) {
+                                         f32x16* d1 = nullptr, f32x16* d2 = nullptr, bf16x8* h1 = nullptr,
+                                         f32x16* h2 = nullptr) {
   const int h4 = 4 * (lane >> 5);
   f32x16 z[2];
 #pragma unroll
@@ -354,12 +243,15 @@ __device__ __forceinline__ void mlp_tile(const RegWeights& w, const RowConsts& c
       for (int j = 0; j < 4; ++j) {
         float d;
         z[t][4 * g + j] = gelu_d(z[t][4 * g + j] + bb[j], d);
-        if constexpr (GRAD) d1[t][4 * g + j] = d;
+        if constexpr (KEEP > 0) d1[t][4 * g + j] = d;
       }
     }
   }
   bf16x8 op[4];
   column_operand(z, op);
+  if constexpr (KEEP > 1)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) h1[k] = op[k];
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
     z[t] = f32x16{};
@@ -377,7 +269,8 @@ __device__ __forceinline__ void mlp_tile(const RegWeights& w, const RowConsts& c
       for (int j = 0; j < 4; ++j) {
         float d;
         const float a = gelu_d(z[t][4 * g + j] + bb[j], d);
-        if constexpr (GRAD) d2[t][4 * g + j] = d;
+        if constexpr (KEEP > 0) d2[t][4 * g + j] = d;
+        if constexpr (KEEP > 1) h2[t][4 * g + j] = a;
         s[4 * g + j] = t == 0 ? a * qq[j] : fmaf(a, qq[j], s[4 * g + j]);
       }
     }
@@ -438,7 +331,7 @@ __device__ __forceinline__ void mlp_queries(const MlpPacked* P, int64_t n, const
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       asm volatile("" ::: "memory");  // the constants are read anew, not kept in 96 registers
-      mlp_tile<false>(w, c, x[t], lane, s[t], nullptr, nullptr);
+      mlp_tile<0>(w, c, x[t], lane, s[t]);
     }
     // tile 0's queries to the lower half-wave, tile 1's to the upper
 #pragma unroll
@@ -588,7 +481,7 @@ __global__ __launch_bounds__(256, 2) void k_mlp_input_grad_gather(const MlpPacke
     float s[16], t[16];
     f32x16 d1[2], d2[2];
     asm volatile("" ::: "memory");  // the constants are read anew, not kept in registers
-    mlp_tile<true>(w, c, x, lane, s, d1, d2);
+    mlp_tile<1>(w, c, x, lane, s, d1, d2);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {  // both halves end with all of the query's terms
       t[r] = s[r];
@@ -645,165 +538,232 @@ __global__ __launch_bounds__(256, 2) void k_mlp_input_grad_gather(const MlpPacke
   }
 }
 
-// Forward + backward of the loss mean_q (exp(-m0_q F_q) - T_q)^2 over the
-// batch; one gradient partial per wave (deterministic reduction afterwards).
-constexpr int kTrainWaves = 2;
+// Forward + backward of the loss mean_q (exp(-m0 F) - t)^2 over the n queries of x
+// [n][8] (7 inputs, m0): each block writes one row of partial gradients.
+//
+// The forward tile with GELU', H1 and GELU(Z2) kept, dZ2 = dout w3 GELU'(Z2) and
+// dZ1 = dH1 GELU'(Z1) in the same layout (a lane per query), the bias and w3
+// gradients summed per lane in fp32. The weight gradients contract over the
+// queries: H1, dZ2, dZ1 and X pass through LDS once, transposed, and accumulate
+// in registers (80 a lane) over all of a wave's tiles. One wave a SIMD, 512
+// registers. Bound by latency at a batch of 65536 (two tiles of 5300 issue cycles a
+// wave, its weights before and its sums after them): 94 -> 28 us, where each wave
+// took 64 queries through LDS between all products, evaluated each GELU twice and
+// spilled 182 registers.
+constexpr int kTrainWaves = 4;
+constexpr int kQStride = 32 + 8;  // bf16 elements of a row of 32 queries, rows apart in the banks
 
-__global__ __launch_bounds__(128) void k_mlp_train(const MlpPacked* gp, const float* x, const float* t_target,
-                                                   int64_t n, float* partials) {
-  __shared__ MlpPacked P;
-  __shared__ TrainLds ws[kTrainWaves];
-  {
-    const float4* src = reinterpret_cast<const float4*>(gp);
-    float4* dst = reinterpret_cast<float4*>(&P);
-    for (int i = threadIdx.x; i < (int)(sizeof(MlpPacked) / 16); i += blockDim.x) dst[i] = src[i];
-  }
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int lr = lane & 31, hk = 8 * (lane >> 5);
-  TrainLds& w = ws[wave];
-  f32x16 gw2[2][2], gw1[2];
+struct TrainTile {
+  uint16_t h1[kH][kQStride], dz2[kH][kQStride], dz1[kH][kQStride], x[kXStride][kQStride];
+};
+struct TrainSums {
+  float part[kPartial];
+  float upper[3][kH];  // b1, b2, w3: the sums of lanes 16..31 (lanes 0..15 in part)
+};
+
+// a tile's LDS contents pass between the lanes of the one wave that owns it
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// rows k0..k0+7 of column q from an operand's eight elements
+__device__ __forceinline__ void scatter_operand(uint16_t (*rows)[kQStride], int k0, int q, bf16x8 v) {
+  const uint4 u = __builtin_bit_cast(uint4, v);
+  const uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
-  for (int a = 0; a < 2; ++a) {
-    gw1[a] = f32x16{};
-#pragma unroll
-    for (int b = 0; b < 2; ++b) gw2[a][b] = f32x16{};
-  }
-  float gb1[2] = {0.f, 0.f}, gb2[2] = {0.f, 0.f}, gw3[2] = {0.f, 0.f}, gb3 = 0.f, loss = 0.f;
-  const float inv_n = 1.f / (float)n;
-  const int64_t chunks = (n + 63) / 64;
-  const int64_t per_block =
-      ((chunks + gridDim.x - 1) / gridDim.x + kTrainWaves - 1) / kTrainWaves * kTrainWaves;
-  for (int64_t it = 0; it < per_block; it += kTrainWaves) {
-    int64_t chunk = (int64_t)blockIdx.x * per_block + it + wave;
-    int64_t q = chunk * 64 + lane;
-    bool valid = q < n;
-    float m0;
-    load_inputs(w, x, q, valid, lane, m0);
-    __syncthreads();
-    f32x16 z1[2][2], z2[2][2];
-    float out = mlp_forward_wave(w, P, lane, z1, z2);
-    // loss and d loss / d out for query `lane`
-    float f = sigmoid(out);
-    float tp = __expf(-m0 * f);
-    float diff = valid ? tp - t_target[q] : 0.f;
-    loss += diff * diff;
-    float dout = valid ? 2.f * diff * inv_n * (-m0 * tp) * f * (1.f - f) : 0.f;
-    w.dout[lane] = dout;
-    gb3 += dout;
-    __syncthreads();
-    // dZ2 = dout w3 GELU'(Z2); accumulate dw3, db2; stage dZ2 (bf16) both ways
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        int n2 = 32 * nt + lr;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          int qq = 32 * mt + c_row(r, lane);
-          float d;
-          float a2 = gelu_d(z2[mt][nt][r], d);
-          float dq = w.dout[qq];
-          gw3[nt] += a2 * dq;
-          float dz2 = dq * P.w3[n2] * d;
-          gb2[nt] += dz2;
-          uint16_t b = bf16_bits(dz2);
-          w.dz[qq][n2] = b;
-          w.dzt[n2][qq] = b;
-        }
-      }
-    __syncthreads();
-    // dW2 += dZ2^T H1 ; dH1 = dZ2 W2
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
-          gw2[mt][nt] = mfma(lds_bf16x8(&w.dzt[32 * mt + lr][16 * kt + hk]),
-                             lds_bf16x8(&w.h1t[32 * nt + lr][16 * kt + hk]), gw2[mt][nt]);
-    f32x16 dh1[2][2];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        f32x16 acc = {};
-#pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
-          acc = mfma(lds_bf16x8(&w.dz[32 * mt + lr][16 * kt + hk]), lds_bf16x8(&P.w2t[32 * nt + lr][16 * kt + hk]),
-                     acc);
-        dh1[mt][nt] = acc;
-      }
-    __syncthreads();
-    // dZ1 = dH1 GELU'(Z1); db1; stage dZ1^T (bf16)
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        int n1 = 32 * nt + lr;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          int qq = 32 * mt + c_row(r, lane);
-          float d;
-          gelu_d(z1[mt][nt][r], d);
-          float dz1 = dh1[mt][nt][r] * d;
-          gb1[nt] += dz1;
-          w.dzt[n1][qq] = bf16_bits(dz1);
-        }
-      }
-    __syncthreads();
-    // dW1 (unfolded over the 16 input slots) += dZ1^T X
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-      for (int kt = 0; kt < 4; ++kt)
-        gw1[mt] = mfma(lds_bf16x8(&w.dzt[32 * mt + lr][16 * kt + hk]), lds_bf16x8(&w.xt[lr][16 * kt + hk]), gw1[mt]);
-    __syncthreads();
-  }
-  // write this wave's partial gradient
-  float* out = partials + ((size_t)blockIdx.x * kTrainWaves + wave) * kPartial;
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      int row = 32 * mt + c_row(r, lane);
-      if (lr < kXStride) out[Q_W1 + row * kXStride + lr] = gw1[mt][r];
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) out[Q_W2 + row * kH + 32 * nt + lr] = gw2[mt][nt][r];
-    }
-  // per-lane vectors: lanes l and l^32 hold the two row halves of a column
-#pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-    float a = gb1[nt] + __shfl_xor(gb1[nt], 32, 64);
-    float b = gb2[nt] + __shfl_xor(gb2[nt], 32, 64);
-    float c = gw3[nt] + __shfl_xor(gw3[nt], 32, 64);
-    if (lane < 32) {
-      out[Q_B1 + 32 * nt + lr] = a;
-      out[Q_B2 + 32 * nt + lr] = b;
-      out[Q_W3 + 32 * nt + lr] = c;
-    }
-  }
-  float sb3 = gb3, sl = loss;
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    sb3 += __shfl_xor(sb3, m, 64);
-    sl += __shfl_xor(sl, m, 64);
-  }
-  if (lane == 0) {
-    out[Q_B3] = sb3;
-    out[Q_LOSS] = sl;
+  for (int j = 0; j < 4; ++j) {
+    rows[k0 + 2 * j][q] = (uint16_t)w[j];
+    rows[k0 + 2 * j + 1][q] = (uint16_t)(w[j] >> 16);
   }
 }
 
-// Sum the per-wave partials in a fixed order and fold dW1's hi/lo halves. One
+// the sum over the lane's row of 16
+__device__ __forceinline__ float row_sum16(float v) {
+  v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x128, 0xF, 0xF, true));  // row_ror:8
+  v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x124, 0xF, 0xF, true));  // row_ror:4
+  v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x122, 0xF, 0xF, true));  // row_ror:2
+  v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x121, 0xF, 0xF, true));  // row_ror:1
+  return v;
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+__global__ __launch_bounds__(64 * kTrainWaves, 1) void k_mlp_train(const MlpPacked* P, const float* x,
+                                                                   const float* t_target, int64_t n,
+                                                                   float* partials) {
+  __shared__ __align__(16) RowConsts c;
+  __shared__ __align__(16) uint16_t w2t[kH][kH + 8];
+  __shared__ __align__(16) union {
+    TrainTile tile[kTrainWaves];
+    TrainSums sums[kTrainWaves];
+  } lds;
+  for (int i = threadIdx.x; i < kH * kH / 8; i += blockDim.x)
+    *reinterpret_cast<bf16x8*>(&w2t[i / 8][8 * (i % 8)]) = global_bf16x8(&P->w2t[i / 8][8 * (i % 8)]);
+  stage_consts(c, P);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lr = lane & 31, half = lane >> 5;
+  const RegWeights w = load_weights(P, lane);
+  const float b3 = P->b3;
+  TrainTile& tl = lds.tile[wave];
+  f32x16 gw2[2][2] = {};
+  f32x4 gw1[4] = {};  // 16x16x32 products: dW1 rows 16 a .. 16 a + 15, columns l % 16
+  f32x16 gb1[2] = {}, gb2[2] = {}, gw3[2] = {};
+  float gb3 = 0.f, loss = 0.f;
+  const float inv_n = 1.f / (float)n;
+  const int64_t step = (int64_t)gridDim.x * kTrainWaves * 32;
+  RowSource in(x, n);
+  float v[kIn];
+  int64_t q0 = ((int64_t)blockIdx.x * kTrainWaves + wave) * 32;
+  in.start(q0 + lr, step);
+  if (q0 < n) in.load(v);
+  for (; q0 < n; q0 += step) {
+    const int64_t q = q0 + lr;
+    const bool valid = q < n;
+    const float m0 = valid ? x[q * 8 + 7] : 0.f, target = valid ? t_target[q] : 0.f;
+    const bf16x8 xo = input_operand(v, lane);
+    if (q0 + step < n) {
+      in.advance();
+      in.load(v);
+    }
+    float s[16], t[16];
+    f32x16 d1[2], d2[2], h2[2];
+    bf16x8 op[4];
+    asm volatile("" ::: "memory");  // the constants are read anew, not kept in registers
+    mlp_tile<2>(w, c, xo, lane, s, d1, d2, op, h2);
+    wave_lds_fence();  // the products of the tile before have read theirs
+    scatter_operand(tl.x, 8 * half, lr, xo);
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) scatter_operand(tl.h1, 16 * kt + 8 * half, lr, op[kt]);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {  // both halves end with all of the query's terms
+      t[r] = s[r];
+      swap_halves(s[r], t[r]);
+    }
+    // loss and d loss / d out of the query
+    const float f = sigmoid(sum_terms(b3, s, t));
+    const float tp = __expf(-m0 * f);
+    const float diff = valid ? tp - target : 0.f;
+    const float dout = valid ? 2.f * diff * inv_n * (-m0 * tp) * f * (1.f - f) : 0.f;
+    if (half == 0) {
+      loss += diff * diff;
+      gb3 += dout;
+    }
+    // dZ2; dw3, db2; dH1^T = W2^T dZ2^T
+    f32x16 dz[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 q4 = *reinterpret_cast<const float4*>(&c.w3[32 * m + 8 * g + 4 * half]);
+        const float qq[4] = {q4.x, q4.y, q4.z, q4.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int r = 4 * g + j;
+          gw3[m][r] = fmaf(h2[m][r], dout, gw3[m][r]);
+          dz[m][r] = dout * qq[j] * d2[m][r];
+          gb2[m][r] += dz[m][r];
+        }
+      }
+    column_operand(dz, op);
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) scatter_operand(tl.dz2, 16 * kt + 8 * half, lr, op[kt]);
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      dz[m] = f32x16{};
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt) dz[m] = mfma(lds_bf16x8(&w2t[32 * m + lr][16 * kt + 8 * half]), op[kt], dz[m]);
+    }
+    // dZ1; db1
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        dz[m][r] *= d1[m][r];
+        gb1[m][r] += dz[m][r];
+      }
+    column_operand(dz, op);
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) scatter_operand(tl.dz1, 16 * kt + 8 * half, lr, op[kt]);
+    wave_lds_fence();
+    // dW2 += dZ2^T H1, dW1 (unfolded over the 16 input slots) += dZ1^T X
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+      bf16x8 a[2], b[2];
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        a[m] = lds_bf16x8(&tl.dz2[32 * m + lr][16 * kt + 8 * half]);
+        b[m] = lds_bf16x8(&tl.h1[32 * m + lr][16 * kt + 8 * half]);
+      }
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) gw2[m][k] = mfma(a[m], b[k], gw2[m][k]);
+    }
+    const bf16x8 xb = lds_bf16x8(&tl.x[lane & 15][8 * (lane >> 4)]);
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+      gw1[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          lds_bf16x8(&tl.dz1[16 * m + (lane & 15)][8 * (lane >> 4)]), xb, gw1[m], 0, 0, 0);
+  }
+  __syncthreads();  // the tiles' storage becomes the waves' sums
+  TrainSums& out = lds.sums[wave];
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out.part[Q_W1 + (16 * m + 4 * (lane >> 4) + r) * kXStride + (lane & 15)] = gw1[m][r];
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int row = 32 * m + c_row(r, lane);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) out.part[Q_W2 + row * kH + 32 * k + lr] = gw2[m][k][r];
+      const float s1 = row_sum16(gb1[m][r]), s2 = row_sum16(gb2[m][r]), s3 = row_sum16(gw3[m][r]);
+      if (lr == 0) {
+        out.part[Q_B1 + row] = s1;
+        out.part[Q_B2 + row] = s2;
+        out.part[Q_W3 + row] = s3;
+      } else if (lr == 16) {
+        out.upper[0][row] = s1;
+        out.upper[1][row] = s2;
+        out.upper[2][row] = s3;
+      }
+    }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    gb3 += __shfl_xor(gb3, m, 64);
+    loss += __shfl_xor(loss, m, 64);
+  }
+  if (lane == 0) {
+    out.part[Q_B3] = gb3;
+    out.part[Q_LOSS] = loss;
+#pragma unroll
+    for (int i = Q_LOSS + 1; i < kPartial; ++i) out.part[i] = 0.f;
+  }
+  __syncthreads();
+  float* row = partials + (size_t)blockIdx.x * kPartial;
+  for (int i = threadIdx.x; i < kPartial; i += blockDim.x) {
+    const int u = i >= Q_B1 && i < Q_W2 ? i - Q_B1 : (i >= Q_B2 && i < Q_B3 ? kH + i - Q_B2 : -1);
+    float sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < kTrainWaves; ++k) {
+      sum += lds.sums[k].part[i];
+      if (u >= 0) sum += (&lds.sums[k].upper[0][0])[u];
+    }
+    row[i] = sum;
+  }
+}
+
+// Sum the blocks' partials in a fixed order and fold dW1's hi/lo halves. One
 // block per 64 partial columns (a multiple of dW1's row of 16, so its halves
 // meet in one block), its 16 waves taking every 16th partial row with eight
-// rows' loads in flight, added up in wave order. Bound by the partials' traffic:
-// 21.8 MB for a batch of 65536 in 9.6 us, where one thread per parameter walking
-// all rows one load at a time took 448 us.
+// rows' loads in flight, added up in wave order. Bound by latency: the 256
+// rows (5.4 MB) of a batch of 65536 in 4.4 us; 1024 rows took 9.6 us so, and 448 us
+// with one thread per parameter walking them one load at a time.
 constexpr int kReduceWaves = 16;
 
-__global__ __launch_bounds__(64 * kReduceWaves) void k_mlp_reduce(const float* partials, int n_waves, int64_t n,
+__global__ __launch_bounds__(64 * kReduceWaves) void k_mlp_reduce(const float* partials, int n_rows, int64_t n,
                                                                   float* grad, float* loss) {
   __shared__ float red[kReduceWaves][64];
   const int col = threadIdx.x & 63, grp = threadIdx.x >> 6;
@@ -812,14 +772,14 @@ __global__ __launch_bounds__(64 * kReduceWaves) void k_mlp_reduce(const float* p
   if (qi < kPartial) {
     const float* src = partials + qi;
     int w = grp;
-    for (; w + 7 * kReduceWaves < n_waves; w += 8 * kReduceWaves) {
+    for (; w + 7 * kReduceWaves < n_rows; w += 8 * kReduceWaves) {
       float v[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) v[k] = src[(size_t)(w + k * kReduceWaves) * kPartial];
 #pragma unroll
       for (int k = 0; k < 8; ++k) s += v[k];
     }
-    for (; w < n_waves; w += kReduceWaves) s += src[(size_t)w * kPartial];
+    for (; w < n_rows; w += kReduceWaves) s += src[(size_t)w * kPartial];
   }
   red[grp][col] = s;
   __syncthreads();
@@ -862,10 +822,16 @@ static int mlp_grid(int64_t n, int waves) {
   return (int)(blocks < 1024 ? (blocks < 1 ? 1 : blocks) : 1024);
 }
 
-size_t mlp_workspace_bytes(int64_t n) { return (size_t)mlp_grid(n, kTrainWaves) * kTrainWaves * kPartial * sizeof(float); }
+// one block a compute unit at most: its weight gradients fill the registers
+static int train_grid(int64_t n) {
+  const int64_t blocks = (n + 32 * kTrainWaves - 1) / (32 * kTrainWaves);
+  return (int)(blocks < 256 ? (blocks < 1 ? 1 : blocks) : 256);
+}
+
+size_t mlp_workspace_bytes(int64_t n) { return (size_t)train_grid(n) * kPartial * sizeof(float); }
 
 hipError_t launch_mlp_pack(const float* theta, void* packed, hipStream_t s) {
-  hipLaunchKernelGGL(k_mlp_pack, dim3(1), dim3(256), 0, s, theta, (MlpPacked*)packed);
+  hipLaunchKernelGGL(k_mlp_pack, dim3(kH * kH / 256), dim3(256), 0, s, theta, (MlpPacked*)packed);
   return hipGetLastError();
 }
 
@@ -903,10 +869,10 @@ hipError_t launch_mlp_forward(const void* packed, const float* x, int64_t n, flo
 
 hipError_t launch_mlp_loss_grad(const void* packed, const float* x, const float* t, int64_t n, float* grad,
                                 float* loss, float* ws, hipStream_t s) {
-  int grid = mlp_grid(n, kTrainWaves);
-  hipLaunchKernelGGL(k_mlp_train, dim3(grid), dim3(128), 0, s, (const MlpPacked*)packed, x, t, n, ws);
+  const int grid = train_grid(n);
+  hipLaunchKernelGGL(k_mlp_train, dim3(grid), dim3(64 * kTrainWaves), 0, s, (const MlpPacked*)packed, x, t, n, ws);
   hipLaunchKernelGGL(k_mlp_reduce, dim3((kPartial + 63) / 64), dim3(64 * kReduceWaves), 0, s, ws,
-                     grid * kTrainWaves, n, grad, loss);
+                     grid, n, grad, loss);
   return hipGetLastError();
 }
 
