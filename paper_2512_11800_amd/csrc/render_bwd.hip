@@ -16,7 +16,11 @@
 // kernel then sums the slots: one reduction, no atomics, deterministic. A
 // byte per slot records whether it was written (the stored coverage mask of
 // that entry and quadrant is non-empty); the reduction skips the others.
-// The passes walk the coverage masks the forward pass stored.
+// The passes walk the coverage masks the forward pass stored (walk_entries).
+// The kernel is bound by VALU issue: per 64 pairs about 3500 issue cycles of pass 2
+// and 1400 of pass 3 beside the queueing. With the queue's state in scalar
+// registers: 2.21 -> 2.06 ms (K = 4), 3.74 -> 3.41 ms (K = 6) at 500k Gaussians,
+// 1920x1080; the gradients are the same bits.
 #include "render_common.h"
 #include "trig.h"
 
@@ -281,27 +285,151 @@ __device__ __forceinline__ void chain_record(float gmu, float gsig, float gom, c
   gr[G_W] = gom * ek;
 }
 
+// The backward pass's queue of pairs, entry by entry (pairs of one entry lie next
+// to each other, so that a segmented scan over the lanes sums an entry's
+// gradients): positions [0, 64) are the window evaluated next. Everything but
+// the lanes' own positions is wave-uniform and kept in scalar registers: an entry
+// is queued under its mask as the execution mask, and the window's segments come
+// from `heads` by scalar logic. Masks fetched with a shuffle, a count in vector
+// registers and a lane's positions by 64-bit selects cost a push about 150 issue
+// cycles, against 50 (2.9 pushes per 64 pairs and pass on the 500k-Gaussian 1080p
+// scene).
+struct Window {
+  int n;           // pairs in the window
+  int base;        // its first item in the ring of 128
+  uint64_t heads;  // positions that begin an entry's pairs
+  uint64_t own;    // this lane's positions: the pairs of its pixel
+  bool carried;    // the first segment continues the entry of the window before
+  bool continues;  // the last segment's entry continues in the next window
+};
+
+// Rank tracking beside a queue: q[item] receives the pair's index among its
+// pixel's covering pairs, counted by the pixel lane's ctr.
+struct QueueRanks {
+  uint32_t* q;  // [128] in LDS, parallel to WaveQueue::item
+  uint32_t ctr;
+};
+
+// Queue the pairs of the staged batch [b, b + nb) from the stored coverage masks of
+// this wave (restricted to the lanes of `keep`), skipping empty entries 64 at a
+// time, and call flush(window) for every 64 pairs and for the rest. on_empty(j) is
+// called by the lane that loaded entry j's mask when the stored mask has pixels but
+// none of them is kept. In a split block (see BlockWork) a wave takes only the
+// entries j with j % 4 == its wave index (`own4` >= 0); otherwise every entry.
+// OWN: the lanes' own positions are wanted.
+template <bool OWN, class Flush, class Empty>
+__device__ __forceinline__ void walk_entries(WaveQueue& q, const uint64_t* masks, int b, int nb, int quad, int own4,
+                                             int lane, uint64_t keep, Flush&& flush, Empty&& on_empty,
+                                             QueueRanks* rank = nullptr) {
+  Window w = {0, 0, 0ull, 0ull, false, false};
+  for (int j0 = 0; j0 < nb; j0 += 64) {
+    const bool in = j0 + lane < nb && (own4 < 0 || ((j0 + lane) & 3) == own4);
+    const uint64_t raw = in ? masks[(size_t)(b + j0 + lane) * 4 + quad] : 0ull;
+    const uint64_t mk = raw & keep;
+    if (in && mk == 0 && raw != 0) on_empty(j0 + lane);
+    uint64_t nz = __ballot(mk != 0);
+    while (nz) {
+      const int l = __builtin_ctzll(nz);
+      nz &= nz - 1;
+      const uint32_t mlo = __builtin_amdgcn_readlane((uint32_t)mk, l);
+      const uint32_t mhi = __builtin_amdgcn_readlane((uint32_t)(mk >> 32), l);
+      const uint64_t m = ((uint64_t)mhi << 32) | mlo;
+      const int n = w.n + __builtin_popcountll(m);
+      const bool cov = __builtin_amdgcn_inverse_ballot_w64(m);
+      const uint16_t item = (uint16_t)(((j0 + l) << 6) | lane);
+      w.heads |= 1ull << w.n;
+      if (n < 64) {
+        if (cov) {
+          const int pos = (int)__builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(mlo, (uint32_t)w.n));
+          q.item[w.base + pos] = item;
+          if (rank) rank->q[w.base + pos] = rank->ctr++;
+          if constexpr (OWN) w.own |= 1ull << pos;
+        }
+        w.n = n;
+        continue;
+      }
+      uint64_t own_next = 0;  // at most one position past the window: an entry has one pair per pixel
+      if (cov) {
+        const int pos = (int)__builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(mlo, (uint32_t)w.n));
+        const int at = (w.base + pos) & 127;
+        q.item[at] = item;
+        if (rank) rank->q[at] = rank->ctr++;
+        if constexpr (OWN) {
+          const uint64_t bit = 1ull << (pos & 63);
+          if (pos < 64)
+            w.own |= bit;
+          else
+            own_next = bit;
+        }
+      }
+      w.n = 64;
+      w.continues = n > 64;
+      flush(w);
+      w.carried = n > 64;
+      w.n = n - 64;
+      w.base ^= 64;
+      w.heads = n > 64 ? 1ull : 0ull;
+      w.own = own_next;
+    }
+  }
+  w.continues = false;
+  if (w.n > 0) flush(w);
+}
+
+// positions of the window that end a segment
+__device__ __forceinline__ uint64_t segment_heads(const Window& w) {  // positions past the window count as heads
+  return w.n < 64 ? w.heads | (~0ull << w.n) : w.heads;
+}
+__device__ __forceinline__ uint64_t segment_ends(const Window& w) {
+  const uint64_t act = w.n < 64 ? (1ull << w.n) - 1 : ~0ull;
+  return ((segment_heads(w) >> 1) | (1ull << 63)) & act;
+}
+
+// Owner accumulation: calls add(load(i)) for this lane's own queue positions
+// i (bits of `own`) in increasing order, two positions per iteration with
+// both loads issued before either value is consumed.
+template <class Load, class Add>
+__device__ __forceinline__ void for_each_own(uint64_t own, Load&& load, Add&& add) {
+  while (own) {
+    const int i0 = __builtin_ctzll(own);
+    own &= own - 1;
+    const bool two = own != 0;
+    const int i1 = two ? __builtin_ctzll(own) : i0;
+    own &= own - 1;
+    const auto v0 = load(i0);
+    const auto v1 = load(i1);
+    add(v0);
+    if (two) add(v1);
+  }
+}
+
 // Segmented inclusive scan over the wave's lanes with DPP moves: four
 // shifts inside each 16-lane row (row_shr 1, 2, 4, 8), then the classic
 // row_bcast 15 (rows 1 and 3) and row_bcast 31 (rows 2 and 3) steps across
 // rows. Each step adds the moved value times a 0/1 mask that keeps the sum
-// inside the lane's segment [seg_start, lane]; the masks depend only on the
-// segment layout, so one set serves every gradient field. The segment's last
-// lane ends with the segment sum.
+// inside the lane's segment; the masks depend only on the segment layout, so one
+// set serves every gradient field. The segment's last lane ends with the segment
+// sum.
 struct ScanMasks {
   float m[6];
 };
-__device__ __forceinline__ ScanMasks scan_masks(int lane, int seg_start) {
-  ScanMasks s;
-  const int row0 = lane & ~15;
-  const int lo = max(seg_start, row0);
-  s.m[0] = lane - 1 >= lo ? 1.f : 0.f;
-  s.m[1] = lane - 2 >= lo ? 1.f : 0.f;
-  s.m[2] = lane - 4 >= lo ? 1.f : 0.f;
-  s.m[3] = lane - 8 >= lo ? 1.f : 0.f;
-  s.m[4] = ((lane >> 4) & 1) && seg_start < row0 ? 1.f : 0.f;  // takes lane 15 or 47
-  s.m[5] = (lane >> 5) && seg_start <= 31 ? 1.f : 0.f;         // takes lane 31
-  return s;
+__device__ __forceinline__ ScanMasks scan_masks(uint64_t heads) {
+  // lane i takes lane i - 2^k of its row where none of the lanes between, nor
+  // i itself, begins a segment
+  const uint64_t c1 = ~heads & 0xfffefffefffefffeull;
+  const uint64_t c2 = c1 & (c1 << 1);
+  const uint64_t c4 = c2 & (c2 << 2);
+  const uint64_t c8 = c4 & (c4 << 4);
+  // rows 1 and 3 take the row before, the upper half lane 31, up to their first head
+  const uint32_t r1 = (uint32_t)(heads >> 16) & 0xffffu, r3 = (uint32_t)(heads >> 48);
+  const uint32_t hi = (uint32_t)(heads >> 32);
+  const uint64_t b15 = ((uint64_t)(((r1 & (0u - r1)) - 1u) & 0xffffu) << 16) |
+                       ((uint64_t)(((r3 & (0u - r3)) - 1u) & 0xffffu) << 48);
+  const uint64_t b31 = (uint64_t)((hi & (0u - hi)) - 1u) << 32;
+  auto one = [](uint64_t m) __attribute__((always_inline)) {
+    return __builtin_amdgcn_inverse_ballot_w64(m) ? 1.f : 0.f;
+  };
+  return {{one(c1), one(c2), one(c4), one(c8), one(b15), one(b31)}};
 }
 // The scan of the gradient fields in one block of v_fmac_f32 with a DPP
 // source (v += (v moved) * mask; the compiler would emit a separate move for
@@ -368,24 +496,18 @@ __device__ __forceinline__ void segment_scan15(float* g, const ScanMasks& s) {
 #undef MB_SCAN18
 #undef MB_SCAN15
 
-// Per-entry sums of the gradients gr[] of the evaluated queue positions
-// [0, n): queued pairs of one entry are contiguous, a segmented scan over the
-// lanes sums each entry's pairs and the segment's last lane writes (ADD =
-// false) or adds to (ADD = true) the entry's slot. An entry that continues
-// past position n - 1 (cont_j) leaves its partial sum in `carry`.
 // The slot a segment's last lane adds to (pass 3), loaded before the pass's
-// arithmetic so that the load's latency hides behind it; zero elsewhere.
+// arithmetic so that the load's latency hides behind it.
 struct SlotVals {
   float4 s[5];
 };
-__device__ __forceinline__ bool writes_slot(bool act, int j, int n, int lane, int cont_j) {
-  const int jnext = __shfl_down(j, 1, 64);
-  const bool last = act && (lane == n - 1 || jnext != j);
-  return last && !(lane == n - 1 && j == cont_j);
+// the lanes that write a slot: the segments' last, but for an entry that goes on
+__device__ __forceinline__ uint64_t slot_lanes(const Window& w) {
+  return segment_ends(w) & ~(w.continues ? 1ull << 63 : 0ull);
 }
-__device__ __forceinline__ SlotVals load_slot(bool w, int j, const float* partials, const int* sk, int wave) {
+__device__ __forceinline__ SlotVals load_slot(const Window& w, int j, const float* partials, const int* sk, int wave) {
   SlotVals v;  // read only by the lanes that load it
-  if (w) {
+  if (__builtin_amdgcn_inverse_ballot_w64(slot_lanes(w))) {
     const float4* slot = reinterpret_cast<const float4*>(partials + ((size_t)sk[j] * 4 + wave) * kGradStride);
 #pragma unroll
     for (int f = 0; f < 5; ++f) v.s[f] = slot[f];
@@ -393,50 +515,43 @@ __device__ __forceinline__ SlotVals load_slot(bool w, int j, const float* partia
   return v;
 }
 
-// ADD = true adds the slot's earlier contents, passed in as `prev` (see
-// load_slot); ADD = false overwrites the slot.
+// Per-entry sums of the gradients gr[] of the window's pairs: a segmented scan
+// over the lanes sums each entry's pairs and the segment's last lane writes
+// (ADD = false) or adds to (ADD = true, with the slot's earlier contents in
+// `prev`) the entry's slot. An entry that continues in the next window leaves its
+// partial sum in `carry`.
 template <bool ADD>
-__device__ __forceinline__ void reduce_to_slots(float* gr, bool act, int j, int n, int lane, int cont_j, int& carry_j,
-                                                float* carry, float* partials, const int* sk, int wave,
+__device__ __forceinline__ void reduce_to_slots(const Window& w, float* gr, int j, int lane, float* carry,
+                                                float* partials, const int* sk, int wave,
                                                 const SlotVals* prev = nullptr) {
-  const int jprev = __shfl_up(j, 1, 64);
-  const bool head = !act || lane == 0 || jprev != j;
-  const uint64_t heads = __ballot(head);
-  const uint64_t upto = lane == 63 ? ~0ull : ((2ull << lane) - 1);
-  const int seg_start = 63 - __builtin_clzll(heads & upto);
-  const int jnext = __shfl_down(j, 1, 64);
-  const bool last = act && (lane == n - 1 || jnext != j);
   // the moment part (ADD) leaves the colour fields zero: they need no scan
+  const ScanMasks sm = scan_masks(segment_heads(w));
   if constexpr (ADD)
-    segment_scan15(gr, scan_masks(lane, seg_start));
+    segment_scan15(gr, sm);
   else
-    segment_scan18(gr, scan_masks(lane, seg_start));
-  if (last) {
-    if (seg_start == 0 && j == carry_j) {
+    segment_scan18(gr, sm);
+  if (w.carried && lane == __builtin_ctzll(segment_ends(w))) {
 #pragma unroll
-      for (int f = 0; f < G_COUNT; ++f) gr[f] += carry[f];
+    for (int f = 0; f < G_COUNT; ++f) gr[f] += carry[f];
+  }
+  if (w.continues && lane == 63) {
+#pragma unroll
+    for (int f = 0; f < G_COUNT; ++f) carry[f] = gr[f];
+  }
+  if (__builtin_amdgcn_inverse_ballot_w64(slot_lanes(w))) {
+    float4* slot = reinterpret_cast<float4*>(partials + ((size_t)sk[j] * 4 + wave) * kGradStride);
+    if constexpr (ADD) {
+      const float* pv = reinterpret_cast<const float*>(prev->s);
+#pragma unroll
+      for (int f = 0; f < G_COUNT; ++f) gr[f] += pv[f];
     }
-    if (lane == n - 1 && j == cont_j) {
-#pragma unroll
-      for (int f = 0; f < G_COUNT; ++f) carry[f] = gr[f];
-    } else {
-      float4* slot = reinterpret_cast<float4*>(partials + ((size_t)sk[j] * 4 + wave) * kGradStride);
-      if constexpr (ADD) {
-        const float* pv = reinterpret_cast<const float*>(prev->s);
-#pragma unroll
-        for (int f = 0; f < G_COUNT; ++f) gr[f] += pv[f];
-      }
-      slot[0] = make_float4(gr[0], gr[1], gr[2], gr[3]);
-      slot[1] = make_float4(gr[4], gr[5], gr[6], gr[7]);
-      slot[2] = make_float4(gr[8], gr[9], gr[10], gr[11]);
-      slot[3] = make_float4(gr[12], gr[13], gr[14], gr[15]);
-      slot[4] = make_float4(gr[16], gr[17], 0.f, 0.f);
-    }
+    slot[0] = make_float4(gr[0], gr[1], gr[2], gr[3]);
+    slot[1] = make_float4(gr[4], gr[5], gr[6], gr[7]);
+    slot[2] = make_float4(gr[8], gr[9], gr[10], gr[11]);
+    slot[3] = make_float4(gr[12], gr[13], gr[14], gr[15]);
+    slot[4] = make_float4(gr[16], gr[17], 0.f, 0.f);
   }
   __builtin_amdgcn_wave_barrier();
-  // the entry continuing into the next evaluation (if any) owns the carry
-  const int jl = __shfl(j, n - 1, 64);
-  carry_j = (jl == cont_j) ? cont_j : -1;
 }
 
 // MODE 0: the moment bounds of Sec. 3.2 (power moments).
@@ -515,11 +630,11 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
     r.amp = from_lane(pb.amp, p);
     return r;
   };
-  // the pair at queue position `lane` (entry j, pixel lane p); inactive lanes
-  // (lane >= n) get p = lane so the cross-lane reads stay uniform
-  auto item_of = [&](int n, int& j, int& p) __attribute__((always_inline)) {
-    const bool act = lane < n;
-    const int it = act ? (int)q.item[lane] : lane;
+  // the pair at the window's position `lane` (entry j, pixel lane p); inactive
+  // lanes get p = lane so the cross-lane reads stay uniform
+  auto item_of = [&](const Window& w, int& j, int& p) __attribute__((always_inline)) {
+    const bool act = lane < w.n;
+    const int it = act ? (int)q.item[w.base + lane] : lane;
     j = act ? (it >> 6) : 0;
     p = it & 63;
     return act;
@@ -635,10 +750,9 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
     const uint64_t sur_mask = __ballot(qb >= 0);
     float dm0s = 0.f, dmus = 0.f, dsigs = 0.f, dfeat[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     QueueRanks rk{wrank[wave], 0u};
-    int carry_j = -1;
-    auto flush = [&](int n, uint64_t own, int cont_j) __attribute__((always_inline)) {
+    auto flush = [&](const Window& w) __attribute__((always_inline)) {
       int j, p;
-      const bool act = item_of(n, j, p);
+      const bool act = item_of(w, j, p);
       const PixelBasis pp = basis_of(p);
       const float lamp = from_lane(lam, p), m0p = from_lane(m0, p);
       float gap[3] = {from_lane(ga[0], p), from_lane(ga[1], p), from_lane(ga[2], p)};
@@ -651,7 +765,7 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
 #pragma unroll
       for (int f = 0; f < G_COUNT; ++f) gr[f] = 0.f;
       if (act) {
-        const uint32_t rank = wrank[wave][lane];
+        const uint32_t rank = wrank[wave][w.base + lane];
         float dx, dy;
         offsets_of(j, p, dx, dy);
         RayG g = ray_params(st, j, dx, dy, lamp);
@@ -730,6 +844,7 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
         gr[G_CB] = s.q * gap[2];
       }
       __builtin_amdgcn_wave_barrier();
+      uint64_t own = w.own;
       while (own) {
         const int i = __builtin_ctzll(own);
         own &= own - 1;
@@ -739,22 +854,12 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
         dmus += res[7 * 64 + i];
         dsigs += res[8 * 64 + i];
       }
-      reduce_to_slots<false>(gr, act, j, n, lane, cont_j, carry_j, cw, ba.partials, sk, quad);
+      reduce_to_slots<false>(w, gr, j, lane, cw, ba.partials, sk, quad);
     };
     for (int b = rg.x; b < rg.y; b += kBlock) {
       int nb = min(kBlock, rg.y - b);
       stage(b, nb, true);
-      QueueCursor qc;
-      queue_reset(qc);
-      carry_j = -1;
-      queue_from_masks(q, qc, a.masks, b, nb, quad, own4, lane, sur_mask,
-                       [&]() __attribute__((always_inline)) {
-                         const int cont_j = qc.cnt > 64 ? (int)(q.item[64] >> 6) : -1;
-                         flush(64, qc.own_lo, cont_j);
-                         queue_pop64<true>(q, qc, lane, wrank[wave]);
-                       },
-                       zero_slot, &rk);
-      if (qc.cnt > 0) flush(qc.cnt, qc.own_lo, -1);
+      walk_entries<true>(q, a.masks, b, nb, quad, own4, lane, sur_mask, flush, zero_slot, &rk);
     }
     // the moment adjoint through the surrogate's inputs (forward-mode Jacobian
     // of the standardised features in double, one moment at a time)
@@ -775,10 +880,9 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
   } else {
   dm[0] = (active && own4 <= 0) ? e0 : 0.f;  // a split block adds e0 once (wave 0)
   {
-    int carry_j = -1;
-    auto flush = [&](int n, uint64_t own, int cont_j) __attribute__((always_inline)) {
+    auto flush = [&](const Window& w) __attribute__((always_inline)) {
       int j, p;
-      const bool act = item_of(n, j, p);
+      const bool act = item_of(w, j, p);
       const PixelBasis pp = basis_of(p);
       LInv<NH> Lp;
       TrigLInv<TRIG ? NH : 1> TLp;
@@ -930,7 +1034,7 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
         float4 q[RS / 4];
       };
       for_each_own(
-          own,
+          w.own,
           [&](int i) __attribute__((always_inline)) {
             Slots v;
 #pragma unroll
@@ -942,22 +1046,12 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
 #pragma unroll
             for (int k = 0; k <= K; ++k) dm[k] += f[k];
           });
-      reduce_to_slots<false>(gr, act, j, n, lane, cont_j, carry_j, cw, ba.partials, sk, quad);
+      reduce_to_slots<false>(w, gr, j, lane, cw, ba.partials, sk, quad);
     };
     for (int b = rg.x; b < rg.y; b += kBlock) {
       int nb = min(kBlock, rg.y - b);
       stage(b, nb, true);
-      QueueCursor qc;
-      queue_reset(qc);
-      carry_j = -1;
-      queue_from_masks(q, qc, a.masks, b, nb, quad, own4, lane, active_mask,
-                       [&]() __attribute__((always_inline)) {
-                         const int cont_j = qc.cnt > 64 ? (int)(q.item[64] >> 6) : -1;
-                         flush(64, qc.own_lo, cont_j);
-                         queue_pop64(q, qc, lane);
-                       },
-                       zero_slot);
-      if (qc.cnt > 0) flush(qc.cnt, qc.own_lo, -1);
+      walk_entries<true>(q, a.masks, b, nb, quad, own4, lane, active_mask, flush, zero_slot);
     }
   }
 
@@ -1012,11 +1106,10 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
 
   // ---- pass 3: the moment part of the Gradient stage ------------------------
   {
-    int carry_j = -1;
-    auto flush = [&](int n, int cont_j) __attribute__((always_inline)) {
+    auto flush = [&](const Window& w) __attribute__((always_inline)) {
       int j, p;
-      const bool act = item_of(n, j, p);
-      const SlotVals prev = load_slot(writes_slot(act, j, n, lane, cont_j), j, ba.partials, sk, quad);
+      const bool act = item_of(w, j, p);
+      const SlotVals prev = load_slot(w, j, ba.partials, sk, quad);
       const PixelBasis pp = basis_of(p);
       const float lamp = from_lane(lam, p);
       float dmp[K + 1];
@@ -1036,22 +1129,12 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
           moment_grads<K>(g, pp, tn, dmp, gm);
         chain_record(gm[0], gm[1], gm[2], g, lamp, dx, dy, st.f[2][j], st.f[3][j], st.f[4][j], gr);
       }
-      reduce_to_slots<true>(gr, act, j, n, lane, cont_j, carry_j, cw, ba.partials, sk, quad, &prev);
+      reduce_to_slots<true>(w, gr, j, lane, cw, ba.partials, sk, quad, &prev);
     };
     for (int b = rg.x; b < rg.y; b += kBlock) {
       int nb = min(kBlock, rg.y - b);
       stage(b, nb, false);
-      QueueCursor qc;
-      queue_reset(qc);
-      carry_j = -1;
-      queue_from_masks(q, qc, a.masks, b, nb, quad, own4, lane, active_mask,
-                       [&]() __attribute__((always_inline)) {
-                         const int cont_j = qc.cnt > 64 ? (int)(q.item[64] >> 6) : -1;
-                         flush(64, cont_j);
-                         queue_pop64(q, qc, lane);
-                       },
-                       [](int) {});
-      if (qc.cnt > 0) flush(qc.cnt, -1);
+      walk_entries<false>(q, a.masks, b, nb, quad, own4, lane, active_mask, flush, [](int) {});
     }
   }
 }

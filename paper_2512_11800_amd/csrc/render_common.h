@@ -29,14 +29,6 @@ struct WaveQueue {
   uint16_t item[128];  // (entry in the staged batch) << 6 | pixel lane
 };
 
-// Optional rank tracking beside a queue: q[pos] receives the pair's index
-// among its pixel's covering pairs, counted by the pixel lane's ctr. Kept out
-// of WaveQueue so the kernels that do not need it spend no LDS on it.
-struct QueueRanks {
-  uint32_t* q;  // [128] in LDS, parallel to WaveQueue::item
-  uint32_t ctr;
-};
-
 struct QueueCursor {
   int cnt;                  // queued pairs (wave-uniform)
   uint64_t own_lo, own_hi;  // this lane's queue positions [0, 64) and [64, 128)
@@ -48,99 +40,16 @@ __device__ __forceinline__ void queue_reset(QueueCursor& qc) {
   qc.own_hi = 0;
 }
 
-// Append this lane's pair (entry j) if cov; all lanes call it with the same
-// ballot mask. Returns the new count.
-__device__ __forceinline__ void queue_push(WaveQueue& q, QueueCursor& qc, uint64_t mask, bool cov, int j,
-                                           int lane, QueueRanks* rank = nullptr) {
-  if (cov) {
-    int pos = qc.cnt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-    q.item[pos] = (uint16_t)((j << 6) | lane);
-    if (rank) rank->q[pos] = rank->ctr++;
-    if (pos < 64)
-      qc.own_lo |= 1ull << pos;
-    else
-      qc.own_hi |= 1ull << (pos - 64);
-  }
-  qc.cnt += __popcll(mask);
-}
-
-// After evaluating positions [0, 64): move the rest to the front (with their
-// ranks when RANK: only a queue filled with ranks needs them).
-template <bool RANK = false>
-__device__ __forceinline__ void queue_pop64(WaveQueue& q, QueueCursor& qc, int lane, uint32_t* rq = nullptr) {
+// After evaluating positions [0, 64): move the rest to the front.
+__device__ __forceinline__ void queue_pop64(WaveQueue& q, QueueCursor& qc, int lane) {
   int rest = qc.cnt - 64;
   uint16_t it = lane < rest ? q.item[64 + lane] : (uint16_t)0;
-  uint32_t rk = (RANK && lane < rest) ? rq[64 + lane] : 0u;
   __builtin_amdgcn_wave_barrier();
-  if (lane < rest) {
-    q.item[lane] = it;
-    if (RANK) rq[lane] = rk;
-  }
+  if (lane < rest) q.item[lane] = it;
   __builtin_amdgcn_wave_barrier();
   qc.own_lo = qc.own_hi;
   qc.own_hi = 0;
   qc.cnt = rest;
-}
-
-// Queue the pairs of the staged batch [b, b + nb) from the stored coverage
-// masks of this wave (restricted to the lanes of `keep`), skipping empty
-// entries 64 at a time. on_full() evaluates and pops 64 queued pairs;
-// on_empty(j) is called by the lane that loaded entry j's mask when the
-// stored mask has pixels but none of them is kept.
-// In a split block (see BlockWork) a wave takes only the entries j with
-// j % 4 == its wave index (`own4` >= 0); otherwise every entry (`own4` < 0).
-// PREFETCH: the masks of the next 64 entries are loaded before the current
-// 64 are queued and evaluated, so that their latency hides behind that work
-// (two more registers live across the evaluation: the forward kernels gain,
-// the register-bound backward does not).
-template <bool PREFETCH = false, class Full, class Empty>
-__device__ __forceinline__ void queue_from_masks(WaveQueue& q, QueueCursor& qc, const uint64_t* masks, int b, int nb,
-                                                 int quad, int own4, int lane, uint64_t keep, Full&& on_full,
-                                                 Empty&& on_empty, QueueRanks* rank = nullptr) {
-  auto load = [&](int j0) __attribute__((always_inline)) {
-    const bool in = j0 + lane < nb && (own4 < 0 || ((j0 + lane) & 3) == own4);
-    return in ? masks[(size_t)(b + j0 + lane) * 4 + quad] : 0ull;
-  };
-  uint64_t next = PREFETCH ? load(0) : 0ull;
-  for (int j0 = 0; j0 < nb; j0 += 64) {
-    const bool in = j0 + lane < nb && (own4 < 0 || ((j0 + lane) & 3) == own4);
-    uint64_t raw;
-    if constexpr (PREFETCH) {
-      raw = next;
-      next = j0 + 64 < nb ? load(j0 + 64) : 0ull;
-    } else {
-      raw = load(j0);
-    }
-    const uint64_t mk = raw & keep;
-    if (in && mk == 0 && raw != 0) on_empty(j0 + lane);
-    uint64_t nz = __ballot(mk != 0);
-    while (nz) {
-      const int l = __builtin_ctzll(nz);
-      nz &= nz - 1;
-      const uint64_t m = __shfl(mk, l, 64);
-      queue_push(q, qc, m, (m >> lane) & 1ull, j0 + l, lane, rank);
-      if (qc.cnt >= 64) on_full();
-    }
-  }
-}
-
-// Owner accumulation: calls add(load(i)) for this lane's own queue positions
-// i (bits of `own`) in increasing order, two positions per iteration with
-// both loads issued before either value is consumed.
-template <class Load, class Add>
-__device__ __forceinline__ void for_each_own(uint64_t own, Load&& load, Add&& add) {
-  while (own) {
-    const int i0 = __builtin_ctzll(own);
-    own &= own - 1;
-    const bool two = own != 0;
-    const int i1 = two ? __builtin_ctzll(own) : i0;
-    own &= own - 1;
-    const auto v0 = load(i0);
-    const auto v1 = load(i1);
-    add(v0);
-    if (two) add(v1);
-  }
 }
 
 // value of pixel lane p (all lanes must take part)

@@ -1,13 +1,16 @@
-"""The forward kernel's walk of a tile's list by pixel words: list lengths at the
-edges of its 64-entry chunks, 256-entry batches and the heavy-tile split (512),
-with every pixel covered (all rounds full) and with coverage of every kind (thin
-rounds queued), on ragged images, against the oracle."""
+"""The forward kernel's walk of a tile's list by pixel words, and the backward
+kernel's by entries: list lengths at the edges of their 64-entry chunks, 256-entry
+batches and the heavy-tile split (512), with every pixel covered (all rounds and
+windows full) and with coverage of every kind (thin rounds queued, segments over
+the windows' ends), on ragged images, against the oracle."""
+import numpy as np
 import pytest
 import torch
 
 import oracle
 import workloads as W
 from tests.gpu_helpers import compare, gpu_render, log, proxy_error, tolerances
+from tests.test_gpu_backward import _check, _gpu_grads
 
 pytestmark = pytest.mark.gpu
 
@@ -35,3 +38,18 @@ def test_walk_covers_each_pair_once():
         _, saved, _ = M.render_forward(g, [W.camera_on_axis(2.0, 17, 33)], W.Options(full_coverage=True))
         c = saved[..., 7]
         assert torch.equal(torch.where(c < 0, -c - 1, c), torch.full_like(c, float(n)))
+
+
+@pytest.mark.parametrize("n", [63, 64, 65, 130, 257, 520])
+@pytest.mark.parametrize("full", [True, False])
+def test_list_lengths_gradients_match_oracle(n, full):
+    """To the backward tests' bar of 1e-3 per parameter group."""
+    scene = W.uniform_scene(n, seed=n, extent=0.25, log_scale_mean=-2.5)
+    cam = W.camera_on_axis(2.0, 21, 18)
+    opts = W.Options(full_coverage=full)
+    g_img = np.random.default_rng(n).normal(size=(cam.width * cam.height, 3))
+    if not full:
+        tol_m, tol_o = tolerances(proxy_error(scene, cam, opts))
+        g_img[oracle.render_image(scene, cam, opts, margin_tol=tol_m, orient_eps=tol_o)["ambiguous"]] = 0.0
+    gpu, _ = _gpu_grads(scene, [cam], opts, g_img)
+    assert _check(gpu, oracle.render_backward(scene, cam, opts, g_img), f"walk n={n} full={full}")
