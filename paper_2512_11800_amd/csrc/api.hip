@@ -238,7 +238,8 @@ double normal_quantile(double u) {
   return x;
 }
 
-void fill_quantiles(const mb_options* o, float* xq, float* eq, float* ecq) {
+void fill_quantiles(const mb_options* o, RenderArgs& a) {
+  float *xq = a.xq, *eq = a.eq, *ecq = a.ecq;
   int nq = o->n_intervals + 1;
   for (int j = 0; j < 8; ++j) { xq[j] = 0.f; eq[j] = 0.f; ecq[j] = 0.f; }
   for (int j = 0; j < nq; ++j) {
@@ -248,6 +249,8 @@ void fill_quantiles(const mb_options* o, float* xq, float* eq, float* ecq) {
     eq[j] = (float)std::exp(-0.5 * (double)o->kappa * o->kappa * x * x);
     ecq[j] = (float)std::erfc((double)o->kappa * x / std::sqrt(2.0));
   }
+  for (int j = 0; j < 8; ++j) a.kxq[j] = o->kappa * xq[j];
+  for (int j = 0; j < 8; ++j) a.dkxq[j] = j + 1 < nq ? a.kxq[j + 1] - a.kxq[j] : 0.f;
 }
 
 int key_bits(int64_t n_keys) {
@@ -337,7 +340,7 @@ int forward_setup(const mb_gaussians* g, const mb_camera* cams, int32_t n_cams, 
   ra.image = image; ra.saved = saved;
   ra.tiles_x = tx; ra.tiles_y = ty; ra.n_cams = n_cams; ra.full_coverage = o->full_coverage;
   ra.kappa = o->kappa; ra.beta = o->beta; ra.eps = o->eps;
-  fill_quantiles(o, ra.xq, ra.eq, ra.ecq);
+  fill_quantiles(o, ra);
   return MB_OK;
 }
 
@@ -723,7 +726,7 @@ int backward_common(const mb_gaussians* g, const mb_camera* cams, int32_t n_cams
   ra.n_pix = (long long)n_cams * cams[0].width * cams[0].height;
   ra.tiles_x = tx; ra.tiles_y = ty; ra.n_cams = n_cams; ra.full_coverage = o->full_coverage;
   ra.kappa = o->kappa; ra.beta = o->beta; ra.eps = o->eps;
-  fill_quantiles(o, ra.xq, ra.eq, ra.ecq);
+  fill_quantiles(o, ra);
   hipError_t e;
   if (q) {
     int64_t n_pix = (int64_t)n_cams * cams[0].width * cams[0].height;

@@ -117,6 +117,8 @@ struct RenderArgs {
   float xq[8];    // standard-normal edge quantiles
   float eq[8];    // exp(-kappa^2 xq^2 / 2)
   float ecq[8];   // erfc(kappa xq / sqrt2)
+  float kxq[8];   // kappa xq, and its differences
+  float dkxq[8];
   float* penalty; // [C,H,W] consistency penalty per pixel, or null
   double* pix_mom; // [kMaxMoments + 1][C*H*W] per-pixel moment sums, written by the forward pass
   long long n_pix; // C*H*W

@@ -19,7 +19,8 @@
 // The passes walk the coverage masks the forward pass stored (walk_entries).
 // The kernel is bound by VALU issue: per 64 pairs about 3500 issue cycles of pass 2
 // and 1400 of pass 3 beside the queueing. With the queue's state in scalar
-// registers: 2.21 -> 2.06 ms (K = 4), 3.74 -> 3.41 ms (K = 6) at 500k Gaussians,
+// registers, the near bound's selects out of the way and the pixels' values in LDS
+// it takes 2.21 -> 1.97 ms (K = 4), 3.74 -> 3.15 ms (K = 6) at 500k Gaussians,
 // 1920x1080; the gradients are the same bits.
 #include "render_common.h"
 #include "trig.h"
@@ -32,7 +33,8 @@ struct QuadState {
   float t[NQ], y[NQ], w0[NQ], F[NQ], tau[NQ], T[NQ], sr[NQ], off[NQ];
   float x[NQ][NH];
   bool below[NQ][NH];
-  bool cl[NQ];
+  bool cl[NQ];  // the edge lies on the near bound; set where `near`
+  bool near;    // wave-uniform: some lane's first edge does (the edges ascend)
   float dt[NQ], ph[NQ], dph[NQ], A[NQ];
   float q;
 };
@@ -49,36 +51,62 @@ __device__ __forceinline__ float dphi_fn(float x, float d, float ph) {
   return fabsf(x) < kPhiSeries ? -s : (d - ph) * fast_rcp(x);
 }
 
-// Edges of one Gaussian's quadrature (App. B) and sigma_i there.
-template <int NH, int NQ>
+// Edges of one Gaussian's quadrature (App. B) and sigma_i there. A wave without an
+// edge on the near bound takes the short forms here and below: the selects and
+// their masks took 2.06 ms where 2.01 do (K = 4), and with the registers they held
+// 3.41 ms where 3.20 do (K = 6, spills), at 500k Gaussians, 1920x1080.
+// FUSED: which operations are fused. The optical depths that the adjoint passes
+// through follow the edges' last bits, and a degenerate pixel's gradients magnify
+// them; the operations are therefore fixed here and do not follow the code around.
+template <int NH, int NQ, bool FUSED>
 __device__ __forceinline__ void quad_geom(const RayG& g, const PixelBasis& pb, float tn, const RenderArgs& a,
                                           QuadState<NH, NQ>& s) {
-  float dtc = g.mu - pb.tc;
-  const float rn = (tn - g.mu) * fast_rcp(g.sig);  // edges moved onto the near bound
-  const float en = exp_neg_half(rn * rn);
+  const float mu = rounded(g.mu), ks = rounded(a.kappa * g.sig);
+  const float dtc = FUSED ? fmaf(g.id, g.le, -pb.tc) : mu - pb.tc;
 #pragma unroll
   for (int j = 0; j < NQ; ++j) {
-    s.off[j] = a.kappa * g.sig * a.xq[j];
-    float t = g.mu + s.off[j];
-    s.cl[j] = t < tn;
-    float dtj = s.cl[j] ? (tn - pb.tc) : (dtc + s.off[j]);
-    s.t[j] = s.cl[j] ? tn : t;
-    s.y[j] = warp_y(pb, s.t[j], dtj);
-    s.sr[j] = s.cl[j] ? en : a.eq[j];
+    s.off[j] = rounded(ks * a.xq[j]);
+    s.t[j] = fmaf(ks, a.xq[j], mu);
+    s.y[j] = FUSED ? fmaf(ks, a.xq[j], dtc) : dtc + s.off[j];
+    s.sr[j] = a.eq[j];
+    s.cl[j] = false;
   }
+  s.near = __ballot(s.t[0] < tn) != 0;
+  if (s.near) {
+    const float rn = (tn - g.mu) * fast_rcp(g.sig);  // edges moved onto the near bound
+    const float en = exp_neg_half(rn * rn);
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+      s.cl[j] = s.t[j] < tn;
+      s.y[j] = s.cl[j] ? (tn - pb.tc) : s.y[j];
+      s.t[j] = s.cl[j] ? tn : s.t[j];
+      s.sr[j] = s.cl[j] ? en : s.sr[j];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) s.y[j] = warp_y(pb, s.t[j], s.y[j]);
 }
 
 // Given the optical depth s.tau at the edges: the Eq. 7 terms, q, and
 // A[j] = dq / dtau_j.
 template <int NH, int NQ>
 __device__ __forceinline__ void quad_terms(const RayG& g, float tn, QuadState<NH, NQ>& s) {
+  if (s.near) {
+#pragma unroll
+    for (int j = 0; j + 1 < NQ; ++j) {
+      const float first = s.t[j + 1] - tn, free = s.off[j + 1] - s.off[j];
+      s.dt[j] = s.cl[j + 1] ? 0.f : (s.cl[j] ? first : free);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j + 1 < NQ; ++j) s.dt[j] = s.off[j + 1] - s.off[j];
+  }
   s.T[0] = __expf(-s.tau[0]);
   s.q = 0.f;
 #pragma unroll
   for (int j = 0; j < NQ; ++j) s.A[j] = 0.f;
 #pragma unroll
   for (int j = 0; j + 1 < NQ; ++j) {
-    s.dt[j] = s.cl[j + 1] ? 0.f : (s.cl[j] ? (g.mu + s.off[j + 1] - tn) : (s.off[j + 1] - s.off[j]));
     float dtau = s.tau[j + 1] - s.tau[j];
     const float d = __expf(-dtau);
     s.T[j + 1] = s.T[j] * d;
@@ -92,10 +120,61 @@ __device__ __forceinline__ void quad_terms(const RayG& g, float tn, QuadState<NH
   }
 }
 
+// dq / d(mu, Sigma, omega) at fixed optical depths
+template <int NH, int NQ>
+__device__ __forceinline__ void quad_position_grads(const RayG& g, const QuadState<NH, NQ>& s, const RenderArgs& a,
+                                                    float& dq0, float& dq1, float& dq2) {
+  dq0 = dq1 = dq2 = 0.f;
+  if (s.near) {
+    const float isg = fast_rcp(g.sig);
+#pragma unroll
+    for (int e = 0; e + 1 < NQ; ++e) {
+      const float cdt = s.T[e] * s.ph[e] * g.omega * s.sr[e];
+      const float dmu0 = s.cl[e] ? 0.f : 1.f, dmu1 = s.cl[e + 1] ? 0.f : 1.f;
+      const float dsg0 = s.cl[e] ? 0.f : a.kxq[e], dsg1 = s.cl[e + 1] ? 0.f : a.kxq[e + 1];
+      dq0 += cdt * (dmu1 - dmu0);
+      dq1 += cdt * (dsg1 - dsg0);
+      const float cs = s.T[e] * s.dt[e] * s.ph[e];
+      if (s.cl[e]) {
+        const float r = (s.t[e] - g.mu) * isg;
+        const float sj = g.omega * s.sr[e];
+        dq0 += cs * sj * r * isg;
+        dq1 += cs * sj * r * r * isg;
+      }
+      dq2 += cs * s.sr[e];
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e + 1 < NQ; ++e) {
+      dq1 += s.T[e] * s.ph[e] * g.omega * s.sr[e] * a.dkxq[e];
+      dq2 += s.T[e] * s.dt[e] * s.ph[e] * s.sr[e];
+    }
+  }
+}
+
+// adds wgt dtau_dt dt_e / d(mu, Sigma) to (gmu, gsig)
+template <int NH, int NQ>
+__device__ __forceinline__ void edge_position_grads(const QuadState<NH, NQ>& s, const RenderArgs& a,
+                                                    const float* gt, float& gmu, float& gsig) {
+  if (s.near) {
+#pragma unroll
+    for (int e = 0; e < NQ; ++e) {
+      gmu += gt[e] * (s.cl[e] ? 0.f : 1.f);
+      gsig += gt[e] * (s.cl[e] ? 0.f : a.kxq[e]);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < NQ; ++e) {
+      gmu += gt[e];
+      gsig += gt[e] * a.kxq[e];
+    }
+  }
+}
+
 template <int NH, int NQ>
 __device__ __forceinline__ void quad_state(const RayG& g, const PixelBasis& pb, const LInv<NH>& L, float m0,
                                            float tn, const RenderArgs& a, QuadState<NH, NQ>& s) {
-  quad_geom<NH, NQ>(g, pb, tn, a, s);
+  quad_geom<NH, NQ, (NH > 2)>(g, pb, tn, a, s);
 #pragma unroll
   for (int j = 0; j < NQ; ++j) {
     s.F[j] = canon_at<NH>(L, s.y[j], a.beta, s.x[j], s.below[j], s.w0[j]);
@@ -114,6 +193,7 @@ __device__ __forceinline__ void trig_quad_state(const RayG& g, const TrigLInv<NH
                                                 const RenderArgs& a, QuadState<NH, NQ>& s, TrigCanon<NH>* tc,
                                                 int* src) {
   cfl start = {__builtin_nanf(""), 0.f};  // the first edge starts from its query point
+  s.near = __ballot(g.mu + a.kappa * g.sig * a.xq[0] < tn) != 0;
 #pragma unroll
   for (int j = 0; j < NQ; ++j) {
     s.off[j] = a.kappa * g.sig * a.xq[j];
@@ -283,6 +363,36 @@ __device__ __forceinline__ void chain_record(float gmu, float gsig, float gom, c
   gr[G_P0X] = -gdx;
   gr[G_P0Y] = -gdy;
   gr[G_W] = gom * ek;
+}
+
+// Staged records without the word that only the coverage test reads.
+struct BwdStage {
+  float4 r[kRecF4 - 1][kBlock];
+  __device__ __forceinline__ const float4& word(int k, int j) const { return r[k == 0 ? 0 : k - 1][j]; }
+};
+// Stage the batch [b, b + nb) (load_batch_covered for these records). Entries whose masks are empty for the
+// pixels of this block (all four quadrants, or the block's one) are never queued,
+// and their records are not loaded.
+__device__ __forceinline__ void load_batch(BwdStage& st, const float4* rec, const int* sorted_rec,
+                                           const uint64_t* masks, int quad, int b, int nb) {
+  int tid = threadIdx.x;
+  if (tid < nb) {
+    const uint64_t* mp = masks + (size_t)(b + tid) * 4;
+    bool need;
+    if (quad >= 0) {
+      need = mp[quad] != 0ull;
+    } else {
+      const ulonglong2 m01 = reinterpret_cast<const ulonglong2*>(mp)[0];
+      const ulonglong2 m23 = reinterpret_cast<const ulonglong2*>(mp)[1];
+      need = (m01.x | m01.y | m23.x | m23.y) != 0ull;
+    }
+    if (need) {
+      const float4* src = rec + (size_t)sorted_rec[b + tid] * kRecStride;
+      st.r[0][tid] = src[0];
+#pragma unroll
+      for (int k = 2; k < kRecF4; ++k) st.r[k - 1][tid] = src[k];
+    }
+  }
 }
 
 // The backward pass's queue of pairs, entry by entry (pairs of one entry lie next
@@ -505,10 +615,10 @@ struct SlotVals {
 __device__ __forceinline__ uint64_t slot_lanes(const Window& w) {
   return segment_ends(w) & ~(w.continues ? 1ull << 63 : 0ull);
 }
-__device__ __forceinline__ SlotVals load_slot(const Window& w, int j, const float* partials, const int* sk, int wave) {
+__device__ __forceinline__ SlotVals load_slot(const Window& w, int j, const float* partials, const BwdStage& st, int wave) {
   SlotVals v;  // read only by the lanes that load it
   if (__builtin_amdgcn_inverse_ballot_w64(slot_lanes(w))) {
-    const float4* slot = reinterpret_cast<const float4*>(partials + ((size_t)sk[j] * 4 + wave) * kGradStride);
+    const float4* slot = reinterpret_cast<const float4*>(partials + ((size_t)__float_as_int(st.word(0, j).z) * 4 + wave) * kGradStride);
 #pragma unroll
     for (int f = 0; f < 5; ++f) v.s[f] = slot[f];
   }
@@ -522,7 +632,7 @@ __device__ __forceinline__ SlotVals load_slot(const Window& w, int j, const floa
 // partial sum in `carry`.
 template <bool ADD>
 __device__ __forceinline__ void reduce_to_slots(const Window& w, float* gr, int j, int lane, float* carry,
-                                                float* partials, const int* sk, int wave,
+                                                float* partials, const BwdStage& st, int wave,
                                                 const SlotVals* prev = nullptr) {
   // the moment part (ADD) leaves the colour fields zero: they need no scan
   const ScanMasks sm = scan_masks(segment_heads(w));
@@ -539,7 +649,7 @@ __device__ __forceinline__ void reduce_to_slots(const Window& w, float* gr, int 
     for (int f = 0; f < G_COUNT; ++f) carry[f] = gr[f];
   }
   if (__builtin_amdgcn_inverse_ballot_w64(slot_lanes(w))) {
-    float4* slot = reinterpret_cast<float4*>(partials + ((size_t)sk[j] * 4 + wave) * kGradStride);
+    float4* slot = reinterpret_cast<float4*>(partials + ((size_t)__float_as_int(st.word(0, j).z) * 4 + wave) * kGradStride);
     if constexpr (ADD) {
       const float* pv = reinterpret_cast<const float*>(prev->s);
 #pragma unroll
@@ -554,6 +664,73 @@ __device__ __forceinline__ void reduce_to_slots(const Window& w, float* gr, int 
   __builtin_amdgcn_wave_barrier();
 }
 
+// A pixel's values for the lanes that evaluate its pairs: the first S of N in a
+// row of LDS, read by 16-byte loads (rows an odd number of 16 bytes apart, spread
+// over the banks), the others broadcast from the pixel lane's registers. A shuffle
+// a value held 20 more registers through the passes and took 27 LDS instructions
+// a window where 5 loads do: 2.01 -> 1.97 ms (K = 4), 3.20 -> 3.15 ms (K = 6) at
+// 500k Gaussians, 1920x1080 (3 blocks a compute unit: 2 take 2.54 and 3.93 ms, 4
+// with 160 entries staged at a time 1.94 ms but more where lists are long).
+template <int S>
+struct PixelRows {
+  static_assert(S % 8 == 4, "rows of an odd number of 16-byte words");
+  float4* r;  // [64][S / 4]
+  template <int N>
+  __device__ __forceinline__ void put(int lane, const float* v) const {
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < S && i < N; i += 4)
+      r[lane * (S / 4) + i / 4] = make_float4(v[i], i + 1 < N ? v[i + 1] : 0.f, i + 2 < N ? v[i + 2] : 0.f,
+                                              i + 3 < N ? v[i + 3] : 0.f);
+    __builtin_amdgcn_wave_barrier();
+  }
+  // out: pixel lane p's values; mine: this lane's own (all lanes must take part)
+  template <int N>
+  __device__ __forceinline__ void get(int p, const float* mine, float* out) const {
+#pragma unroll
+    for (int i = 0; i < S && i < N; i += 4) {
+      const float4 v = r[p * (S / 4) + i / 4];
+      out[i] = v.x;
+      if (i + 1 < N) out[i + 1] = v.y;
+      if (i + 2 < N) out[i + 2] = v.z;
+      if (i + 3 < N) out[i + 3] = v.w;
+    }
+#pragma unroll
+    for (int i = S; i < N; ++i) out[i] = from_lane(mine[i], p);
+  }
+};
+
+// A window's results, N floats a pair, in LDS arrays of 16-, 8- and 4-byte elements
+template <int N>
+struct Results {
+  float v[N];
+  __device__ __forceinline__ void store(float* res, int i) const {
+    constexpr int n4 = N / 4;
+#pragma unroll
+    for (int k = 0; k < n4; ++k)
+      reinterpret_cast<float4*>(res)[64 * k + i] = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+    if constexpr (N & 2) reinterpret_cast<float2*>(res + 256 * n4)[i] = make_float2(v[4 * n4], v[4 * n4 + 1]);
+    if constexpr (N & 1) res[64 * (N - 1) + i] = v[N - 1];
+  }
+  __device__ __forceinline__ void load(const float* res, int i) {
+    constexpr int n4 = N / 4;
+#pragma unroll
+    for (int k = 0; k < n4; ++k) {
+      const float4 f = reinterpret_cast<const float4*>(res)[64 * k + i];
+      v[4 * k] = f.x;
+      v[4 * k + 1] = f.y;
+      v[4 * k + 2] = f.z;
+      v[4 * k + 3] = f.w;
+    }
+    if constexpr (N & 2) {
+      const float2 f = reinterpret_cast<const float2*>(res + 256 * n4)[i];
+      v[4 * n4] = f.x;
+      v[4 * n4 + 1] = f.y;
+    }
+    if constexpr (N & 1) v[N - 1] = res[64 * (N - 1) + i];
+  }
+};
+
 // MODE 0: the moment bounds of Sec. 3.2 (power moments).
 // MODE 1: the backward pass through the learned surrogate (the forward pass
 // was mb_render_forward_surrogate): the optical depth at every edge is m_0 F
@@ -563,21 +740,23 @@ __device__ __forceinline__ void reduce_to_slots(const Window& w, float* gr, int 
 // the adjoint of the reconstruction on the circle (trig_adjoint) and of
 // Eq. 14 (trig_moment_grads) in place of the power moments'.
 template <int K, int NQ, int MODE>
-__global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void k_render_bwd(BwdArgs ba,
-                                                                                              CamSet cams) {
+constexpr int kBwdBlocks = (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2;  // blocks a compute unit
+template <int K, int NQ, int MODE>
+__global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(BwdArgs ba, CamSet cams) {
   constexpr bool SUR = MODE == 1;
   constexpr bool TRIG = MODE == 2;
   static_assert(!TRIG || K == 4 || K == 6, "the trigonometric path takes two or three complex moments");
   constexpr int NH = K / 2;
   constexpr int NL = (NH + 1) * (NH + 2) / 2;
-  constexpr int RS = (K + 4) / 4 * 4;  // plain pass 2: K + 1 adjoint moments per pair, padded to float4s
-  constexpr int NRES = SUR ? 9 : RS;   // results per queued pair ([k][64], or [64][RS] in the plain pass 2)
+  constexpr int NRES = SUR ? 9 : K + 1;  // results per queued pair
+  // pixel rows: as many values as leave LDS for the blocks the registers allow
+  constexpr int S = SUR ? 12 : (kBwdBlocks<K, NQ, MODE> == 3 ? 20 : 28);
   const RenderArgs& a = ba.r;
-  __shared__ Stage st;
-  __shared__ int sk[kBlock];
+  __shared__ BwdStage st;
   __shared__ WaveQueue wq[4];
   __shared__ uint32_t wrank[4][SUR ? 128 : 1];           // pair ranks (surrogate queries)
   __shared__ __align__(16) float wres[4][NRES * 64];     // per queued pair results
+  __shared__ float4 prow[4][64 * S / 4];                 // pixel values
   __shared__ float carry[4][G_COUNT];                    // partial slot of an entry split over evaluations
   const int tiles_per_cam = a.tiles_x * a.tiles_y;
   const int n_keys = tiles_per_cam * a.n_cams;
@@ -606,6 +785,7 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
   const size_t pix = inside ? ((size_t)ci * c.height + py) * c.width + px : 0;
   WaveQueue& q = wq[wave];
   float* res = wres[wave];
+  const PixelRows<S> rows{prow[wave]};
 
   float sv[8] = {0.f, 0.f, 0.f, 0.f, tn + 1.f, 1.f, 0.f, 0.f};
   float gi[3] = {0.f, 0.f, 0.f};
@@ -640,18 +820,18 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
     return act;
   };
   auto offsets_of = [&](int j, int p, float& dx, float& dy) __attribute__((always_inline)) {
-    dx = (float)(x0 + (p & 7)) + 0.5f - st.f[0][j].x;
-    dy = (float)(y0 + (p >> 3)) + 0.5f - st.f[0][j].y;
+    dx = (float)(x0 + (p & 7)) + 0.5f - st.word(0, j).x;
+    dy = (float)(y0 + (p >> 3)) + 0.5f - st.word(0, j).y;
   };
   // flags: mark which of the entries' slots this block writes (an entry's
   // slot for a quadrant whose stored mask is empty is neither written nor
   // read: its sum is zero)
   auto stage = [&](int b, int nb, bool flags) __attribute__((always_inline)) {
     __syncthreads();
-    load_batch_covered(st, a.rec, a.sorted_rec, a.masks, bw.quad, b, nb);
+    load_batch(st, a.rec, a.sorted_rec, a.masks, bw.quad, b, nb);
     if (tid < nb) {
       const int k = ba.sorted_k[b + tid];
-      sk[tid] = k;
+      st.r[0][tid].z = __int_as_float(k);  // the entry's index in place of its centre offset (coverage only)
       if (flags) {
         const uint64_t* mp = a.masks + (size_t)(b + tid) * 4;
         if (bw.quad >= 0) {
@@ -725,7 +905,7 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
   // the slot of an entry whose stored mask has pixels, none of which this
   // pass keeps (outside the image, or without density), is written as zero
   auto zero_slot = [&](int j) __attribute__((always_inline)) {
-    float4* slot = reinterpret_cast<float4*>(ba.partials + ((size_t)sk[j] * 4 + quad) * kGradStride);
+    float4* slot = reinterpret_cast<float4*>(ba.partials + ((size_t)__float_as_int(st.word(0, j).z) * 4 + quad) * kGradStride);
 #pragma unroll
     for (int f = 0; f < kGradStride / 4; ++f) slot[f] = make_float4(0.f, 0.f, 0.f, 0.f);
   };
@@ -770,7 +950,7 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
         offsets_of(j, p, dx, dy);
         RayG g = ray_params(st, j, dx, dy, lamp);
         QuadState<NH, NQ> s;
-        quad_geom<NH, NQ>(g, pp, tn, a, s);
+        quad_geom<NH, NQ, false>(g, pp, tn, a, s);
         // F as the forward pass used it; its input gradient beside it
         const long long qi = qbase_p + (long long)rank * NQ;
         const float* qg = a.q_g + qi * 8;
@@ -786,7 +966,7 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
           src[e] = up ? e : src[e > 0 ? e - 1 : 0];
         }
         quad_terms<NH, NQ>(g, tn, s);
-        float4 f5 = st.f[5][j];
+        float4 f5 = st.word(5, j);
         const float gbar = gap[0] * f5.y + gap[1] * f5.z + gap[2] * f5.w + gbp;
         // dL/dtau gathered onto the edges whose queries supplied it
         float wsrc[NQ];
@@ -798,7 +978,7 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
           for (int e2 = 0; e2 <= e; ++e2) wsrc[e2] += src[e] == e2 ? gbar * s.A[e] : 0.f;
         }
         float c[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        float gmu = 0.f, gsig = 0.f, gom = 0.f;
+        float gmu = 0.f, gsig = 0.f, gom = 0.f, gt[NQ];
         const float isg = fast_rcp(ssigp);
 #pragma unroll
         for (int e = 0; e < NQ; ++e) {
@@ -811,34 +991,17 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
           const float gz = fabsf(zr) < 10.f ? wgt * m0p * ge[7] * isg : 0.f;  // dL/dy at the edge
           c[7] -= gz;       // z = (y - mu) / sig
           c[8] -= gz * zr;
-          const float dydt = warp_dy(pp, s.t[e]);
-          gmu += gz * dydt * (s.cl[e] ? 0.f : 1.f);
-          gsig += gz * dydt * (s.cl[e] ? 0.f : a.kappa * a.xq[e]);
+          gt[e] = rounded(gz * warp_dy(pp, s.t[e]));
         }
-        float dq0 = 0.f, dq1 = 0.f, dq2 = 0.f;
-#pragma unroll
-        for (int e = 0; e + 1 < NQ; ++e) {
-          float cdt = s.T[e] * s.ph[e] * g.omega * s.sr[e];
-          float dmu0 = s.cl[e] ? 0.f : 1.f, dmu1 = s.cl[e + 1] ? 0.f : 1.f;
-          float dsg0 = s.cl[e] ? 0.f : a.kappa * a.xq[e], dsg1 = s.cl[e + 1] ? 0.f : a.kappa * a.xq[e + 1];
-          dq0 += cdt * (dmu1 - dmu0);
-          dq1 += cdt * (dsg1 - dsg0);
-          float cs = s.T[e] * s.dt[e] * s.ph[e];
-          if (s.cl[e]) {
-            float r = (s.t[e] - g.mu) * fast_rcp(g.sig);
-            float sj = g.omega * s.sr[e];
-            const float igs = fast_rcp(g.sig);
-            dq0 += cs * sj * r * igs;
-            dq1 += cs * sj * r * r * igs;
-          }
-          dq2 += cs * s.sr[e];
-        }
+        edge_position_grads<NH, NQ>(s, a, gt, gmu, gsig);
+        float dq0, dq1, dq2;
+        quad_position_grads<NH, NQ>(g, s, a, dq0, dq1, dq2);
         gmu += gbar * dq0;
         gsig += gbar * dq1;
         gom += gbar * dq2;
 #pragma unroll
         for (int k = 0; k < 9; ++k) res[k * 64 + lane] = c[k];
-        chain_record(gmu, gsig, gom, g, lamp, dx, dy, st.f[2][j], st.f[3][j], st.f[4][j], gr);
+        chain_record(gmu, gsig, gom, g, lamp, dx, dy, st.word(2, j), st.word(3, j), st.word(4, j), gr);
         gr[G_CR] = s.q * gap[0];
         gr[G_CG] = s.q * gap[1];
         gr[G_CB] = s.q * gap[2];
@@ -854,7 +1017,7 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
         dmus += res[7 * 64 + i];
         dsigs += res[8 * 64 + i];
       }
-      reduce_to_slots<false>(w, gr, j, lane, cw, ba.partials, sk, quad);
+      reduce_to_slots<false>(w, gr, j, lane, cw, ba.partials, st, quad);
     };
     for (int b = rg.x; b < rg.y; b += kBlock) {
       int nb = min(kBlock, rg.y - b);
@@ -879,31 +1042,59 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
     }
   } else {
   dm[0] = (active && own4 <= 0) ? e0 : 0.f;  // a split block adds e0 once (wave 0)
+  // the pixel's values: factor, m_0, lambda, b_1..K, basis (power moments), a, b
+  constexpr int V_BK = (TRIG ? 2 : 1) * NL + 2, NV = V_BK + K + (TRIG ? 4 : 8);
+  float own[NV];
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    if constexpr (TRIG) {
+      own[i] = TL.re[i];
+      own[NL + i] = TL.im[i];
+    } else {
+      own[i] = L.l[i];
+    }
+  }
+  own[V_BK - 2] = m0;
+  own[V_BK - 1] = lam;
+#pragma unroll
+  for (int k = 1; k <= K; ++k) own[V_BK - 1 + k] = bk[k];
+  if constexpr (!TRIG) {
+    own[V_BK + K] = pb.tc;
+    own[V_BK + K + 1] = pb.p;
+    own[V_BK + K + 2] = pb.p15;
+    own[V_BK + K + 3] = pb.amp;
+  }
+#pragma unroll
+  for (int ch = 0; ch < 3; ++ch) own[NV - 4 + ch] = ga[ch];
+  own[NV - 1] = gb;
+  rows.template put<NV>(lane, own);
   {
     auto flush = [&](const Window& w) __attribute__((always_inline)) {
       int j, p;
       const bool act = item_of(w, j, p);
-      const PixelBasis pp = basis_of(p);
+      float pv[NV];
+      rows.template get<NV>(p, own, pv);
+      PixelBasis pp;
       LInv<NH> Lp;
       TrigLInv<TRIG ? NH : 1> TLp;
       if constexpr (TRIG) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
-          TLp.re[i] = from_lane(TL.re[i], p);
-          TLp.im[i] = from_lane(TL.im[i], p);
+          TLp.re[i] = pv[i];
+          TLp.im[i] = pv[NL + i];
         }
       } else {
 #pragma unroll
-        for (int i = 0; i < NL; ++i) Lp.l[i] = from_lane(L.l[i], p);
+        for (int i = 0; i < NL; ++i) Lp.l[i] = pv[i];
+        pp.tc = pv[V_BK + K];
+        pp.p = pv[V_BK + K + 1];
+        pp.p15 = pv[V_BK + K + 2];
+        pp.amp = pv[V_BK + K + 3];
       }
-      const float lamp = from_lane(lam, p), m0p = from_lane(m0, p);
-      float gap[3] = {from_lane(ga[0], p), from_lane(ga[1], p), from_lane(ga[2], p)};
-      const float gbp = from_lane(gb, p);
-      const float gpp = from_lane(gpen, p);
-      float bkp[K + 1];
-      bkp[0] = 1.f;
-#pragma unroll
-      for (int k = 1; k <= K; ++k) bkp[k] = from_lane(bk[k], p);
+      const float m0p = pv[V_BK - 2], lamp = pv[V_BK - 1];
+      const float* bkp = pv + V_BK - 1;  // bkp[k], k = 1..K
+      const float *gap = pv + NV - 4, gbp = pv[NV - 1];
+      const float gpp = want_gp ? from_lane(gpen, p) : 0.f;
       float gr[G_COUNT];
 #pragma unroll
       for (int f = 0; f < G_COUNT; ++f) gr[f] = 0.f;
@@ -919,7 +1110,7 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
         } else {
           quad_state<NH, NQ>(g, pp, Lp, m0p, tn, a, s);
         }
-        float4 f5 = st.f[5][j];
+        float4 f5 = st.word(5, j);
         float gbar = gap[0] * f5.y + gap[1] * f5.z + gap[2] * f5.w + gbp;
         // consistency penalty (App. E): dP/dtau at the edges (bq, scaled by the
         // pixel's dL/dP) and its direct dependence on (mu, Sigma, omega)
@@ -951,7 +1142,7 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
             gmu += tr * cs * (dm0 - dm1);
           }
         }
-        float d[K + 1];
+        float d[K + 1], gt[NQ];
 #pragma unroll
         for (int k = 0; k <= K; ++k) d[k] = 0.f;
         // (radiance + penalty) gradient at fixed moments: through tau at the
@@ -975,8 +1166,7 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
             for (int k = 1; k <= K; ++k) d[k] += wgt * gk[k];
             d[0] += wgt * s.F[e];
             const float dtau_dt = m0p * dpsi * kTrigSpan * warp_abs_d(s.t[e], tn);
-            gmu += wgt * dtau_dt * (s.cl[e] ? 0.f : 1.f);
-            gsig += wgt * dtau_dt * (s.cl[e] ? 0.f : a.kappa * a.xq[e]);
+            gt[e] = rounded(wgt * dtau_dt);
           }
         } else {
 #pragma unroll
@@ -988,65 +1178,39 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
             for (int k = 1; k <= K; ++k) d[k] += wgt * lamk[k];
             d[0] += wgt * s.F[e];  // minus sum_k b_k d[k], taken once after the edges
             float dtau_dt = -m0p * s.w0[e] * dl * warp_dy(pp, s.t[e]);
-            float dtdmu = s.cl[e] ? 0.f : 1.f;
-            float dtdsig = s.cl[e] ? 0.f : a.kappa * a.xq[e];
-            gmu += wgt * dtau_dt * dtdmu;
-            gsig += wgt * dtau_dt * dtdsig;
+            gt[e] = rounded(wgt * dtau_dt);
           }
         }
+        edge_position_grads<NH, NQ>(s, a, gt, gmu, gsig);
 #pragma unroll
         for (int k = 1; k <= K; ++k) d[0] -= bkp[k] * d[k];  // the tau = m_0 F(b) chain at b = m / m_0
-        float dq0 = 0.f, dq1 = 0.f, dq2 = 0.f;
-#pragma unroll
-        for (int e = 0; e + 1 < NQ; ++e) {
-          float cdt = s.T[e] * s.ph[e] * g.omega * s.sr[e];
-          float dmu0 = s.cl[e] ? 0.f : 1.f, dmu1 = s.cl[e + 1] ? 0.f : 1.f;
-          float dsg0 = s.cl[e] ? 0.f : a.kappa * a.xq[e], dsg1 = s.cl[e + 1] ? 0.f : a.kappa * a.xq[e + 1];
-          dq0 += cdt * (dmu1 - dmu0);
-          dq1 += cdt * (dsg1 - dsg0);
-          float cs = s.T[e] * s.dt[e] * s.ph[e];
-          if (s.cl[e]) {
-            float r = (s.t[e] - g.mu) * fast_rcp(g.sig);
-            float sj = g.omega * s.sr[e];
-            const float isg = fast_rcp(g.sig);
-            dq0 += cs * sj * r * isg;
-            dq1 += cs * sj * r * r * isg;
-          }
-          dq2 += cs * s.sr[e];
-        }
+        float dq0, dq1, dq2;
+        quad_position_grads<NH, NQ>(g, s, a, dq0, dq1, dq2);
         gmu += gbar * dq0;
         gsig += gbar * dq1;
         gom += gbar * dq2;
-        float e[RS];
+        Results<K + 1> r;
 #pragma unroll
-        for (int k = 0; k < RS; ++k) e[k] = k <= K ? d[k] : 0.f;
-        float4* r4 = reinterpret_cast<float4*>(res + lane * RS);
-#pragma unroll
-        for (int q4 = 0; q4 < RS / 4; ++q4) r4[q4] = make_float4(e[4 * q4], e[4 * q4 + 1], e[4 * q4 + 2], e[4 * q4 + 3]);
-        chain_record(gmu, gsig, gom, g, lamp, dx, dy, st.f[2][j], st.f[3][j], st.f[4][j], gr);
+        for (int k = 0; k <= K; ++k) r.v[k] = d[k];
+        r.store(res, lane);
+        chain_record(gmu, gsig, gom, g, lamp, dx, dy, st.word(2, j), st.word(3, j), st.word(4, j), gr);
         gr[G_CR] = s.q * gap[0];
         gr[G_CG] = s.q * gap[1];
         gr[G_CB] = s.q * gap[2];
       }
       __builtin_amdgcn_wave_barrier();
-      const float4* r4 = reinterpret_cast<const float4*>(res);
-      struct Slots {
-        float4 q[RS / 4];
-      };
       for_each_own(
           w.own,
           [&](int i) __attribute__((always_inline)) {
-            Slots v;
-#pragma unroll
-            for (int q4 = 0; q4 < RS / 4; ++q4) v.q[q4] = r4[i * (RS / 4) + q4];
-            return v;
+            Results<K + 1> r;
+            r.load(res, i);
+            return r;
           },
-          [&](const Slots& v) __attribute__((always_inline)) {
-            const float* f = reinterpret_cast<const float*>(v.q);
+          [&](const Results<K + 1>& r) __attribute__((always_inline)) {
 #pragma unroll
-            for (int k = 0; k <= K; ++k) dm[k] += f[k];
+            for (int k = 0; k <= K; ++k) dm[k] += r.v[k];
           });
-      reduce_to_slots<false>(w, gr, j, lane, cw, ba.partials, sk, quad);
+      reduce_to_slots<false>(w, gr, j, lane, cw, ba.partials, st, quad);
     };
     for (int b = rg.x; b < rg.y; b += kBlock) {
       int nb = min(kBlock, rg.y - b);
@@ -1071,6 +1235,13 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
     }
   }
 
+  if (!SUR && __ballot(active && mix_eps != 0.f) != 0) {
+    // (b is formed again: few pixels come here, and it is not kept through the passes)
+    if (active && mix_eps != 0.f) {
+#pragma unroll
+      for (int k = 1; k <= K; ++k) bk[k] = (float)(a.pix_mom[(size_t)k * a.n_pix + pix] / a.pix_mom[pix]);
+    }
+  }
   if (!SUR && active && mix_eps != 0.f) {
     // a degenerate pixel: the pairs took dL/db' at the mixture b' (dm[1..K]);
     // back to b through the mixture, and dm[0]'s share -sum_k b_k dL/db_k
@@ -1105,16 +1276,37 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
   }
 
   // ---- pass 3: the moment part of the Gradient stage ------------------------
+  constexpr int NV3 = K + 2 + (TRIG ? 0 : 4);  // dm, lambda, basis
+  static_assert(NV3 <= S, "pass 3 takes all values from LDS");
+  {
+    float own[NV3];
+#pragma unroll
+    for (int k = 0; k <= K; ++k) own[k] = dm[k];
+    own[K + 1] = lam;
+    if constexpr (!TRIG) {
+      own[K + 2] = pb.tc;
+      own[K + 3] = pb.p;
+      own[K + 4] = pb.p15;
+      own[K + 5] = pb.amp;
+    }
+    rows.template put<NV3>(lane, own);
+  }
   {
     auto flush = [&](const Window& w) __attribute__((always_inline)) {
       int j, p;
       const bool act = item_of(w, j, p);
-      const SlotVals prev = load_slot(w, j, ba.partials, sk, quad);
-      const PixelBasis pp = basis_of(p);
-      const float lamp = from_lane(lam, p);
-      float dmp[K + 1];
-#pragma unroll
-      for (int k = 0; k <= K; ++k) dmp[k] = from_lane(dm[k], p);
+      const SlotVals prev = load_slot(w, j, ba.partials, st, quad);
+      float pv[NV3];
+      rows.template get<NV3>(p, nullptr, pv);
+      const float* dmp = pv;
+      const float lamp = pv[K + 1];
+      PixelBasis pp;
+      if constexpr (!TRIG) {
+        pp.tc = pv[K + 2];
+        pp.p = pv[K + 3];
+        pp.p15 = pv[K + 4];
+        pp.amp = pv[K + 5];
+      }
       float gr[G_COUNT];
 #pragma unroll
       for (int f = 0; f < G_COUNT; ++f) gr[f] = 0.f;
@@ -1127,9 +1319,9 @@ __global__ __launch_bounds__(256, (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2) void
           trig_moment_grads<NH>(g, tn, dmp, gm);
         else
           moment_grads<K>(g, pp, tn, dmp, gm);
-        chain_record(gm[0], gm[1], gm[2], g, lamp, dx, dy, st.f[2][j], st.f[3][j], st.f[4][j], gr);
+        chain_record(gm[0], gm[1], gm[2], g, lamp, dx, dy, st.word(2, j), st.word(3, j), st.word(4, j), gr);
       }
-      reduce_to_slots<true>(w, gr, j, lane, cw, ba.partials, sk, quad, &prev);
+      reduce_to_slots<true>(w, gr, j, lane, cw, ba.partials, st, quad, &prev);
     };
     for (int b = rg.x; b < rg.y; b += kBlock) {
       int nb = min(kBlock, rg.y - b);

@@ -9,11 +9,13 @@ namespace mb {
 
 struct Stage {
   float4 f[kRecF4][kBlock];
+  __device__ __forceinline__ const float4& word(int k, int j) const { return f[k][j]; }
 };
 
 struct RayG {
   float mu, sig, omega;
   float id, xid, ek;  // 1 / D, X / D and exp(-X / 2D) at the pixel offset (for the adjoint)
+  float le;           // mu D
 };
 
 // ---------------------------------------------------------------------------
@@ -350,9 +352,10 @@ __device__ __forceinline__ void walk_pairs(WaveQueue& q, const uint64_t* masks, 
 }
 
 // Eqs. 4-6 for the pixel ray in the projected-mean frame (see common.h)
-__device__ __forceinline__ RayG ray_params(const Stage& st, int j, float dx, float dy, float lam) {
-  float4 f2 = st.f[2][j], f3 = st.f[3][j], f4 = st.f[4][j];
-  float w = st.f[5][j].x;
+template <class St>
+__device__ __forceinline__ RayG ray_params(const St& st, int j, float dx, float dy, float lam) {
+  float4 f2 = st.word(2, j), f3 = st.word(3, j), f4 = st.word(4, j);
+  float w = st.word(5, j).x;
   float d = f2.x + 2.f * (f2.y * dx + f2.z * dy) + f2.w * dx * dx + 2.f * f3.x * dx * dy + f3.y * dy * dy;
   float e = f3.z + f3.w * dx + f4.x * dy;
   float x = f4.y * dx * dx + 2.f * f4.z * dx * dy + f4.w * dy * dy;
@@ -361,7 +364,8 @@ __device__ __forceinline__ RayG ray_params(const Stage& st, int j, float dx, flo
   g.id = id;
   g.xid = x * id;
   g.ek = exp_neg_half(g.xid);
-  g.mu = lam * e * id;
+  g.le = lam * e;
+  g.mu = g.le * id;
   g.sig = lam * fast_rsq(d);
   g.omega = w * g.ek;
   return g;
