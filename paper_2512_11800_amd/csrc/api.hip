@@ -268,7 +268,11 @@ int build_lists(const mb_gaussians* g, const GaussWs& w, const PairWs& p, int n_
   EmitArgs ea;
   ea.rec = w.rec; ea.tbox = w.tbox; ea.offsets = w.offsets; ea.counts = w.counts;
   ea.n = g->n; ea.n_cams = n_cams; ea.tiles_x = tx; ea.tiles_y = ty; ea.full_coverage = full_coverage;
-  ea.keys = p.keys_a; ea.entry_rec = p.entry_rec;
+  uint32_t* keys[2] = {p.keys_a, p.keys_b};
+  int* vals[2] = {p.vals_a, p.vals_b};
+  const int bits = key_bits(n_keys);
+  const int split = split_heavy ? kSplitEntries : 0x7FFFFFFF;
+  ea.keys = keys[radix_passes(bits) & 1]; ea.entry_rec = p.entry_rec;
   ea.ranges = g->n > 0 ? p.ranges : nullptr;  // no emit launch without Gaussians
   ea.n_keys = n_keys;
   ea.cap = n_entries;
@@ -278,10 +282,16 @@ int build_lists(const mb_gaussians* g, const GaussWs& w, const PairWs& p, int n_
     e = launch_emit(ea, s);
   }
   if (e != hipSuccess) return hip_fail(e, "emit");
+  if (g->n > 0 && solo_lists(n_entries, n_keys)) {
+    StageTimer t(S_LISTS, s);
+    e = launch_solo_lists(ea.keys, p.entry_rec, n_entries, n_dev, n_keys, bits, split, p.vals_a, p.sorted_rec, p.ranges,
+                          p.order, s);
+    if (e != hipSuccess) return hip_fail(e, "lists");
+    return MB_OK;
+  }
   {
     StageTimer t(S_SORT, s);
-    e = launch_radix_sort(p.keys_a, p.vals_a, p.keys_b, p.vals_b, n_entries, n_dev, key_bits(n_keys), p.radix_tmp,
-                          s, true);
+    e = launch_radix_sort(keys, vals, n_entries, n_dev, bits, p.radix_tmp, s);
   }
   if (e != hipSuccess) return hip_fail(e, "sort");
   {
@@ -289,7 +299,7 @@ int build_lists(const mb_gaussians* g, const GaussWs& w, const PairWs& p, int n_
     e = launch_finish_lists(p.keys_a, p.vals_a, p.entry_rec, n_entries, n_dev, p.sorted_rec, p.ranges, n_keys,
                             ea.ranges != nullptr, s);
     if (e == hipSuccess)
-      e = launch_tile_order(p.ranges, n_keys, split_heavy ? kSplitEntries : 0x7FFFFFFF, p.order, p.order_tmp, s);
+      e = launch_tile_order(p.ranges, n_keys, split, p.order, p.order_tmp, s);
   }
   if (e != hipSuccess) return hip_fail(e, "lists");
   return MB_OK;

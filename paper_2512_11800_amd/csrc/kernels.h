@@ -85,9 +85,18 @@ hipError_t launch_scan(const int* in, int* out, int64_t n, int* tmp, int* total,
 // on the device. identity_vals: the input values are 0, 1, 2, ... and vals_a
 // is not read.
 size_t radix_tmp_ints(int64_t n);
-hipError_t launch_radix_sort(uint32_t* keys_a, int* vals_a, uint32_t* keys_b, int* vals_b,
-                             int64_t n, const int* n_dev, int bits, int* tmp, hipStream_t s,
-                             bool identity_vals = false);
+// stable LSD radix sort by the low `bits` of the keys, buffers keys[0], keys[1]
+// and vals[0], vals[1] in turn; the result is in the buffers 0, the input keys in
+// buffer radix_passes(bits) % 2 (the input values are 0, 1, 2, ...). n: the count,
+// or with n_dev the capacity the launches are sized for, the count itself on the
+// device.
+int radix_passes(int bits);
+hipError_t launch_radix_sort(uint32_t* const* keys, int* const* vals, int64_t n, const int* n_dev, int bits, int* tmp,
+                             hipStream_t s);
+// for few entries: the sort, the ranges and the block list in one launch
+bool solo_lists(int64_t n, int n_keys);
+hipError_t launch_solo_lists(const uint32_t* keys, const int* entry_rec, int64_t n, const int* n_dev, int n_keys,
+                             int bits, int split, int* vals, int* sorted_rec, int2* ranges, int* blocks, hipStream_t s);
 
 // after the sort: sorted_rec[i] = entry_rec[vals[i]], ranges[key] =
 // [first, last+1) over the sorted keys (ranges zeroed first, here unless
