@@ -96,8 +96,11 @@ __device__ __forceinline__ void add_rounded(double& acc, double m) {
 template <int K, int NQ, int MODE>
 __global__
 // waves per SIMD: five for K = 4 (0.90 ms against 0.92 ms with four, at the scene
-// above), four for K = 6 (1.62 against 1.75 ms with three)
-__launch_bounds__(256, K == 4 && MODE != kModeTrig ? 5 : (K == 6 && MODE == kModePlain ? 4 : 3))
+// above), four for K = 6 (1.62 against 1.75 ms with three) and for the
+// trigonometric K = 4 (0.54 against 0.58 ms with three, 200k Gaussians, 1280x720;
+// fused operations issue slower at an odd number of waves), three beyond, where
+// four spill (K = 8, five intervals: 0.83 against 0.86 ms)
+__launch_bounds__(256, K == 4 ? (MODE == kModeTrig ? 4 : 5) : (K == 6 && MODE == kModePlain ? 4 : 3))
 void k_render_fwd(RenderArgs a, CamSet cams) {
   constexpr int NH = K / 2;
   __shared__ Stage st;

@@ -500,7 +500,7 @@ __global__ __launch_bounds__(64 * kSoloWaves) void k_solo_order(const int2* rang
 // block for a list (or, with the count on the device, a capacity) of at most
 // kSoloItems entries and kSoloKeys tiles, as much as two buffers and the ranges
 // fill the LDS with: 17 us for 5500 entries on 64 tiles, where the eight launches
-// of the general path take 31 us. At the limit (two digits) the two are alike.
+// of the general path take 31 us. At the limits the two are alike.
 constexpr int kSoloKeys = 2048;
 __global__ __launch_bounds__(64 * kSoloWaves) void k_solo_lists(const uint32_t* keys, const int* entry_rec, int n_max,
                                                                 const int* n_dev, int n_keys, int passes, int split,
