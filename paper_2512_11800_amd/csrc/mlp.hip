@@ -442,28 +442,39 @@ __global__ __launch_bounds__(256, 3) void k_mlp_table(const MlpPacked* P, const 
 // F and its gradient dF/dx with respect to the 7 inputs for every query of
 // the render's list (for the backward pass through the surrogate): the forward
 // tile with its GELU' kept, then dZ2 = F (1 - F) w3 GELU'(Z2) (bf16) against W2
-// and dZ1 = dH1 GELU'(Z1) (bf16) as the forward's transposed products, and
-// dx = dZ1 W1 on the vector unit: the halves of the wave exchange their neurons,
-// the lower sums dx_0..2, the upper dx_3..6. out: [cap][8] = F, dF/dx_0..6.
-// Bound by vector issue, 5300 cycles per 32 queries (GELU' adds 8 fused
-// operations to each GELU, dx 256): 2277 -> 1062 us for the queries of a surrogate
-// step (960 x 540), where the activations and both layers' products passed through
-// LDS before and each GELU was evaluated twice.
+// and dZ1 = dH1 GELU'(Z1) (bf16) against W1 as the forward's transposed products;
+// W1's operand has an empty row first, so that the lower half-wave ends with
+// (0, dx_0..2) and the upper with dx_3..6. out: [cap][8] = F, dF/dx_0..6.
+// Bound by vector issue, 4360 cycles per 32 queries (GELU' adds 8 fused operations
+// to each GELU): 2277 -> 848 us for the queries of a surrogate step (960 x 540),
+// where the activations and both layers' products passed through LDS before and
+// each GELU was evaluated twice; 1062 us with dx = dZ1 W1 on the vector unit, whose
+// rounding error is 1.8 times the matrix instruction's (rms, 64 random terms).
 __global__ __launch_bounds__(256, 2) void k_mlp_input_grad_gather(const MlpPacked* P, const float* pixfeat,
                                                                const int* q_pix, const float* q_z,
                                                                const unsigned long long* q_count, int64_t q_cap,
                                                                int64_t n_pix, float* out_g) {
   __shared__ __align__(16) RowConsts c;
   __shared__ __align__(16) uint16_t w2t[kH][kH + 8];  // W2^T, rows apart in the banks
-  __shared__ __align__(16) float w1g[kH][8];  // W1 rows by neuron: 0, dx_0..2 | dx_3..6
   const unsigned long long cnt = *q_count;
   const int64_t n = cnt < (unsigned long long)q_cap ? (int64_t)cnt : q_cap;
   for (int i = threadIdx.x; i < kH * kH / 8; i += blockDim.x)
     *reinterpret_cast<bf16x8*>(&w2t[i / 8][8 * (i % 8)]) = global_bf16x8(&P->w2t[i / 8][8 * (i % 8)]);
-  for (int i = threadIdx.x; i < kH * 8; i += blockDim.x) w1g[i >> 3][i & 7] = (i & 7) ? P->w1f[(i & 7) - 1][i >> 3] : 0.f;
   stage_consts(c, P);
   const int lane = threadIdx.x & 63, lr = lane & 31, half = lane >> 5;
   const RegWeights w = load_weights(P, lane);
+  // W1^T as the A operand: row 0 empty, rows 1..7 the inputs
+  bf16x8 w1t[4];
+#pragma unroll
+  for (int kt = 0; kt < 4; ++kt) {
+    uint32_t u[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float* f = &P->w1f[lr >= 1 && lr <= kIn ? lr - 1 : 0][16 * kt + 8 * half + 2 * j];
+      u[j] = lr >= 1 && lr <= kIn ? pack_bf16(f[0], f[1]) : 0u;
+    }
+    w1t[kt] = __builtin_bit_cast(bf16x8, make_uint4(u[0], u[1], u[2], u[3]));
+  }
   const float b3 = P->b3;
   const int64_t step = (int64_t)gridDim.x * (blockDim.x >> 6) * 32;
   int64_t q0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 32;
@@ -508,31 +519,15 @@ __global__ __launch_bounds__(256, 2) void k_mlp_input_grad_gather(const MlpPacke
 #pragma unroll
       for (int kt = 0; kt < 4; ++kt) dz[m] = mfma(lds_bf16x8(&w2t[32 * m + lr][16 * kt + 8 * half]), op[kt], dz[m]);
     }
-    // dZ1 (bf16) and dx, neuron by neuron
-    float gx[4] = {0.f, 0.f, 0.f, 0.f};
+    // dZ1 (bf16), dx^T = W1^T dZ1^T
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        uint32_t a[2], b[2];  // neurons 8 g + 4 half + (0, 1), (2, 3), then those of both halves
+      for (int r = 0; r < 16; ++r) dz[m][r] *= d1[m][r];
+    column_operand(dz, op);
+    f32x16 gx = {};
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          a[j] = pack_bf16(dz[m][4 * g + 2 * j] * d1[m][4 * g + 2 * j],
-                           dz[m][4 * g + 2 * j + 1] * d1[m][4 * g + 2 * j + 1]);
-          b[j] = a[j];
-          swap_halves(a[j], b[j]);
-        }
-        const uint32_t u[4] = {a[0], a[1], b[0], b[1]};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float dzv = __uint_as_float((e & 1) ? (u[e >> 1] & 0xffff0000u) : (u[e >> 1] << 16));
-          const float4 wr = *reinterpret_cast<const float4*>(&w1g[32 * m + 8 * g + e][4 * half]);
-          gx[0] = fmaf(dzv, wr.x, gx[0]);
-          gx[1] = fmaf(dzv, wr.y, gx[1]);
-          gx[2] = fmaf(dzv, wr.z, gx[2]);
-          gx[3] = fmaf(dzv, wr.w, gx[3]);
-        }
-      }
+    for (int kt = 0; kt < 4; ++kt) gx = mfma(w1t[kt], op[kt], gx);
     const int64_t q = q0 + lr;
     if (q < n) reinterpret_cast<float4*>(out_g + q * 8)[half] = make_float4(half ? gx[0] : f, gx[1], gx[2], gx[3]);
   }
