@@ -58,7 +58,7 @@ __device__ __forceinline__ void queue_pop64(WaveQueue& q, QueueCursor& qc, int l
 __device__ __forceinline__ float from_lane(float v, int p) { return __shfl(v, p, 64); }
 
 // Work of a render block (see launch_tile_order): tile key (camera * tiles +
-// tile; n_keys for an empty block) and, for a block of a split tile, the
+// tile; n_keys or more for an empty block) and, for a block of a split tile, the
 // quadrant its four waves share (quad = -1: the whole tile, one quadrant per
 // wave).
 struct BlockWork {

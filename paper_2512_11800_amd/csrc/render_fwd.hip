@@ -93,14 +93,80 @@ __device__ __forceinline__ void add_rounded(double& acc, double m) {
   acc += m;
 }
 
-template <int K, int NQ, int MODE>
+// The wide form (WIDE), for frames of few tiles: a block takes one quadrant of a
+// tile, and its four waves evaluate the pixels' pairs four at a time, wave w the
+// pixel's pairs 4 i + w; after each step every wave adds the four results in list
+// order, so that all sums are the ordinary form's to the last bit. LDS holds a step's
+// results, V floats a pair, twice, `half` floats apart (a wave may run one step ahead).
+// eval(j, v): entry j against this lane's pixel; add(v): its share of the sums.
+// In the ordinary form a tile is one block and each quadrant one wave, and few tiles
+// leave most of the chip idle: 64 tiles of 128x128 (2000 Gaussians) 92 -> 62 us, 475
+// of 397x301 (20000) 392 -> 217 us, 1200 of 640x480 (10000 and 100000) 292 -> 258 and
+// 1774 -> 1589 us (K = 4); K = 6 and 8 gain as much or more. Where all tiles are
+// split the two are alike within 2%. Beyond, the lanes without a pair in a step cost
+// more than the waves bring: 1900 tiles 1.06 times as fast with K = 4 but 0.93 with K
+// = 8, 3072 tiles 0.99 and 0.87.
+constexpr int kWideTiles = 1200;
+
+// The wide form's blocks: the split tiles' as in the block list, then four for each
+// other tile in its order.
+struct WideWork {
+  int key, quad;
+  bool split;
+};
+__device__ __forceinline__ WideWork wide_work(const RenderArgs& a, int n_keys) {
+  const int last = a.order[render_blocks(n_keys) - 1];
+  const int ns = last < 0 ? n_keys : last - n_keys;  // split tiles
+  const int b = (int)blockIdx.x, i = (b >> 2) - ns;
+  WideWork w;
+  w.quad = b & 3;
+  w.split = i < 0;
+  w.key = w.split ? (-a.order[b] - 1) >> 2 : a.order[4 * ns + i];
+  return w;
+}
+template <int V, class Eval, class Add>
+__device__ __forceinline__ void wide_rounds(float* buf, int half, const uint64_t* masks, int b, int nb, int quad, int lane,
+                                            int wave, bool live, int& step, Eval&& eval, Add&& add) {
+  const int nc = n_chunks(nb, -1);
+  for (int c = 0; c < nc; ++c) {
+    const uint64_t word = transpose_masks(load_masks(masks, b, nb, quad, -1, c, lane), lane);
+    uint64_t m = live ? word : 0ull;
+    int left = __popcll(m);
+    for (int w = 0; w < wave; ++w) m &= m - 1;
+    while (__ballot(left > 0) != 0) {  // the same in all four waves
+      float* to = buf + (step & 1) * half;
+      if (m != 0) {
+        float v[V];
+        eval(chunk_entry(c, (int)__builtin_ctzll(m), -1), v);
+#pragma unroll
+        for (int k = 0; k < V; ++k) to[(wave * V + k) * 64 + lane] = v[k];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) m &= m - 1;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < 4; ++w)
+        if (w < left) {
+          float v[V];
+#pragma unroll
+          for (int k = 0; k < V; ++k) v[k] = to[(w * V + k) * 64 + lane];
+          add(v);
+        }
+      left -= 4;
+      ++step;
+    }
+  }
+}
+
+template <int K, int NQ, int MODE, bool WIDE = false>
 __global__
 // waves per SIMD: five for K = 4 (0.90 ms against 0.92 ms with four, at the scene
 // above), four for K = 6 (1.62 against 1.75 ms with three) and for the
 // trigonometric K = 4 (0.54 against 0.58 ms with three, 200k Gaussians, 1280x720;
 // fused operations issue slower at an odd number of waves), three beyond, where
-// four spill (K = 8, five intervals: 0.83 against 0.86 ms)
-__launch_bounds__(256, K == 4 ? (MODE == kModeTrig ? 4 : 5) : (K == 6 && MODE == kModePlain ? 4 : 3))
+// four spill (K = 8, five intervals: 0.83 against 0.86 ms). The wide form: as many
+// as its LDS and registers allow without spills.
+__launch_bounds__(256, WIDE ? (K == 4 ? 4 : (K == 6 ? 3 : 2)) : (K == 4 ? (MODE == kModeTrig ? 4 : 5) : (K == 6 && MODE == kModePlain ? 4 : 3)))
 void k_render_fwd(RenderArgs a, CamSet cams) {
   constexpr int NH = K / 2;
   __shared__ Stage st;
@@ -108,7 +174,14 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
   __shared__ int s_scan[4];
   const int tiles_per_cam = a.tiles_x * a.tiles_y;
   const int n_keys = tiles_per_cam * a.n_cams;
-  const BlockWork bw = block_work(a);
+  static_assert(!WIDE || MODE == kModePlain, "the wide form is the plain path's");
+  WideWork bw;
+  if constexpr (WIDE) {
+    bw = wide_work(a, n_keys);
+  } else {
+    const BlockWork b = block_work(a);
+    bw = {b.key, b.quad, b.quad >= 0};
+  }
   const int key = bw.key;
   if (key >= n_keys) return;
   const int ci = key / tiles_per_cam;
@@ -116,11 +189,14 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
   const int ty = tile / a.tiles_x, tx = tile - ty * a.tiles_x;
   const CamConst& c = cams.c[ci];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int2 rg = a.ranges[key];
   // the wave's 8x8 pixel block; in a split block all four waves share one
   // and each takes every fourth list entry (own4)
-  const bool split = bw.quad >= 0;
-  const int quad = split ? bw.quad : wave;
+  const bool split = bw.split;
+  const bool wide = WIDE && !split;
+  const int quad = WIDE || split ? bw.quad : wave;
   const int own4 = split ? wave : -1;
+  const bool writer = wide ? wave == 0 : own4 <= 0;  // of the pixel's sums, which all of its waves hold
   const int px = tx * kTile + (quad & 1) * 8 + (lane & 7);
   const int py = ty * kTile + (quad >> 1) * 8 + (lane >> 3);
   const bool inside = px < c.width && py < c.height;
@@ -129,22 +205,25 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
   const float rx = (u - c.cx) / c.fx, ry = (v - c.cy) / c.fy;
   const float lam = sqrtf(1.f + rx * rx + ry * ry);
   const float tn = c.tn;
-  const int2 rg = a.ranges[key];
   const size_t pix = ((size_t)ci * c.height + (inside ? py : 0)) * c.width + (inside ? px : 0);
 
+  constexpr bool kTrig = MODE == kModeTrig;
+  constexpr bool kDblMom = K >= 8 || kTrig;  // moments per pair in double
+  // a step's results in the wide form: four pairs of a pixel's moments, or of its sums of pass 2
+  constexpr int kWideHalf = 4 * 64 * (kDblMom ? 2 * (K + 1) : (K + 1 > 5 ? K + 1 : 5));
   __shared__ WaveQueue wq[4];
   __shared__ float band[kBlock];  // per staged entry: the coverage test's rounding band (cover_setup)
   // results of the queued pairs of pass 2: q (r, g, b, 1), consistency penalty
-  __shared__ __align__(16) float wres[4][5 * 64];
-  constexpr bool kTrig = MODE == kModeTrig;
-  constexpr bool kDblMom = K >= 8 || kTrig;  // moments per pair in double
+  __shared__ __align__(16) float wres[WIDE ? 1 : 4][WIDE ? 2 * kWideHalf : 5 * 64];
   WaveQueue& q = wq[wave];
-  float* res = wres[wave];
+  float* res = &wres[0][0] + wave * 5 * 64;
+  float* wbuf = &wres[0][0];  // the wide form's
   const int x0 = tx * kTile + (quad & 1) * 8, y0 = ty * kTile + (quad >> 1) * 8;
   // partial per-pixel sums of a split block's four waves, combined in wave
   // order through the (then idle) staging buffer; every wave ends with the
   // same totals
   float* xch = reinterpret_cast<float*>(&st);
+  int step = 0;
   // this lane's pixel against staged entry j
   auto ray_own = [&](int j) __attribute__((always_inline)) {
     return ray_params(st, j, u - st.f[0][j].x, v - st.f[0][j].y, lam);
@@ -168,7 +247,7 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
       if (tid < nb) band[tid] = cover_setup(st, tid, tx * kTile, ty * kTile);
       __syncthreads();
       const int nc = n_chunks(nb, own4);
-      for (int ch = 0; ch < nc; ++ch) {
+      for (int ch = wide ? wave : 0; ch < nc; ch += wide ? 4 : 1) {
         const int jl = chunk_entry(ch, lane, own4);
         const bool mine = jl < nb;
         const int jr = mine ? jl : 0;
@@ -184,6 +263,7 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
         }
         mask = mine ? mask & inside_mask : 0ull;
         if (mine) a.masks[(size_t)(b + jl) * 4 + quad] = mask;
+        if (wide) continue;
         const uint64_t word = transpose_masks(mask, lane);
         n_cov += __popcll(word);
         word_rounds(word, ch, own4, [&](int j) __attribute__((always_inline)) {
@@ -193,6 +273,24 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
           swm = fma(wgt, mu, swm);
           swq = fma(wgt, fma(mu, mu, sg * sg), swq);
         });
+      }
+      if (wide) {
+        __syncthreads();  // all of the batch's masks
+        wide_rounds<3>(
+            wbuf, kWideHalf, a.masks, b, nb, quad, lane, wave, true, step,
+            [&](int j, float* v) __attribute__((always_inline)) {
+              const RayG g = ray_own(j);
+              v[0] = g.omega * g.sig;
+              v[1] = g.mu;
+              v[2] = g.sig;
+            },
+            [&](const float* v) __attribute__((always_inline)) {
+              const double wgt = (double)v[0], mu = (double)v[1], sg = (double)v[2];
+              ++n_cov;
+              sw += wgt;
+              swm = fma(wgt, mu, swm);
+              swq = fma(wgt, fma(mu, mu, sg * sg), swq);
+            });
       }
     }
   }
@@ -242,6 +340,35 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
         load_batch_covered(st, a.rec, a.sorted_rec, a.masks, bw.quad, b, nb);
         __syncthreads();
       }
+      if (wide) {
+        if constexpr (kDblMom) {
+          wide_rounds<2 * (K + 1)>(
+              wbuf, kWideHalf, a.masks, b, nb, quad, lane, wave, true, step,
+              [&](int j, float* v) __attribute__((always_inline)) {
+                double m[K + 1];
+                particle_moments_d<K>(ray_own(j), pb, tn, m);
+#pragma unroll
+                for (int k = 0; k <= K; ++k) {
+                  v[2 * k] = __int_as_float(__double2loint(m[k]));
+                  v[2 * k + 1] = __int_as_float(__double2hiint(m[k]));
+                }
+              },
+              [&](const float* v) __attribute__((always_inline)) {
+#pragma unroll
+                for (int k = 0; k <= K; ++k)
+                  acc[k] += __hiloint2double(__float_as_int(v[2 * k + 1]), __float_as_int(v[2 * k]));
+              });
+        } else {
+          wide_rounds<K + 1>(
+              wbuf, kWideHalf, a.masks, b, nb, quad, lane, wave, true, step,
+              [&](int j, float* v) __attribute__((always_inline)) { particle_moments<K>(ray_own(j), pb, tn, v); },
+              [&](const float* v) __attribute__((always_inline)) {
+#pragma unroll
+                for (int k = 0; k <= K; ++k) acc[k] += (double)v[k];
+              });
+        }
+        continue;
+      }
       for_each_own_entry(a.masks, b, nb, quad, own4, lane, true, [&](int j) __attribute__((always_inline)) {
         const RayG g = ray_own(j);
         if constexpr (kTrig) {
@@ -279,7 +406,7 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
     }
   }
   // the backward pass starts from these sums (one column per moment)
-  if (inside && own4 <= 0) {
+  if (inside && writer) {
 #pragma unroll
     for (int k = 0; k <= K; ++k) a.pix_mom[(size_t)k * a.n_pix + pix] = acc[k];
   }
@@ -431,6 +558,29 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
         load_batch_covered(st, a.rec, a.sorted_rec, a.masks, bw.quad, b, nb);
         __syncthreads();
       }
+      if (wide) {
+        wide_rounds<5>(
+            wbuf, kWideHalf, a.masks, b, nb, quad, lane, wave, inside && live, step,
+            [&](int j, float* v) __attribute__((always_inline)) {
+              const RayG g = ray_own(j);
+              QEdges<NQ> e;
+              const float qv = particle_quadrature<NH, NQ>(g, pb, L, m0, tn, a, e);
+              const float4 f5 = st.f[5][j];
+              v[0] = qv * f5.y;
+              v[1] = qv * f5.z;
+              v[2] = qv * f5.w;
+              v[3] = qv;
+              v[4] = want_pen ? pair_penalty<NQ>(g, tn, e, a) : 0.f;
+            },
+            [&](const float* v) __attribute__((always_inline)) {
+              sr += v[0];
+              sg += v[1];
+              sb += v[2];
+              so += v[3];
+              spen += v[4];
+            });
+        continue;
+      }
       walk_pairs(q, a.masks, b, nb, quad, own4, lane, inside && live,
                  [&](bool direct, bool on, int j, int p, uint64_t own) __attribute__((always_inline)) {
         // the pixel's values: the lane's own, or those of pixel lane p
@@ -552,6 +702,7 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
     }
     if (wave != 0) return;
   }
+  if (!writer) return;
 
   // ---- epilogue: Eq. 15 ------------------------------------------------------
   if (!inside) return;
@@ -773,6 +924,19 @@ hipError_t launch_render_forward(const RenderArgs& a, const CamSet& cams, int n_
                                  hipStream_t s, int mode) {
   int n_keys = a.tiles_x * a.tiles_y * a.n_cams;
   dim3 grid(render_blocks(n_keys)), block(kBlock);
+#define MB_LAUNCH_WIDE(KK, NN)                                                                  \
+  if (wide && n_moments == KK && n_intervals == NN) {                                           \
+    hipLaunchKernelGGL((k_render_fwd<KK, NN + 1, kModePlain, true>), dim3(4 * n_keys), block, 0, s, a, cams); \
+    return hipGetLastError();                                                                   \
+  }
+  const bool wide = mode == kModePlain && n_keys <= kWideTiles;
+  MB_LAUNCH_WIDE(4, 3)
+  MB_LAUNCH_WIDE(6, 3)
+  MB_LAUNCH_WIDE(4, 5)
+  MB_LAUNCH_WIDE(6, 5)
+  MB_LAUNCH_WIDE(8, 3)
+  MB_LAUNCH_WIDE(8, 5)
+#undef MB_LAUNCH_WIDE
 #define MB_LAUNCH(KK, NN, MM)                                                       \
   if (n_moments == KK && n_intervals == NN && mode == MM) {                         \
     hipLaunchKernelGGL((k_render_fwd<KK, NN + 1, MM>), grid, block, 0, s, a, cams); \

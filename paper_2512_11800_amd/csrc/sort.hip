@@ -387,7 +387,7 @@ __global__ __launch_bounds__(256) void k_tile_keys(const int2* ranges, int n_key
 
 // Block list of the render kernels from the ordered tiles: the first ns tiles
 // (the heavy ones) get four blocks each, coded -(4 key + quadrant) - 1, then
-// one block per remaining tile (its key), then blocks coded n_keys that exit
+// one block per remaining tile (its key), then blocks coded n_keys + ns that exit
 // at once (the grid is render_blocks()).
 __global__ __launch_bounds__(256) void k_block_list(const uint32_t* sorted_keys, const int* order, int n_keys,
                                                    int* blocks) {
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(256) void k_block_list(const uint32_t* sorted_keys,
       blocks[3 * ns + t] = order[t];
     }
   } else if (t >= n_keys + 3 * ns) {
-    blocks[t] = n_keys;
+    blocks[t] = n_keys + ns;
   }
 }
 
@@ -470,7 +470,7 @@ __device__ __forceinline__ void write_block_list(int n_keys, int ns, int* blocks
         blocks[3 * ns + t] = key;
       }
     } else if (t >= n_keys + 3 * ns) {
-      blocks[t] = n_keys;
+      blocks[t] = n_keys + ns;
     }
   }
 }

@@ -53,3 +53,27 @@ def test_list_lengths_gradients_match_oracle(n, full):
         g_img[oracle.render_image(scene, cam, opts, margin_tol=tol_m, orient_eps=tol_o)["ambiguous"]] = 0.0
     gpu, _ = _gpu_grads(scene, [cam], opts, g_img)
     assert _check(gpu, oracle.render_backward(scene, cam, opts, g_img), f"walk n={n} full={full}")
+
+
+@pytest.mark.parametrize("n,w,h", [(40, 129, 130), (3000, 201, 130), (30000, 250, 260), (4000, 640, 480)])
+@pytest.mark.parametrize("k_mom,n_int", [(4, 3), (6, 3), (8, 3), (4, 5), (6, 5), (8, 5)])
+def test_few_tiles_render_as_in_a_batch(n, w, h, k_mom, n_int):
+    """A frame of few tiles shares each quadrant's pairs among a block's waves; the
+    same camera in a batch of more than 1200 tiles takes the ordinary form. Same
+    image, state, penalty and gradients to the last bit, with empty, light and heavy
+    (split) tiles, and at the rule's edge of 1200."""
+    import paper_2512_11800_amd as M
+    g = M.Gaussians.from_scene(W.uniform_scene(n, seed=n, extent=0.4, log_scale_mean=-3.0))
+    cam = W.camera_on_axis(2.0, w, h)
+    many = 1201 // (((w + 15) // 16) * ((h + 15) // 16)) + 1
+    opts = W.Options(n_moments=k_mom, n_intervals=n_int)
+    outs = []
+    for cams in ([cam], [cam] * many):
+        img, saved, st, pen = M.render_forward(g, cams, opts, penalty=True)
+        gi, gp = torch.zeros_like(img), torch.zeros_like(pen)
+        gen = torch.Generator().manual_seed(n)
+        gi[0] = torch.randn(img[0].shape, generator=gen).cuda()
+        gp[0] = 0.1 * torch.randn(pen[0].shape, generator=gen).cuda()
+        grads = M.render_backward(g, cams, opts, st, saved, gi, gp)
+        outs.append([img[0], saved[0], pen[0]] + [grads[k] for k in sorted(grads)])
+    assert all(torch.equal(x, y) for x, y in zip(*outs))
