@@ -629,25 +629,31 @@ __device__ __forceinline__ SlotVals load_slot(const Window& w, int j, const floa
 // over the lanes sums each entry's pairs and the segment's last lane writes
 // (ADD = false) or adds to (ADD = true, with the slot's earlier contents in
 // `prev`) the entry's slot. An entry that continues in the next window leaves its
-// partial sum in `carry`.
+// partial sum there, in `carry`.
 template <bool ADD>
-__device__ __forceinline__ void reduce_to_slots(const Window& w, float* gr, int j, int lane, float* carry,
-                                                float* partials, const BwdStage& st, int wave,
-                                                const SlotVals* prev = nullptr) {
+__device__ __forceinline__ void scan_window(const Window& w, float* gr) {
   // the moment part (ADD) leaves the colour fields zero: they need no scan
   const ScanMasks sm = scan_masks(segment_heads(w));
   if constexpr (ADD)
     segment_scan15(gr, sm);
   else
     segment_scan18(gr, sm);
+}
+__device__ __forceinline__ void take_carry(const Window& w, float* gr, int lane, const float* carry) {
   if (w.carried && lane == __builtin_ctzll(segment_ends(w))) {
 #pragma unroll
     for (int f = 0; f < G_COUNT; ++f) gr[f] += carry[f];
   }
+}
+__device__ __forceinline__ void leave_carry(const Window& w, const float* gr, int lane, float* carry) {
   if (w.continues && lane == 63) {
 #pragma unroll
     for (int f = 0; f < G_COUNT; ++f) carry[f] = gr[f];
   }
+}
+template <bool ADD>
+__device__ __forceinline__ void write_slots(const Window& w, float* gr, int j, float* partials, const BwdStage& st,
+                                            int wave, const SlotVals* prev = nullptr) {
   if (__builtin_amdgcn_inverse_ballot_w64(slot_lanes(w))) {
     float4* slot = reinterpret_cast<float4*>(partials + ((size_t)__float_as_int(st.word(0, j).z) * 4 + wave) * kGradStride);
     if constexpr (ADD) {
@@ -661,7 +667,91 @@ __device__ __forceinline__ void reduce_to_slots(const Window& w, float* gr, int 
     slot[3] = make_float4(gr[12], gr[13], gr[14], gr[15]);
     slot[4] = make_float4(gr[16], gr[17], 0.f, 0.f);
   }
+}
+template <bool ADD>
+__device__ __forceinline__ void reduce_to_slots(const Window& w, float* gr, int j, int lane, float* carry,
+                                                float* partials, const BwdStage& st, int wave,
+                                                const SlotVals* prev = nullptr) {
+  scan_window<ADD>(w, gr);
+  take_carry(w, gr, lane, carry);
+  leave_carry(w, gr, lane, carry);
+  write_slots<ADD>(w, gr, j, partials, st, wave, prev);
   __builtin_amdgcn_wave_barrier();
+}
+
+// The wide form, for frames of few tiles: a block takes one quadrant of a tile, and
+// the windows of its list go to its four waves in turn. Every wave queues all
+// pairs, four windows (a group) at a time, and calls flush(group). The windows are
+// the ordinary form's, and all sums keep their order: the gradients are the same bits.
+// The ordinary form leaves most of the chip idle there (as in the forward kernel):
+// 64 tiles of 128x128 (2000 Gaussians) 167 -> 98 us, 475 of 397x301 (20000) 855 ->
+// 476 us, 1200 of 640x480 (10000 and 100000) 689 -> 584 us and 4.25 -> 3.62 ms (K =
+// 4); K = 6 1088 -> 1016 us and 6.99 -> 7.05 ms there, K = 8 1841 -> 1508 us. Beyond,
+// K = 6 loses: 9.7 -> 10.8 ms at 1900 tiles (100000). Where all tiles are split the
+// two are alike within 2%.
+struct Group {
+  int n, base;         // pairs in the group, its first item in the ring of 512
+  uint64_t heads[5];   // of the four windows, entry starts only; [4] the next group's
+  uint64_t own[5];
+  __device__ __forceinline__ Window window(int k) const {  // k: wave-uniform
+    uint64_t h = 0, next = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      h = k == i ? heads[i] : h;
+      next = k == i ? heads[i + 1] : next;
+    }
+    Window w;
+    w.n = min(max(n - 64 * k, 0), 64);
+    w.base = (base + 64 * k) & 511;
+    w.carried = w.n > 0 && (h & 1) == 0;
+    w.heads = h | 1;
+    w.own = 0;
+    w.continues = n > 64 * (k + 1) && (next & 1) == 0;
+    return w;
+  }
+};
+template <bool OWN, class Flush, class Empty>
+__device__ __forceinline__ void walk_groups(uint16_t* ring, const uint64_t* masks, int b, int nb, int quad, int lane,
+                                            uint64_t keep, Flush&& flush, Empty&& on_empty) {
+  Group g = {};
+  for (int j0 = 0; j0 < nb; j0 += 64) {
+    const bool in = j0 + lane < nb;
+    const uint64_t raw = in ? masks[(size_t)(b + j0 + lane) * 4 + quad] : 0ull;
+    const uint64_t mk = raw & keep;
+    if (in && mk == 0 && raw != 0) on_empty(j0 + lane);
+    uint64_t nz = __ballot(mk != 0);
+    while (nz) {
+      const int l = __builtin_ctzll(nz);
+      nz &= nz - 1;
+      const uint32_t mlo = __builtin_amdgcn_readlane((uint32_t)mk, l);
+      const uint32_t mhi = __builtin_amdgcn_readlane((uint32_t)(mk >> 32), l);
+      const uint64_t m = ((uint64_t)mhi << 32) | mlo;
+      const bool cov = __builtin_amdgcn_inverse_ballot_w64(m);
+      const int pos = (int)__builtin_amdgcn_mbcnt_hi(mhi, __builtin_amdgcn_mbcnt_lo(mlo, (uint32_t)g.n));
+      if (cov) ring[(g.base + pos) & 511] = (uint16_t)(((j0 + l) << 6) | lane);
+      const uint64_t bit = OWN && cov ? 1ull << (pos & 63) : 0ull;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if ((g.n >> 6) == k) {  // the entry's pairs lie in windows k and k + 1
+          g.heads[k] |= 1ull << (g.n & 63);
+          if constexpr (OWN) {
+            g.own[k] |= (pos >> 6) == k ? bit : 0ull;
+            g.own[k + 1] |= (pos >> 6) == k ? 0ull : bit;
+          }
+        }
+      g.n += __builtin_popcountll(m);
+      if (g.n >= 256) {
+        flush(g);
+        g.n -= 256;
+        g.base ^= 256;
+        g.heads[0] = g.heads[4];
+        g.own[0] = g.own[4];
+#pragma unroll
+        for (int k = 1; k < 5; ++k) g.heads[k] = g.own[k] = 0;
+      }
+    }
+  }
+  if (g.n > 0) flush(g);
 }
 
 // A pixel's values for the lanes that evaluate its pairs: the first S of N in a
@@ -741,10 +831,11 @@ struct Results {
 // Eq. 14 (trig_moment_grads) in place of the power moments'.
 template <int K, int NQ, int MODE>
 constexpr int kBwdBlocks = (K <= 6 && NQ == 4 && MODE == 0) ? 3 : 2;  // blocks a compute unit
-template <int K, int NQ, int MODE>
-__global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(BwdArgs ba, CamSet cams) {
+template <int K, int NQ, int MODE, bool WIDE = false>
+__global__ __launch_bounds__(256, (WIDE ? 2 : kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(BwdArgs ba, CamSet cams) {
   constexpr bool SUR = MODE == 1;
   constexpr bool TRIG = MODE == 2;
+  static_assert(!WIDE || MODE == 0, "the wide form is the plain path's");
   static_assert(!TRIG || K == 4 || K == 6, "the trigonometric path takes two or three complex moments");
   constexpr int NH = K / 2;
   constexpr int NL = (NH + 1) * (NH + 2) / 2;
@@ -754,13 +845,20 @@ __global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(B
   const RenderArgs& a = ba.r;
   __shared__ BwdStage st;
   __shared__ WaveQueue wq[4];
+  __shared__ uint16_t ring[WIDE ? 4 : 1][WIDE ? 512 : 1];  // the wide form's queues
   __shared__ uint32_t wrank[4][SUR ? 128 : 1];           // pair ranks (surrogate queries)
-  __shared__ __align__(16) float wres[4][NRES * 64];     // per queued pair results
-  __shared__ float4 prow[4][64 * S / 4];                 // pixel values
-  __shared__ float carry[4][G_COUNT];                    // partial slot of an entry split over evaluations
+  __shared__ __align__(16) float wres[WIDE ? 8 : 4][NRES * 64];  // per queued pair results
+  __shared__ float4 prow[WIDE ? 1 : 4][64 * S / 4];      // pixel values (of the block's one quadrant: WIDE)
+  __shared__ float carry[WIDE ? 8 : 4][G_COUNT];         // partial slot of an entry split over evaluations
   const int tiles_per_cam = a.tiles_x * a.tiles_y;
   const int n_keys = tiles_per_cam * a.n_cams;
-  const BlockWork bw = block_work(a);
+  WideWork bw;
+  if constexpr (WIDE) {
+    bw = wide_work(a, n_keys);
+  } else {
+    const BlockWork b = block_work(a);
+    bw = {b.key, b.quad, b.quad >= 0};
+  }
   const int key = bw.key;
   if (key >= n_keys) return;
   const int ci = key / tiles_per_cam;
@@ -770,9 +868,11 @@ __global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(B
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // as in the forward pass: a split block's waves share one quadrant and
   // take every fourth list entry; slots and masks are per (entry, quadrant)
-  const bool split = bw.quad >= 0;
-  const int quad = split ? bw.quad : wave;
+  const bool split = bw.split;
+  const bool wide = WIDE && !split;
+  const int quad = WIDE || split ? bw.quad : wave;
   const int own4 = split ? wave : -1;
+  int par = 0;  // of the wide form's groups
   const int x0 = tx * kTile + (quad & 1) * 8, y0 = ty * kTile + (quad >> 1) * 8;
   const int px = x0 + (lane & 7);
   const int py = y0 + (lane >> 3);
@@ -785,7 +885,7 @@ __global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(B
   const size_t pix = inside ? ((size_t)ci * c.height + py) * c.width + px : 0;
   WaveQueue& q = wq[wave];
   float* res = wres[wave];
-  const PixelRows<S> rows{prow[wave]};
+  const PixelRows<S> rows{prow[WIDE ? 0 : wave]};
 
   float sv[8] = {0.f, 0.f, 0.f, 0.f, tn + 1.f, 1.f, 0.f, 0.f};
   float gi[3] = {0.f, 0.f, 0.f};
@@ -814,7 +914,7 @@ __global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(B
   // lanes get p = lane so the cross-lane reads stay uniform
   auto item_of = [&](const Window& w, int& j, int& p) __attribute__((always_inline)) {
     const bool act = lane < w.n;
-    const int it = act ? (int)q.item[w.base + lane] : lane;
+    const int it = act ? (int)(wide ? ring[wave][w.base + lane] : q.item[w.base + lane]) : lane;
     j = act ? (it >> 6) : 0;
     p = it & 63;
     return act;
@@ -1069,8 +1169,9 @@ __global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(B
   own[NV - 1] = gb;
   rows.template put<NV>(lane, own);
   {
-    auto flush = [&](const Window& w) __attribute__((always_inline)) {
-      int j, p;
+    // the window's pairs: gr their gradients, res their adjoint moments
+    auto evaluate = [&](const Window& w, int& j, float* gr, float* res) __attribute__((always_inline)) {
+      int p;
       const bool act = item_of(w, j, p);
       float pv[NV];
       rows.template get<NV>(p, own, pv);
@@ -1095,7 +1196,6 @@ __global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(B
       const float* bkp = pv + V_BK - 1;  // bkp[k], k = 1..K
       const float *gap = pv + NV - 4, gbp = pv[NV - 1];
       const float gpp = want_gp ? from_lane(gpen, p) : 0.f;
-      float gr[G_COUNT];
 #pragma unroll
       for (int f = 0; f < G_COUNT; ++f) gr[f] = 0.f;
       if (act) {
@@ -1198,9 +1298,10 @@ __global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(B
         gr[G_CG] = s.q * gap[1];
         gr[G_CB] = s.q * gap[2];
       }
-      __builtin_amdgcn_wave_barrier();
+    };
+    auto add_own = [&](uint64_t own, const float* res) __attribute__((always_inline)) {
       for_each_own(
-          w.own,
+          own,
           [&](int i) __attribute__((always_inline)) {
             Results<K + 1> r;
             r.load(res, i);
@@ -1210,12 +1311,50 @@ __global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(B
 #pragma unroll
             for (int k = 0; k <= K; ++k) dm[k] += r.v[k];
           });
+    };
+    auto flush = [&](const Window& w) __attribute__((always_inline)) {
+      int j;
+      float gr[G_COUNT];
+      evaluate(w, j, gr, res);
+      __builtin_amdgcn_wave_barrier();
+      add_own(w.own, res);
       reduce_to_slots<false>(w, gr, j, lane, cw, ba.partials, st, quad);
+    };
+    // each wave its window of the group, then the adjoint moments in window order
+    // by every wave; a sum carried into wave 0's window is the group before's
+    auto flush_group = [&](const Group& g) __attribute__((always_inline)) {
+      const Window w = g.window(wave);
+      int j = 0;
+      float gr[G_COUNT], carried[G_COUNT];
+      if (w.n > 0) {
+        evaluate(w, j, gr, wres[4 * par + wave]);
+        scan_window<false>(w, gr);
+        leave_carry(w, gr, lane, carry[4 * par + wave]);
+        if (wave == 0 && w.carried)
+#pragma unroll
+          for (int f = 0; f < G_COUNT; ++f) carried[f] = carry[4 * (par ^ 1) + 3][f];
+      }
+      __syncthreads();
+      if (w.n > 0) {
+        take_carry(w, gr, lane, wave == 0 ? carried : carry[4 * par + wave - 1]);
+        write_slots<false>(w, gr, j, ba.partials, st, quad);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (g.n > 64 * k) add_own(g.own[k], wres[4 * par + k]);
+      par ^= 1;
     };
     for (int b = rg.x; b < rg.y; b += kBlock) {
       int nb = min(kBlock, rg.y - b);
       stage(b, nb, true);
-      walk_entries<true>(q, a.masks, b, nb, quad, own4, lane, active_mask, flush, zero_slot);
+      if (wide) {
+        if constexpr (WIDE)
+          walk_groups<true>(ring[wave], a.masks, b, nb, quad, lane, active_mask, flush_group, [&](int j) {
+            if (wave == 0) zero_slot(j);
+          });
+      } else {
+        walk_entries<true>(q, a.masks, b, nb, quad, own4, lane, active_mask, flush, zero_slot);
+      }
     }
   }
 
@@ -1289,13 +1428,14 @@ __global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(B
       own[K + 4] = pb.p15;
       own[K + 5] = pb.amp;
     }
+    if constexpr (WIDE) __syncthreads();  // the rows are the four waves'
     rows.template put<NV3>(lane, own);
   }
   {
-    auto flush = [&](const Window& w) __attribute__((always_inline)) {
-      int j, p;
+    auto evaluate = [&](const Window& w, int& j, float* gr, SlotVals& prev) __attribute__((always_inline)) {
+      int p;
       const bool act = item_of(w, j, p);
-      const SlotVals prev = load_slot(w, j, ba.partials, st, quad);
+      prev = load_slot(w, j, ba.partials, st, quad);
       float pv[NV3];
       rows.template get<NV3>(p, nullptr, pv);
       const float* dmp = pv;
@@ -1307,7 +1447,6 @@ __global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(B
         pp.p15 = pv[K + 4];
         pp.amp = pv[K + 5];
       }
-      float gr[G_COUNT];
 #pragma unroll
       for (int f = 0; f < G_COUNT; ++f) gr[f] = 0.f;
       if (act) {
@@ -1321,12 +1460,43 @@ __global__ __launch_bounds__(256, (kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(B
           moment_grads<K>(g, pp, tn, dmp, gm);
         chain_record(gm[0], gm[1], gm[2], g, lamp, dx, dy, st.word(2, j), st.word(3, j), st.word(4, j), gr);
       }
+    };
+    auto flush = [&](const Window& w) __attribute__((always_inline)) {
+      int j;
+      float gr[G_COUNT];
+      SlotVals prev;
+      evaluate(w, j, gr, prev);
       reduce_to_slots<true>(w, gr, j, lane, cw, ba.partials, st, quad, &prev);
+    };
+    auto flush_group = [&](const Group& g) __attribute__((always_inline)) {
+      const Window w = g.window(wave);
+      int j = 0;
+      float gr[G_COUNT], carried[G_COUNT];
+      SlotVals prev;
+      if (w.n > 0) {
+        evaluate(w, j, gr, prev);
+        scan_window<true>(w, gr);
+        leave_carry(w, gr, lane, carry[4 * par + wave]);
+        if (wave == 0 && w.carried)
+#pragma unroll
+          for (int f = 0; f < G_COUNT; ++f) carried[f] = carry[4 * (par ^ 1) + 3][f];
+      }
+      __syncthreads();
+      if (w.n > 0) {
+        take_carry(w, gr, lane, wave == 0 ? carried : carry[4 * par + wave - 1]);
+        write_slots<true>(w, gr, j, ba.partials, st, quad, &prev);
+      }
+      par ^= 1;
     };
     for (int b = rg.x; b < rg.y; b += kBlock) {
       int nb = min(kBlock, rg.y - b);
       stage(b, nb, false);
-      walk_entries<false>(q, a.masks, b, nb, quad, own4, lane, active_mask, flush, [](int) {});
+      if (wide) {
+        if constexpr (WIDE)
+          walk_groups<false>(ring[wave], a.masks, b, nb, quad, lane, active_mask, flush_group, [](int) {});
+      } else {
+        walk_entries<false>(q, a.masks, b, nb, quad, own4, lane, active_mask, flush, [](int) {});
+      }
     }
   }
 }
@@ -1338,6 +1508,19 @@ hipError_t launch_render_backward(const RenderArgs& r, const float* saved, const
   BwdArgs ba{r, saved, grad_image, grad_penalty, sorted_k, partials, used};
   int n_keys = r.tiles_x * r.tiles_y * r.n_cams;
   dim3 grid(render_blocks(n_keys)), block(kBlock);
+#define MB_LAUNCH_WIDE(KK, NN)                                                                               \
+  if (wide && n_moments == KK && n_intervals == NN) {                                                        \
+    hipLaunchKernelGGL((k_render_bwd<KK, NN + 1, 0, true>), dim3(4 * n_keys), block, 0, s, ba, cams);        \
+    return hipGetLastError();                                                                                \
+  }
+  const bool wide = mode == 0 && n_keys <= kWideTiles;
+  MB_LAUNCH_WIDE(4, 3)
+  MB_LAUNCH_WIDE(6, 3)
+  MB_LAUNCH_WIDE(4, 5)
+  MB_LAUNCH_WIDE(6, 5)
+  MB_LAUNCH_WIDE(8, 3)
+  MB_LAUNCH_WIDE(8, 5)
+#undef MB_LAUNCH_WIDE
 #define MB_LAUNCH(KK, NN, SS)                                                          \
   if (n_moments == KK && n_intervals == NN && mode == SS) {                            \
     hipLaunchKernelGGL((k_render_bwd<KK, NN + 1, SS>), grid, block, 0, s, ba, cams); \

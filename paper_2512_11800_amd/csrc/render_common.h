@@ -78,6 +78,23 @@ __device__ __forceinline__ BlockWork block_work(const RenderArgs& a) {
   return w;
 }
 
+// The blocks of the kernels' wide form for frames of few tiles: the split tiles' as in the block list, then four for each
+// other tile in its order.
+struct WideWork {
+  int key, quad;
+  bool split;
+};
+__device__ __forceinline__ WideWork wide_work(const RenderArgs& a, int n_keys) {
+  const int last = a.order[render_blocks(n_keys) - 1];
+  const int ns = last < 0 ? n_keys : last - n_keys;  // split tiles
+  const int b = (int)blockIdx.x, i = (b >> 2) - ns;
+  WideWork w;
+  w.quad = b & 3;
+  w.split = i < 0;
+  w.key = w.split ? (-a.order[b] - 1) >> 2 : a.order[4 * ns + i];
+  return w;
+}
+
 __device__ __forceinline__ void load_batch(Stage& st, const float4* rec, const int* sorted_rec, int b, int nb) {
   int tid = threadIdx.x;
   if (tid < nb) {

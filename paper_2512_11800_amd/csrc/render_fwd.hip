@@ -106,24 +106,6 @@ __device__ __forceinline__ void add_rounded(double& acc, double m) {
 // split the two are alike within 2%. Beyond, the lanes without a pair in a step cost
 // more than the waves bring: 1900 tiles 1.06 times as fast with K = 4 but 0.93 with K
 // = 8, 3072 tiles 0.99 and 0.87.
-constexpr int kWideTiles = 1200;
-
-// The wide form's blocks: the split tiles' as in the block list, then four for each
-// other tile in its order.
-struct WideWork {
-  int key, quad;
-  bool split;
-};
-__device__ __forceinline__ WideWork wide_work(const RenderArgs& a, int n_keys) {
-  const int last = a.order[render_blocks(n_keys) - 1];
-  const int ns = last < 0 ? n_keys : last - n_keys;  // split tiles
-  const int b = (int)blockIdx.x, i = (b >> 2) - ns;
-  WideWork w;
-  w.quad = b & 3;
-  w.split = i < 0;
-  w.key = w.split ? (-a.order[b] - 1) >> 2 : a.order[4 * ns + i];
-  return w;
-}
 template <int V, class Eval, class Add>
 __device__ __forceinline__ void wide_rounds(float* buf, int half, const uint64_t* masks, int b, int nb, int quad, int lane,
                                             int wave, bool live, int& step, Eval&& eval, Add&& add) {
