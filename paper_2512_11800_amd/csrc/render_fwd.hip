@@ -450,8 +450,8 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
         // the moment bounds at the nodes y_g = mean + sd z_g
         const float dz = 2.f * kTabZ / (float)(a.tab_nodes - 1);
         float* tp = a.tab + pix * a.tab_nodes;
-        for (int g = 0; g < a.tab_nodes; ++g)
-          tp[g] = live ? orth_F<NH>(orth, fmaf(orth.l2, smu + ssig * (-kTabZ + dz * (float)g), orth.l1), a.beta) : 0.f;
+        for (int g = 0; live && g < a.tab_nodes; ++g)  // an empty pixel's table is never read
+          tp[g] = orth_F<NH>(orth, fmaf(orth.l2, smu + ssig * (-kTabZ + dz * (float)g), orth.l1), a.beta);
       }
     }
     return;
