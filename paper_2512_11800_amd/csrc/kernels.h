@@ -112,7 +112,7 @@ hipError_t launch_finish_lists(const uint32_t* keys, const int* vals, const int*
 size_t order_tmp_ints(int n_keys);
 hipError_t launch_tile_order(const int2* ranges, int n_keys, int split, int* blocks, int* tmp, hipStream_t s);
 
-// The render kernels of the plain path take their wide form up to this many tiles
+// The whole-frame render kernels take their wide form up to this many tiles
 // (see wide_rounds and walk_groups).
 constexpr int kWideTiles = 1200;
 

@@ -688,7 +688,8 @@ __device__ __forceinline__ void reduce_to_slots(const Window& w, float* gr, int 
 // 476 us, 1200 of 640x480 (10000 and 100000) 689 -> 584 us and 4.25 -> 3.62 ms (K =
 // 4); K = 6 1088 -> 1016 us and 6.99 -> 7.05 ms there, K = 8 1841 -> 1508 us. Beyond,
 // K = 6 loses: 9.7 -> 10.8 ms at 1900 tiles (100000). Where all tiles are split the
-// two are alike within 2%.
+// two are alike within 2%. Trigonometric K = 4: 296 -> 139 us and 1.60 -> 0.86 ms at
+// 64 and 475 tiles, 9.14 -> 7.91 ms at 1200 (100000).
 struct Group {
   int n, base;         // pairs in the group, its first item in the ring of 512
   uint64_t heads[5];   // of the four windows, entry starts only; [4] the next group's
@@ -835,7 +836,7 @@ template <int K, int NQ, int MODE, bool WIDE = false>
 __global__ __launch_bounds__(256, (WIDE ? 2 : kBwdBlocks<K, NQ, MODE>)) void k_render_bwd(BwdArgs ba, CamSet cams) {
   constexpr bool SUR = MODE == 1;
   constexpr bool TRIG = MODE == 2;
-  static_assert(!WIDE || MODE == 0, "the wide form is the plain path's");
+  static_assert(!WIDE || !SUR, "the wide form is that of the whole adjoint");
   static_assert(!TRIG || K == 4 || K == 6, "the trigonometric path takes two or three complex moments");
   constexpr int NH = K / 2;
   constexpr int NL = (NH + 1) * (NH + 2) / 2;
@@ -1508,18 +1509,22 @@ hipError_t launch_render_backward(const RenderArgs& r, const float* saved, const
   BwdArgs ba{r, saved, grad_image, grad_penalty, sorted_k, partials, used};
   int n_keys = r.tiles_x * r.tiles_y * r.n_cams;
   dim3 grid(render_blocks(n_keys)), block(kBlock);
-#define MB_LAUNCH_WIDE(KK, NN)                                                                               \
-  if (wide && n_moments == KK && n_intervals == NN) {                                                        \
-    hipLaunchKernelGGL((k_render_bwd<KK, NN + 1, 0, true>), dim3(4 * n_keys), block, 0, s, ba, cams);        \
+#define MB_LAUNCH_WIDE(KK, NN, SS)                                                                           \
+  if (wide && n_moments == KK && n_intervals == NN && mode == SS) {                                          \
+    hipLaunchKernelGGL((k_render_bwd<KK, NN + 1, SS, true>), dim3(4 * n_keys), block, 0, s, ba, cams);       \
     return hipGetLastError();                                                                                \
   }
-  const bool wide = mode == 0 && n_keys <= kWideTiles;
-  MB_LAUNCH_WIDE(4, 3)
-  MB_LAUNCH_WIDE(6, 3)
-  MB_LAUNCH_WIDE(4, 5)
-  MB_LAUNCH_WIDE(6, 5)
-  MB_LAUNCH_WIDE(8, 3)
-  MB_LAUNCH_WIDE(8, 5)
+  // (not the trigonometric K = 6, whose sums follow the compiler's choice of fused
+  // operations in the last bit)
+  const bool wide = n_keys <= kWideTiles;
+  MB_LAUNCH_WIDE(4, 3, 0)
+  MB_LAUNCH_WIDE(6, 3, 0)
+  MB_LAUNCH_WIDE(4, 5, 0)
+  MB_LAUNCH_WIDE(6, 5, 0)
+  MB_LAUNCH_WIDE(8, 3, 0)
+  MB_LAUNCH_WIDE(8, 5, 0)
+  MB_LAUNCH_WIDE(4, 3, 2)
+  MB_LAUNCH_WIDE(4, 5, 2)
 #undef MB_LAUNCH_WIDE
 #define MB_LAUNCH(KK, NN, SS)                                                          \
   if (n_moments == KK && n_intervals == NN && mode == SS) {                            \

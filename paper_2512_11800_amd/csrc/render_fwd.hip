@@ -105,7 +105,8 @@ __device__ __forceinline__ void add_rounded(double& acc, double m) {
 // 1774 -> 1589 us (K = 4); K = 6 and 8 gain as much or more. Where all tiles are
 // split the two are alike within 2%. Beyond, the lanes without a pair in a step cost
 // more than the waves bring: 1900 tiles 1.06 times as fast with K = 4 but 0.93 with K
-// = 8, 3072 tiles 0.99 and 0.87.
+// = 8, 3072 tiles 0.99 and 0.87. Trigonometric K = 4: 217 -> 112 us at 64 tiles, 1.07
+// -> 0.54 ms at 475, 4.56 -> 4.06 ms at 1200 (100000).
 template <int V, class Eval, class Add>
 __device__ __forceinline__ void wide_rounds(float* buf, int half, const uint64_t* masks, int b, int nb, int quad, int lane,
                                             int wave, bool live, int& step, Eval&& eval, Add&& add) {
@@ -148,7 +149,7 @@ __global__
 // fused operations issue slower at an odd number of waves), three beyond, where
 // four spill (K = 8, five intervals: 0.83 against 0.86 ms). The wide form: as many
 // as its LDS and registers allow without spills.
-__launch_bounds__(256, WIDE ? (K == 4 ? 4 : (K == 6 ? 3 : 2)) : (K == 4 ? (MODE == kModeTrig ? 4 : 5) : (K == 6 && MODE == kModePlain ? 4 : 3)))
+__launch_bounds__(256, WIDE ? (MODE == kModeTrig ? 2 : (K == 4 ? 4 : (K == 6 ? 3 : 2))) : (K == 4 ? (MODE == kModeTrig ? 4 : 5) : (K == 6 && MODE == kModePlain ? 4 : 3)))
 void k_render_fwd(RenderArgs a, CamSet cams) {
   constexpr int NH = K / 2;
   __shared__ Stage st;
@@ -156,7 +157,7 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
   __shared__ int s_scan[4];
   const int tiles_per_cam = a.tiles_x * a.tiles_y;
   const int n_keys = tiles_per_cam * a.n_cams;
-  static_assert(!WIDE || MODE == kModePlain, "the wide form is the plain path's");
+  static_assert(!WIDE || MODE == kModePlain || MODE == kModeTrig, "the wide form is that of the whole render");
   WideWork bw;
   if constexpr (WIDE) {
     bw = wide_work(a, n_keys);
@@ -328,7 +329,10 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
               wbuf, kWideHalf, a.masks, b, nb, quad, lane, wave, true, step,
               [&](int j, float* v) __attribute__((always_inline)) {
                 double m[K + 1];
-                particle_moments_d<K>(ray_own(j), pb, tn, m);
+                if constexpr (kTrig)
+                  particle_trig_moments_d<NH>(ray_own(j), tn, m);
+                else
+                  particle_moments_d<K>(ray_own(j), pb, tn, m);
 #pragma unroll
                 for (int k = 0; k <= K; ++k) {
                   v[2 * k] = __int_as_float(__double2loint(m[k]));
@@ -546,7 +550,11 @@ void k_render_fwd(RenderArgs a, CamSet cams) {
             [&](int j, float* v) __attribute__((always_inline)) {
               const RayG g = ray_own(j);
               QEdges<NQ> e;
-              const float qv = particle_quadrature<NH, NQ>(g, pb, L, m0, tn, a, e);
+              float qv;
+              if constexpr (kTrig)
+                qv = particle_quadrature_trig<NH, NQ>(g, TL, m0, tn, a, e);
+              else
+                qv = particle_quadrature<NH, NQ>(g, pb, L, m0, tn, a, e);
               const float4 f5 = st.f[5][j];
               v[0] = qv * f5.y;
               v[1] = qv * f5.z;
@@ -906,18 +914,22 @@ hipError_t launch_render_forward(const RenderArgs& a, const CamSet& cams, int n_
                                  hipStream_t s, int mode) {
   int n_keys = a.tiles_x * a.tiles_y * a.n_cams;
   dim3 grid(render_blocks(n_keys)), block(kBlock);
-#define MB_LAUNCH_WIDE(KK, NN)                                                                  \
-  if (wide && n_moments == KK && n_intervals == NN) {                                           \
-    hipLaunchKernelGGL((k_render_fwd<KK, NN + 1, kModePlain, true>), dim3(4 * n_keys), block, 0, s, a, cams); \
-    return hipGetLastError();                                                                   \
+#define MB_LAUNCH_WIDE(KK, NN, MM)                                                                           \
+  if (wide && n_moments == KK && n_intervals == NN && mode == MM) {                                          \
+    hipLaunchKernelGGL((k_render_fwd<KK, NN + 1, MM, true>), dim3(4 * n_keys), block, 0, s, a, cams);        \
+    return hipGetLastError();                                                                                \
   }
-  const bool wide = mode == kModePlain && n_keys <= kWideTiles;
-  MB_LAUNCH_WIDE(4, 3)
-  MB_LAUNCH_WIDE(6, 3)
-  MB_LAUNCH_WIDE(4, 5)
-  MB_LAUNCH_WIDE(6, 5)
-  MB_LAUNCH_WIDE(8, 3)
-  MB_LAUNCH_WIDE(8, 5)
+  // (not the trigonometric K = 6, whose sums follow the compiler's choice of fused
+  // operations in the last bit)
+  const bool wide = n_keys <= kWideTiles;
+  MB_LAUNCH_WIDE(4, 3, kModePlain)
+  MB_LAUNCH_WIDE(6, 3, kModePlain)
+  MB_LAUNCH_WIDE(4, 5, kModePlain)
+  MB_LAUNCH_WIDE(6, 5, kModePlain)
+  MB_LAUNCH_WIDE(8, 3, kModePlain)
+  MB_LAUNCH_WIDE(8, 5, kModePlain)
+  MB_LAUNCH_WIDE(4, 3, kModeTrig)
+  MB_LAUNCH_WIDE(4, 5, kModeTrig)
 #undef MB_LAUNCH_WIDE
 #define MB_LAUNCH(KK, NN, MM)                                                       \
   if (n_moments == KK && n_intervals == NN && mode == MM) {                         \

@@ -56,8 +56,9 @@ def test_list_lengths_gradients_match_oracle(n, full):
 
 
 @pytest.mark.parametrize("n,w,h", [(40, 129, 130), (3000, 201, 130), (30000, 250, 260), (4000, 640, 480)])
-@pytest.mark.parametrize("k_mom,n_int", [(4, 3), (6, 3), (8, 3), (4, 5), (6, 5), (8, 5)])
-def test_few_tiles_render_as_in_a_batch(n, w, h, k_mom, n_int):
+@pytest.mark.parametrize("k_mom,n_int,basis", [(k, i, "power") for k in (4, 6, 8) for i in (3, 5)]
+                         + [(k, i, "trigonometric") for k in (4, 6) for i in (3, 5)])
+def test_few_tiles_render_as_in_a_batch(n, w, h, k_mom, n_int, basis):
     """A frame of few tiles shares each quadrant's pairs among a block's waves; the
     same camera in a batch of more than 1200 tiles takes the ordinary form. Same
     image, state, penalty and gradients to the last bit, with empty, light and heavy
@@ -66,7 +67,7 @@ def test_few_tiles_render_as_in_a_batch(n, w, h, k_mom, n_int):
     g = M.Gaussians.from_scene(W.uniform_scene(n, seed=n, extent=0.4, log_scale_mean=-3.0))
     cam = W.camera_on_axis(2.0, w, h)
     many = 1201 // (((w + 15) // 16) * ((h + 15) // 16)) + 1
-    opts = W.Options(n_moments=k_mom, n_intervals=n_int)
+    opts = W.Options(n_moments=k_mom, n_intervals=n_int, basis=basis)
     outs = []
     for cams in ([cam], [cam] * many):
         img, saved, st, pen = M.render_forward(g, cams, opts, penalty=True)
