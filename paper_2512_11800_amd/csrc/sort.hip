@@ -432,9 +432,14 @@ __device__ __forceinline__ void solo_pass(int n, int (*cnt)[256], int* first, in
   rank_digits<kSoloRounds>(i0, i1, cnt[wave], place,
                            [&](int, int64_t i) __attribute__((always_inline)) { return digit((int)i); });
   __syncthreads();
-  int tot = 0;
-  if (tid < 256)
-    for (int w = 0; w < kSoloWaves; ++w) tot += cnt[w][tid];
+  int c[kSoloWaves], tot = 0;
+  if (tid < 256) {
+#pragma unroll
+    for (int w = 0; w < kSoloWaves; ++w) {
+      c[w] = cnt[w][tid];
+      tot += c[w];
+    }
+  }
   const int inc = wave_inclusive_sum(tot);
   if (tid < 256 && lane == 63) lds4[wave] = inc;
   __syncthreads();
@@ -442,10 +447,10 @@ __device__ __forceinline__ void solo_pass(int n, int (*cnt)[256], int* first, in
     int off = inc - tot;
     for (int w = 0; w < wave; ++w) off += lds4[w];
     first[tid] = off;
+#pragma unroll
     for (int w = 0; w < kSoloWaves; ++w) {
-      const int c = cnt[w][tid];
       cnt[w][tid] = off;
-      off += c;
+      off += c[w];
     }
   }
   __syncthreads();
@@ -455,6 +460,21 @@ __device__ __forceinline__ void solo_pass(int n, int (*cnt)[256], int* first, in
     if (i < i1) out(i, cnt[wave][place[r] >> 16] + (int)(place[r] & 0xffffu));
   }
   __syncthreads();
+}
+
+// load(i) for the items [0, n), then store(i, value), by the whole block: eight
+// loads of a thread in flight, for one block has nothing else to hide them behind
+template <class Load, class Store>
+__device__ __forceinline__ void solo_copy(int n, Load&& load, Store&& store) {
+  constexpr int kThreads = 64 * kSoloWaves, kFlight = 8;
+  for (int i0 = threadIdx.x; i0 < n; i0 += kFlight * kThreads) {
+    decltype(load(0)) v[kFlight];
+#pragma unroll
+    for (int k = 0; k < kFlight; ++k) v[k] = load(min(i0 + k * kThreads, n - 1));
+#pragma unroll
+    for (int k = 0; k < kFlight; ++k)
+      if (i0 + k * kThreads < n) store(i0 + k * kThreads, v[k]);
+  }
 }
 
 // the block list (see k_block_list) from tile t's order, by the whole block
@@ -476,7 +496,7 @@ __device__ __forceinline__ void write_block_list(int n_keys, int ns, int* blocks
 }
 
 // k_tile_keys, the sort and k_block_list in one block for at most kSoloItems
-// tiles, which 14 bits of LDS order hold: 15 us for the 8160 tiles of 1920x1080, 8
+// tiles, which 14 bits of LDS order hold: 14 us for the 8160 tiles of 1920x1080, 8
 // us for the 3024 of 1003x757, where the six launches take 25 and 20 us.
 __global__ __launch_bounds__(64 * kSoloWaves) void k_solo_order(const int2* ranges, int n_keys, int split,
                                                                 int* blocks) {
@@ -485,10 +505,9 @@ __global__ __launch_bounds__(64 * kSoloWaves) void k_solo_order(const int2* rang
   __shared__ int lds4[4];
   __shared__ uint8_t keys[kSoloItems];
   __shared__ uint16_t order[kSoloItems];
-  for (int i = threadIdx.x; i < n_keys; i += blockDim.x) {
-    const int2 r = ranges[i];
-    keys[i] = (uint8_t)tile_key(max(r.y - r.x, 0), split);
-  }
+  solo_copy(
+      n_keys, [&](int i) __attribute__((always_inline)) { return ranges[i]; },
+      [&](int i, int2 r) __attribute__((always_inline)) { keys[i] = (uint8_t)tile_key(max(r.y - r.x, 0), split); });
   __syncthreads();
   solo_pass(
       n_keys, cnt, first, lds4, [&](int i) __attribute__((always_inline)) { return (uint32_t)keys[i]; },
@@ -499,7 +518,7 @@ __global__ __launch_bounds__(64 * kSoloWaves) void k_solo_order(const int2* rang
 // The sort of the emitted entries, the per-tile ranges and the block list in one
 // block for a list (or, with the count on the device, a capacity) of at most
 // kSoloItems entries and kSoloKeys tiles, as much as two buffers and the ranges
-// fill the LDS with: 17 us for 5500 entries on 64 tiles, where the eight launches
+// fill the LDS with: 16 us for 5500 entries on 64 tiles, where the eight launches
 // of the general path take 31 us. At the limits the two are alike.
 constexpr int kSoloKeys = 2048;
 __global__ __launch_bounds__(64 * kSoloWaves) void k_solo_lists(const uint32_t* keys, const int* entry_rec, int n_max,
@@ -512,7 +531,9 @@ __global__ __launch_bounds__(64 * kSoloWaves) void k_solo_lists(const uint32_t* 
   __shared__ int lds4[4];
   __shared__ uint32_t buf[2][kSoloItems];  // key << 16 | entry
   __shared__ uint16_t beg[kSoloKeys], end[kSoloKeys];
-  for (int i = threadIdx.x; i < n; i += blockDim.x) buf[0][i] = (keys[i] << 16) | (uint32_t)i;
+  solo_copy(
+      n, [&](int i) __attribute__((always_inline)) { return keys[i]; },
+      [&](int i, uint32_t key) __attribute__((always_inline)) { buf[0][i] = (key << 16) | (uint32_t)i; });
   for (int t = threadIdx.x; t < n_keys; t += blockDim.x) beg[t] = end[t] = 0;
   __syncthreads();
   for (int p = 0; p < passes; ++p) {
@@ -523,14 +544,15 @@ __global__ __launch_bounds__(64 * kSoloWaves) void k_solo_lists(const uint32_t* 
         [&](int i, int pos) __attribute__((always_inline)) { to[pos] = in[i]; });
   }
   const uint32_t* sorted = buf[passes & 1];
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const uint32_t e = sorted[i], key = e >> 16;
-    const int v = (int)(e & 0xffffu);
-    vals[i] = v;
-    sorted_rec[i] = entry_rec[v];
-    if (i == 0 || (sorted[i - 1] >> 16) != key) beg[key] = (uint16_t)i;
-    if (i == n - 1 || (sorted[i + 1] >> 16) != key) end[key] = (uint16_t)(i + 1);
-  }
+  solo_copy(
+      n, [&](int i) __attribute__((always_inline)) { return entry_rec[sorted[i] & 0xffffu]; },
+      [&](int i, int rec) __attribute__((always_inline)) {
+        const uint32_t e = sorted[i], key = e >> 16;
+        vals[i] = (int)(e & 0xffffu);
+        sorted_rec[i] = rec;
+        if (i == 0 || (sorted[i - 1] >> 16) != key) beg[key] = (uint16_t)i;
+        if (i == n - 1 || (sorted[i + 1] >> 16) != key) end[key] = (uint16_t)(i + 1);
+      });
   __syncthreads();
   uint32_t* order = buf[(passes & 1) ^ 1];
   for (int t = threadIdx.x; t < n_keys; t += blockDim.x) ranges[t] = make_int2(beg[t], end[t]);
