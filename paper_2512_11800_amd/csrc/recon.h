@@ -198,86 +198,6 @@ __device__ __forceinline__ void roots4(const float* c, float* x) {
   for (int i = 0; i < 3; ++i) x[i + 1] = quartic_newton(c, x3[i], 2);
 }
 
-// roots3 in two steps: roots3_raw leaves x[1] and x[2] for the Newton steps (polish3; not where the
-// degree dropped, returned true).
-__device__ __forceinline__ bool roots3_raw(const float* c, float* x) {
-  float scale = fabsf(c[0]) + fabsf(c[1]) + fabsf(c[2]) + fabsf(c[3]);
-  if (!(fabsf(c[3]) > 1e-12f * scale)) {
-    // degree drop: one atom at infinity (zero weight)
-    roots2(c, x);
-    x[2] = copysignf(1e30f, -c[2] * c[3]);
-    return true;
-  }
-  float inv = fast_rcp(c[3]);
-  float a = c[2] * inv, b = c[1] * inv, cc = c[0] * inv;
-  float a3 = a * (1.f / 3.f);
-  float q = a3 * a3 - b * (1.f / 3.f);
-  float r = a3 * a3 * a3 - 0.5f * a3 * b + 0.5f * cc;
-  q = fmaxf(q, 0.f);
-  float sq = fast_sqrt(q);
-  float den = q * sq;
-  float arg = den > 0.f ? fminf(fmaxf(r * fast_rcp(den), -1.f), 1.f) : 0.f;
-  // the trigonometric roots only seed the Newton steps below, so a short
-  // arccosine (Abramowitz & Stegun 4.4.45, |error| < 7e-5) and the hardware
-  // cosine are accurate enough
-  const float aa = fabsf(arg);
-  float ac = fast_sqrt(1.f - aa) * (1.5707288f + aa * (-0.2121144f + aa * (0.0742610f + aa * -0.0187293f)));
-  ac = arg < 0.f ? 3.14159265358979f - ac : ac;
-  float th = ac * (1.f / 3.f);
-  const float two_pi_3 = 2.0943951023931953f;
-  float big = 0.f;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    float xk = -2.f * sq * __cosf(th + two_pi_3 * (float)k) - a3;
-    big = fabsf(xk) > fabsf(big) ? xk : big;
-  }
-  big = cubic_newton(c, big, 2);
-  // p(x) = (x - big)(A x^2 + B x + C), matched from the constant term up
-  float ib = fast_rcp(big);
-  float cq = -c[0] * ib;
-  float bq = (cq - c[1]) * ib;
-  float aq = (bq - c[2]) * ib;
-  float qc[3] = {cq, bq, aq};
-  float x2[2];
-  roots2(qc, x2);
-  x[0] = big;
-  x[1] = x2[0];
-  x[2] = x2[1];
-  return false;
-}
-__device__ __forceinline__ float polish3(const float* c, float x) { return cubic_newton(c, x, 2); }
-// roots4 likewise: roots4_raw leaves x[1..3] for the steps on the quartic (polish4; not where the
-// degree dropped, returned true).
-__device__ __forceinline__ bool roots4_raw(const float* c, float* x) {
-  float scale = fabsf(c[0]) + fabsf(c[1]) + fabsf(c[2]) + fabsf(c[3]) + fabsf(c[4]);
-  if (!(fabsf(c[4]) > 1e-12f * scale)) {
-    roots3(c, x);
-    x[3] = copysignf(1e30f, -c[3] * c[4]);
-    return true;
-  }
-  float inv = fast_rcp(c[4]);
-  float a[4] = {c[0] * inv, c[1] * inv, c[2] * inv, c[3] * inv};
-  float mean = -0.25f * a[3];
-  float var = fmaxf(0.25f * (a[3] * a[3] - 2.f * a[2]) - mean * mean, 0.f);
-  float half = fast_sqrt(3.f * var) * 1.0001f + 1e-6f * (fabsf(mean) + 1.f);
-  float hi = laguerre4(a, mean + half, 4);
-  float lo = laguerre4(a, mean - half, 4);
-  float big = quartic_newton(c, fabsf(hi) >= fabsf(lo) ? hi : lo, 1);
-  // p(x) = (x - big)(A x^3 + B x^2 + C x + D), matched from the constant term up
-  float ib = fast_rcp(big);
-  float d = -c[0] * ib;
-  float cc = (d - c[1]) * ib;
-  float b = (cc - c[2]) * ib;
-  float aa = (b - c[3]) * ib;
-  float qc[4] = {d, cc, b, aa};
-  float x3[3];
-  roots3(qc, x3);
-  x[0] = big;
-#pragma unroll
-  for (int i = 0; i < 3; ++i) x[i + 1] = x3[i];
-  return false;
-}
-__device__ __forceinline__ float polish4(const float* c, float x) { return quartic_newton(c, x, 2); }
 template <int NH>
 __device__ __forceinline__ void kernel_roots(const float* c, float* x) {
   static_assert(NH >= 2 && NH <= 4, "two to four atoms besides the query");
@@ -287,21 +207,6 @@ __device__ __forceinline__ void kernel_roots(const float* c, float* x) {
     roots3(c, x);
   else
     roots4(c, x);
-}
-
-// x[0..3] sorted: the smallest two and the largest
-__device__ __forceinline__ void sort4(const float* x, float& s0, float& s1, float& s3) {
-  s0 = fminf(x[0], x[1]);
-  s1 = fmaxf(x[0], x[1]);
-  float s2 = fminf(x[2], x[3]);
-  s3 = fmaxf(x[2], x[3]);
-  float t = fminf(s0, s2);
-  s2 = fmaxf(s0, s2);
-  s0 = t;
-  t = fmaxf(s1, s3);
-  s1 = fminf(s1, s3);
-  s3 = t;
-  s1 = fminf(s1, s2);
 }
 
 // sum_{x_i < y} w_i from the count of atoms below y: the weights of the
@@ -332,8 +237,18 @@ __device__ __forceinline__ float mass_below(const LInv<NH>& L, float y, float w0
     const float ws = weight(cnt <= 1 ? lo : hi);
     return cnt == 0 ? 0.f : (cnt == 1 ? ws : (cnt == 2 ? 1.f - w0 - ws : 1.f - w0));
   } else {
-    float s0, s1, s3;
-    sort4(x, s0, s1, s3);
+    // sorting network: s0 <= s1 <= s2 <= s3
+    float s0 = fminf(x[0], x[1]), s1 = fmaxf(x[0], x[1]);
+    float s2 = fminf(x[2], x[3]), s3 = fmaxf(x[2], x[3]);
+    float t = fminf(s0, s2);
+    s2 = fmaxf(s0, s2);
+    s0 = t;
+    t = fmaxf(s1, s3);
+    s1 = fminf(s1, s3);
+    s3 = t;
+    t = fminf(s1, s2);
+    s2 = fmaxf(s1, s2);
+    s1 = t;
     const float wa = weight(cnt <= 2 ? s0 : s3);
     const float wb = weight(s1);
     return cnt == 0 ? 0.f
@@ -341,71 +256,20 @@ __device__ __forceinline__ float mass_below(const LInv<NH>& L, float y, float w0
   }
 }
 
-// Normalised interpolated bound F(y) = sum_{x_i<y} w_i + beta w_0. The value is
-// canon_at's to the last bit (the backward pass forms the same optical depths
-// again), but only the atom whose weight enters is finished: the others' last
-// Newton steps, and for NH = 2 the other zero and the comparisons, are left out
-// (K(y, y) > 0, so the two atoms lie on either side of y exactly when the
-// leading coefficient is negative, else both on the side of their mean).
+// Normalised interpolated bound F(y) = sum_{x_i<y} w_i + beta w_0, canon_at's F to
+// the last bit: the backward pass forms the forward's optical depths again, so an
+// atom is counted, and its weight taken, after the same Newton steps.
 template <int NH>
 __device__ __forceinline__ float bound_F(const LInv<NH>& L, float y, float beta) {
-  float z[NH + 1], c[NH + 1];
+  float z[NH + 1], c[NH + 1], x[NH];
   linv_apply<NH>(L, y, z);
   float zz = z[0] * z[0];
 #pragma unroll
   for (int i = 1; i <= NH; ++i) zz = fmaf(z[i], z[i], zz);
   const float w0 = fast_rcp(zz);
   linv_t_apply<NH>(L, z, c);
-  // a weight lies in [0, 1] (the first polynomial is 1); the clamp, an output
-  // modifier of the reciprocal, also turns the NaN of an atom at infinity into 0
-  auto weight = [&](float xs) __attribute__((always_inline)) {
-    return __builtin_amdgcn_fmed3f(christoffel<NH>(L, xs), 0.f, 1.f);
-  };
-  float mass;
-  if constexpr (NH == 2) {
-    // where the zeros enclose y they are apart, and the discriminant is positive
-    const float sq = fast_sqrt(c[1] * c[1] - 4.f * c[2] * c[0]);
-    const float q = -0.5f * (c[1] + copysignf(sq, c[1]));
-    const bool pos = c[1] >= 0.f;
-    const float lo = (pos ? c[0] : q) * fast_rcp(pos ? q : c[2]);  // the lower zero where c2 < 0
-    const float ws = weight(lo);
-    const float all = fmaf(2.f * c[2], y, c[1]) > 0.f ? 1.f - w0 : 0.f;
-    mass = c[2] < 0.f ? ws : all;
-  } else if constexpr (NH == 3) {
-    float x[3];
-    const bool drop = roots3_raw(c, x);
-    int cnt = 0;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      x[i] = x[i] == x[i] ? x[i] : 1e30f;
-      cnt += x[i] < y ? 1 : 0;
-    }
-    float xs = cnt <= 1 ? fminf(fminf(x[0], x[1]), x[2]) : fmaxf(fmaxf(x[0], x[1]), x[2]);
-    const float xp = polish3(c, xs);
-    xs = drop || xs == x[0] ? xs : xp;
-    const float ws = weight(xs);
-    mass = cnt == 0 ? 0.f : (cnt == 1 ? ws : (cnt == 2 ? 1.f - w0 - ws : 1.f - w0));
-  } else {
-    float x[4];
-    const bool drop = roots4_raw(c, x);
-    const float big = x[0];
-    int cnt = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x[i] = x[i] == x[i] ? x[i] : 1e30f;
-      cnt += x[i] < y ? 1 : 0;
-    }
-    float s0, s1, s3;
-    sort4(x, s0, s1, s3);
-    float xa = cnt <= 2 ? s0 : s3;
-    const float xap = polish4(c, xa), xbp = polish4(c, s1);
-    xa = drop || xa == big ? xa : xap;
-    s1 = drop || s1 == big ? s1 : xbp;
-    const float wa = weight(xa), wb = weight(s1);
-    mass = cnt == 0 ? 0.f
-                    : (cnt == 1 ? wa : (cnt == 2 ? wa + wb : (cnt == 3 ? 1.f - w0 - wa : 1.f - w0)));
-  }
-  return mass + beta * w0;
+  kernel_roots<NH>(c, x);
+  return mass_below<NH>(L, y, w0, x) + beta * w0;
 }
 
 // Canonical representation at y with its atoms (for the adjoint): returns F
