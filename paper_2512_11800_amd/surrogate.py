@@ -48,23 +48,18 @@ def mlp_forward(packed: torch.Tensor, x: torch.Tensor) -> torch.Tensor:
     return out
 
 
-class _Ws:
-    buf: Optional[torch.Tensor] = None
-
-
 def mlp_loss_grad(packed: torch.Tensor, x: torch.Tensor, t_target: torch.Tensor):
     """(loss [1], grad [P]) of mean (exp(-m0 F) - t)^2."""
     lib = L.load()
     x = x.to(torch.float32).contiguous()
     t_target = t_target.to(torch.float32).contiguous()
     n = x.shape[0]
-    need = int(lib.mb_mlp_workspace_bytes(n))
-    if _Ws.buf is None or _Ws.buf.numel() < need or _Ws.buf.device != x.device:
-        _Ws.buf = torch.empty(need, dtype=torch.uint8, device=x.device)
+    # the call's own: fits on other streams or threads write theirs at the same time
+    ws = torch.empty(int(lib.mb_mlp_workspace_bytes(n)), dtype=torch.uint8, device=x.device)
     grad = torch.empty(param_count(), dtype=torch.float32, device=x.device)
     loss = torch.empty(1, dtype=torch.float32, device=x.device)
     L.check(lib.mb_mlp_loss_grad(_ptr(packed), _ptr(x), _ptr(t_target), n, _ptr(grad), _ptr(loss),
-                                 _ptr(_Ws.buf), _Ws.buf.numel(), _stream()))
+                                 _ptr(ws), ws.numel(), _stream()))
     return loss, grad
 
 
