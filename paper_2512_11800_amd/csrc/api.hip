@@ -633,7 +633,7 @@ int mb_render_forward_surrogate(const mb_gaussians* g, const mb_camera* cams, in
   ra.q_z = q.q_z;
   ra.q_pix = q.q_pix;
   ra.q_f = q.q_f;
-  hipError_t e = hipMemsetAsync(q.count, 0, sizeof(unsigned long long), s);
+  hipError_t e = launch_zero_words(q.count, 2, s);  // a 64-bit count
   if (e != hipSuccess) return hip_fail(e, "query counter reset");
   {
     StageTimer t(S_RENDER_FWD, s);

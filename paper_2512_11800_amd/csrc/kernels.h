@@ -74,6 +74,9 @@ hipError_t launch_adc_plan(int n, const float* scales, const float* dens, const 
                            hipStream_t s);
 hipError_t launch_adc_apply(const AdcApplyArgs& a, hipStream_t s);
 
+// clear n <= 64 32-bit words
+hipError_t launch_zero_words(void* p, int n, hipStream_t s);
+
 // exclusive scan of int32 counts (n items) into out (n items), total in *total.
 // tmp must hold scan_tmp_ints(n) ints.
 size_t scan_tmp_ints(int64_t n);

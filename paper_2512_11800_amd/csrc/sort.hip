@@ -132,12 +132,24 @@ __global__ __launch_bounds__(256) void k_scan_down_direct(const int* in, int* ou
   }
 }
 
+// A kernel, not hipMemsetAsync: callers may capture the frame, and a graph's memset
+// nodes have not been reliable on replays.
+__global__ void k_zero_words(uint32_t* p, int n) {
+  if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
+}
+
+hipError_t launch_zero_words(void* p, int n, hipStream_t s) {
+  if (n > 64) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, (uint32_t*)p, n);
+  return hipGetLastError();
+}
+
 size_t scan_tmp_ints(int64_t n) { return (size_t)((n + kChunk - 1) / kChunk) + 1; }
 
 hipError_t launch_scan(const int* in, int* out, int64_t n, int* tmp, int* total, hipStream_t s) {
   int64_t nb = (n + kChunk - 1) / kChunk;
   if (nb == 0) {
-    if (total) return hipMemsetAsync(total, 0, sizeof(int), s);
+    if (total) return launch_zero_words(total, 1, s);
     return hipSuccess;
   }
   hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kBlock), 0, s, in, n, tmp);
