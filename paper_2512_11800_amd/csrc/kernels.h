@@ -82,11 +82,7 @@ hipError_t launch_zero_words(void* p, int n, hipStream_t s);
 size_t scan_tmp_ints(int64_t n);
 hipError_t launch_scan(const int* in, int* out, int64_t n, int* tmp, int* total, hipStream_t s);
 
-// stable LSD radix sort of (keys, vals) on the low `bits` bits of keys.
-// Buffers *_a hold the input and receive the output; *_b are scratch. The
-// launch is sized for n items; with n_dev the count is min(*n_dev, n), read
-// on the device. identity_vals: the input values are 0, 1, 2, ... and vals_a
-// is not read.
+// ints of scratch (`tmp`) of a radix pass over n items
 size_t radix_tmp_ints(int64_t n);
 // stable LSD radix sort by the low `bits` of the keys, buffers keys[0], keys[1]
 // and vals[0], vals[1] in turn; the result is in the buffers 0, the input keys in

@@ -79,11 +79,6 @@ __device__ __forceinline__ float gelu_d(float x, float& d) {
   d = sg + 2.f * c * x * sg * (1.f - sg) * (1.f + 3.f * a * x2);
   return x * sg;
 }
-__device__ __forceinline__ float gelu(float x) {
-  float d;
-  return gelu_d(x, d);
-}
-
 __device__ __forceinline__ bf16x8 lds_bf16x8(const uint16_t* p) {
   return *reinterpret_cast<const bf16x8*>(p);
 }
@@ -439,7 +434,7 @@ __global__ __launch_bounds__(256, 3) void k_mlp_forward_gather(const MlpPacked* 
 }
 
 // tab [n_pix][n_nodes]: the tabulated schedule's F, for the pixels with an optical
-// depth (54% of the scene of 500k Gaussians at 1920x1080: 3.05 -> 1.84 ms)
+// depth (54% in the case tabulated_network of perf/cases.py: 3.05 -> 1.84 ms)
 __global__ __launch_bounds__(256, 3) void k_mlp_table(const MlpPacked* P, const float* pixfeat, int64_t n_pix,
                                                       int n_nodes, float* tab) {
   mlp_queries(P, n_pix * n_nodes, TableSource(pixfeat, n_pix, n_nodes),

@@ -20,8 +20,9 @@
 // The kernel is bound by VALU issue: per 64 pairs about 3500 issue cycles of pass 2
 // and 1400 of pass 3 beside the queueing. With the queue's state in scalar
 // registers, the near bound's selects out of the way and the pixels' values in LDS
-// it takes 2.21 -> 1.97 ms (K = 4), 3.74 -> 3.15 ms (K = 6) at 500k Gaussians,
-// 1920x1080; the gradients are the same bits.
+// it takes 2.21 -> 1.98 ms (K = 4), 3.74 -> 3.15 ms (K = 6) in the case step_1080p of
+// perf/cases.py (500k Gaussians, 1920x1080); the gradients are the same bits
+// (trigonometric K = 6: equal but for the last bits of the sums).
 #include "render_common.h"
 #include "trig.h"
 
@@ -54,7 +55,7 @@ __device__ __forceinline__ float dphi_fn(float x, float d, float ph) {
 // Edges of one Gaussian's quadrature (App. B) and sigma_i there. A wave without an
 // edge on the near bound takes the short forms here and below: the selects and
 // their masks took 2.06 ms where 2.01 do (K = 4), and with the registers they held
-// 3.41 ms where 3.20 do (K = 6, spills), at 500k Gaussians, 1920x1080.
+// 3.41 ms where 3.20 do (K = 6, spills), in the case step_1080p.
 // FUSED: which operations are fused. The optical depths that the adjoint passes
 // through follow the edges' last bits, and a degenerate pixel's gradients magnify
 // them; the operations are therefore fixed here and do not follow the code around.
@@ -592,13 +593,21 @@ __device__ __forceinline__ void reduce_to_slots(const Window& w, float* gr, int 
 // the windows of its list go to its four waves in turn. Every wave queues all
 // pairs, four windows (a group) at a time, and calls flush(group). The windows are
 // the ordinary form's, and all sums keep their order: the gradients are the same bits.
-// The ordinary form leaves most of the chip idle there (as in the forward kernel):
-// 64 tiles of 128x128 (2000 Gaussians) 167 -> 98 us, 475 of 397x301 (20000) 855 ->
-// 476 us, 1200 of 640x480 (10000 and 100000) 689 -> 584 us and 4.25 -> 3.62 ms (K =
-// 4); K = 6 1088 -> 1016 us and 6.99 -> 7.05 ms there, K = 8 1841 -> 1508 us. Beyond,
-// K = 6 loses: 9.7 -> 10.8 ms at 1900 tiles (100000). Where all tiles are split the
-// two are alike within 2%. Trigonometric K = 4: 296 -> 139 us and 1.60 -> 0.86 ms at
-// 64 and 475 tiles, 9.14 -> 7.91 ms at 1200 (100000).
+// The ordinary form leaves most of the chip idle there (as in the forward kernel).
+// Ordinary -> wide, K = 4, 6 and 8 (three intervals):
+//   64 tiles, 128x128, 2000 Gaussians       166 -> 99, 252 -> 125, 412 -> 175 us
+//   475 tiles, 397x301, 20000               844 -> 489, 1366 -> 768, 2375 -> 1302 us
+//   1200 tiles, 640x480, 10000              651 -> 581, 1063 -> 994, 1828 -> 1544 us
+//   1200 tiles, 100000                      4.20 -> 3.59, 6.94 -> 6.99, 13.9 -> 12.0 ms
+//   1200 tiles, 200000, most of them split  7.66 -> 6.99, 12.7 -> 14.0, 26.0 -> 24.0 ms
+//   1900 tiles, 10000                       760 -> 877, 1250 -> 1519, 2190 -> 2346 us
+//   1900 tiles, 100000                      5.92 -> 5.53, 9.93 -> 11.0, 20.1 -> 19.0 ms
+//   3072 tiles, 10000                       909 -> 1356, 1523 -> 2372, 2942 -> 3684 us
+// Beyond 1200 tiles every variant loses in thin frames. K = 6 loses in dense ones near
+// the line already: its ordinary form has three blocks a compute unit, the wide one
+// two. With five intervals K = 6 gains there (10.6 -> 9.06 ms at 100000), K = 4 loses
+// in thin frames (759 -> 813 us at 10000). Trigonometric K = 4: 296 -> 139 us and 1.59
+// -> 0.87 ms at 64 and 475 tiles, 9.11 -> 7.92 ms at 1200 (100000).
 struct Group {
   int n, base;         // pairs in the group, its first item in the ring of 512
   uint64_t heads[5];   // of the four windows, entry starts only; [4] the next group's
@@ -668,8 +677,8 @@ __device__ __forceinline__ void walk_groups(uint16_t* ring, const uint64_t* mask
 // row of LDS, read by 16-byte loads (rows an odd number of 16 bytes apart, spread
 // over the banks), the others broadcast from the pixel lane's registers. A shuffle
 // a value held 20 more registers through the passes and took 27 LDS instructions
-// a window where 5 loads do: 2.01 -> 1.97 ms (K = 4), 3.20 -> 3.15 ms (K = 6) at
-// 500k Gaussians, 1920x1080 (3 blocks a compute unit: 2 take 2.54 and 3.93 ms, 4
+// a window where 5 loads do: 2.01 -> 1.97 ms (K = 4), 3.20 -> 3.15 ms (K = 6) in the
+// case step_1080p (3 blocks a compute unit: 2 take 2.54 and 3.93 ms, 4
 // with 160 entries staged at a time 1.94 ms but more where lists are long).
 template <int S>
 struct PixelRows {

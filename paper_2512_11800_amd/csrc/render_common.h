@@ -20,11 +20,11 @@ struct RayG {
 
 // ---------------------------------------------------------------------------
 // Per-wave compaction of covering pairs. A wave owns an 8x8 pixel block; while
-// it walks the staged list, the (entry, pixel) pairs that pass the coverage
-// test are appended to a queue in (entry, pixel) order and evaluated 64 at a
-// time, one pair per lane, so the arithmetic runs on full waves whatever the
-// fraction of the block a Gaussian covers. A pair's results go back to the
-// pixel's own lane (the owner), which adds them in queue order: per pixel the
+// it walks the stored coverage masks, (entry, pixel) pairs are appended to a queue,
+// all of them entry by entry (walk_entries) or those of thin rounds (walk_pairs), and
+// evaluated 64 at a time, one pair per lane, so the arithmetic runs on full waves
+// whatever the fraction of the block a Gaussian covers. A pair's results go back to
+// the pixel's own lane (the owner), which adds them in queue order: per pixel the
 // summation order is the list order, as without compaction.
 // ---------------------------------------------------------------------------
 struct WaveQueue {
@@ -272,7 +272,7 @@ __device__ __forceinline__ uint64_t load_masks(const uint64_t* masks, int b, int
   return j < nb ? masks[(size_t)(b + j) * 4 + quad] : 0ull;
 }
 // body(j) for the entries of this lane's word m of chunk c (no cross-lane
-// operations in it): 64 pairs take 1.38 rounds on the 500k-Gaussian 1080p scene,
+// operations in it): 64 pairs take 1.38 rounds in the case step_1080p of perf/cases.py,
 // for the pixels of a block have unequal counts.
 template <class Body>
 __device__ __forceinline__ void word_rounds(uint64_t m, int c, int own4, Body&& body) {
@@ -299,8 +299,8 @@ __device__ __forceinline__ void for_each_own_entry(const uint64_t* masks, int b,
 // a round with kDirectLanes lanes or more is evaluated as it stands, and the
 // pairs of the thinner rounds are queued and evaluated 64 at a time, one per
 // lane, their results sent back to the pixel's own lane. The queue is emptied at
-// the end of each chunk, so a pixel's results still arrive in list order. On the
-// 500k-Gaussian 1080p scene 86% of the pairs are evaluated directly, 97% of
+// the end of each chunk, so a pixel's results still arrive in list order. In the
+// case step_1080p 86% of the pairs are evaluated directly, 97% of
 // their lanes at work; all rounds direct would leave 73% at work, all pairs
 // queued cost a push, thirteen broadcasts and an owner sum each.
 // eval(direct, on, j, p, own): one evaluation for the lanes with `on`, of entry
@@ -375,8 +375,7 @@ __device__ __forceinline__ void walk_pairs(WaveQueue& q, const uint64_t* masks, 
 // is queued under its mask as the execution mask, and the window's segments come
 // from `heads` by scalar logic. Masks fetched with a shuffle, a count in vector
 // registers and a lane's positions by 64-bit selects cost a push about 150 issue
-// cycles, against 50 (2.9 pushes per 64 pairs and pass on the 500k-Gaussian 1080p
-// scene).
+// cycles, against 50 (2.9 pushes per 64 pairs and pass in the case step_1080p).
 struct Window {
   int n;           // pairs in the window
   int base;        // its first item in the ring of 128

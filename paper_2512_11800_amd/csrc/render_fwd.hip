@@ -13,9 +13,9 @@
 // pixel: every lane walks its own pixel's entries (see word_rounds, walk_pairs).
 // The kernel is bound by VALU issue. With the pairs of all three passes queued in
 // (entry, pixel) order and their results summed by owner loops through LDS it
-// took 1.16 ms (K = 4), 1.95 ms (K = 6) at 500k Gaussians, 1920x1080, against
-// 0.90 and 1.62 ms: what went is the queueing, the broadcasts and the owner
-// loops. Every pixel's sums keep their order and every pair its arithmetic: the
+// took 1.17 ms (K = 4), 1.97 ms (K = 6) in the case step_1080p of perf/cases.py (500k
+// Gaussians, 1920x1080), against 0.91 and 1.71 ms: what went is the queueing, the
+// broadcasts and the owner loops. Every pixel's sums keep their order and every pair its arithmetic: the
 // image, the saved state and the moments are the same to the last bit (a
 // degenerate pixel's gradients magnify a changed bit by four decades).
 //
@@ -100,13 +100,19 @@ __device__ __forceinline__ void add_rounded(double& acc, double m) {
 // results, V floats a pair, twice, `half` floats apart (a wave may run one step ahead).
 // eval(j, v): entry j against this lane's pixel; add(v): its share of the sums.
 // In the ordinary form a tile is one block and each quadrant one wave, and few tiles
-// leave most of the chip idle: 64 tiles of 128x128 (2000 Gaussians) 92 -> 62 us, 475
-// of 397x301 (20000) 392 -> 217 us, 1200 of 640x480 (10000 and 100000) 292 -> 258 and
-// 1774 -> 1589 us (K = 4); K = 6 and 8 gain as much or more. Where all tiles are
-// split the two are alike within 2%. Beyond, the lanes without a pair in a step cost
-// more than the waves bring: 1900 tiles 1.06 times as fast with K = 4 but 0.93 with K
-// = 8, 3072 tiles 0.99 and 0.87. Trigonometric K = 4: 217 -> 112 us at 64 tiles, 1.07
-// -> 0.54 ms at 475, 4.56 -> 4.06 ms at 1200 (100000).
+// leave most of the chip idle. Ordinary -> wide, K = 4, 6 and 8 (three intervals):
+//   64 tiles, 128x128, 2000 Gaussians       96 -> 63, 165 -> 98, 314 -> 173 us
+//   475 tiles, 397x301, 20000               401 -> 225, 784 -> 417, 1668 -> 917 us
+//   1200 tiles, 640x480, 10000              299 -> 249, 609 -> 462, 1286 -> 1102 us
+//   1200 tiles, 100000                      1.80 -> 1.55, 3.68 -> 3.27, 8.61 -> 8.31 ms
+//   1200 tiles, 200000, most of them split  3.26 -> 3.04, 6.67 -> 6.41, 15.8 -> 16.6 ms
+//   1900 tiles, 10000                       337 -> 360, 687 -> 678, 1503 -> 1629 us
+//   1900 tiles, 100000                      2.51 -> 2.36, 5.28 -> 5.04, 12.1 -> 13.1 ms
+//   3072 tiles, 10000                       422 -> 541, 860 -> 1037, 1870 -> 2516 us
+// A split tile is the same work in both forms, with K = 8 at two blocks a compute unit
+// instead of three. Beyond 1200 tiles the lanes without a pair in a step cost more than
+// the waves bring. Trigonometric K = 4: 216 -> 108 us at 64 tiles, 1.07 -> 0.55 ms at
+// 475, 4.60 -> 4.19 ms at 1200 (100000).
 template <int V, class Eval, class Add>
 __device__ __forceinline__ void wide_rounds(float* buf, int half, const uint64_t* masks, int b, int nb, int quad, int lane,
                                             int wave, bool live, int& step, Eval&& eval, Add&& add) {
@@ -143,12 +149,16 @@ __device__ __forceinline__ void wide_rounds(float* buf, int half, const uint64_t
 
 template <int K, int NQ, int MODE, bool WIDE = false>
 __global__
-// waves per SIMD: five for K = 4 (0.90 ms against 0.92 ms with four, at the scene
-// above), four for K = 6 (1.62 against 1.75 ms with three) and for the
-// trigonometric K = 4 (0.54 against 0.58 ms with three, 200k Gaussians, 1280x720;
-// fused operations issue slower at an odd number of waves), three beyond, where
-// four spill (K = 8, five intervals: 0.83 against 0.86 ms). The wide form: as many
-// as its LDS and registers allow without spills.
+// waves per SIMD: five for K = 4 (0.91 ms against 0.92 ms with four, in the case above),
+// four for K = 6 (1.71 against 1.85 ms with three) and for the trigonometric K = 4
+// (0.54 against 0.59 ms with three, 200k Gaussians, 1280x720; fused operations issue
+// slower at an odd number of waves), three beyond. The same with five intervals, where
+// they spill 16 (K = 4), 11 (K = 6) and 22 registers (trigonometric) and the fewer
+// waves none: K = 4 1.15 ms either way in the case above, 0.21 against 0.19 ms with
+// four (100k Gaussians, 1003x757); K = 6 2.39 against 2.48 and 0.41 against 0.40 ms with
+// three; trigonometric K = 4 0.71 against 0.77 ms with three (1280x720). K = 8 with
+// five intervals: 0.85 ms with three, 0.90 with four (1003x757), 5.5 and 5.4 ms in the
+// case above. The wide form: as many as its LDS and registers allow without spills.
 __launch_bounds__(256, WIDE ? (MODE == kModeTrig ? 2 : (K == 4 ? 4 : (K == 6 ? 3 : 2))) : (K == 4 ? (MODE == kModeTrig ? 4 : 5) : (K == 6 && MODE == kModePlain ? 4 : 3)))
 void k_render_fwd(RenderArgs a, CamSet cams) {
   constexpr int NH = K / 2;
