@@ -17,7 +17,8 @@
 // Gaussians, 1920x1080), against 0.91 and 1.71 ms: what went is the queueing, the
 // broadcasts and the owner loops. Every pixel's sums keep their order and every pair its arithmetic: the
 // image, the saved state and the moments are the same to the last bit (a
-// degenerate pixel's gradients magnify a changed bit by four decades).
+// degenerate pixel's gradients magnify a changed bit by four decades), except where
+// a Gaussian reaches over the near bound: the edges moved there round in another order.
 //
 // Variants (MODE):
 //   kModePlain    the path above;
